@@ -105,6 +105,16 @@ int32_t e2eg_normalize(int32_t n, int64_t nnz, const int32_t* d_row_ptr,
                        const int32_t* d_col_idx, int32_t* d_deg, float* d_dinv_sqrt,
                        void* d_sched, size_t sched_bytes, void* ws, size_t ws_bytes, void* stream);
 
+/* e2eg_normalize_built: e2eg_normalize (d_val NULL; d_deg_w is then not looked at) or
+ * e2eg_normalize_weighted (d_val given) for a CSR that e2eg_build_csr made, unchanged, with values, if any,
+ * from e2eg_edge_weights: such a structure is symmetric by construction, so the test for it (see
+ * e2eg_sched_check_symmetric) is not run and the schedule says "symmetric".  On anything else the transposed
+ * entry points would silently apply the stored operator instead of its transpose.
+ */
+int32_t e2eg_normalize_built(int32_t n, int64_t nnz, const int32_t* d_row_ptr, const int32_t* d_col_idx,
+                             const float* d_val, int32_t* d_deg, float* d_deg_w, float* d_dinv_sqrt,
+                             void* d_sched, size_t sched_bytes, void* ws, size_t ws_bytes, void* stream);
+
 /* e2eg_sched_check_symmetric: may the transposed entry points (e2eg_propagate_bwd,
  * e2eg_propagate_weighted_bwd, e2eg_aggregate with E2EG_AGG_MEAN_T) run on this schedule?  They
  * apply the stored operator itself, which equals its transpose (Appendix A: the backward pass
@@ -286,8 +296,7 @@ int32_t e2eg_gradnorm_step(int32_t T, const double* h_loss, const double* h_loss
  * stored entries of row i; d_deg_w[i] (may be NULL) = d~_i = the sum of row i of d_val, added in
  * double in a fixed order; d_dinv_sqrt[i] = (float)(1 / sqrt(d~_i)), 0 where the sum is not positive.  d_sched needs e2eg_sched_weighted_bytes(n, nnz)
  * bytes: the unweighted schedule followed by the values in the library's own entry order.  Each
- * row must hold a column at most once (a repeat leaves one of the values out).  The workspace is
- * that of e2eg_normalize.
+ * row must hold a column at most once.  The workspace is that of e2eg_normalize.
  *
  * e2eg_propagate_weighted_fwd / _bwd: e2eg_propagate_fwd / _bwd, argument for argument, on a
  * schedule made by e2eg_normalize_weighted; each gathered row is multiplied by its entry's value

@@ -39,6 +39,7 @@ SIGNATURES = {
     "e2eg_sched_bytes": (_sz, [_i32, _i64]),
     "e2eg_normalize_workspace_bytes": (_sz, [_i32, _i64]),
     "e2eg_normalize": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _vp, _sz, _vp, _sz, _vp]),
+    "e2eg_normalize_built": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _sz, _vp, _sz, _vp]),
     "e2eg_propagate_workspace_bytes": (_sz, [_i32, _i64, _i32, _i32, _i32]),
     "e2eg_propagate_fwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _i64, _vp, _i64, _i64, _vp, _sz, _vp]),
     "e2eg_propagate_bwd": (_i32, [_i32, _i64, _vp, _vp, _vp, _vp, _i32, _i32, _i32, _vp, _i64, _vp, _i64, _vp, _i64, _vp, _sz, _vp]),
@@ -156,6 +157,14 @@ def e2eg_normalize(n, nnz, d_row_ptr, d_col_idx, d_deg, d_dinv_sqrt, d_sched, sc
                                          _ptr(d_sched),
                                          _nbytes(d_sched) if sched_bytes is None else sched_bytes, _ptr(ws),
                                          _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+
+
+def e2eg_normalize_built(n, nnz, d_row_ptr, d_col_idx, d_val, d_deg, d_deg_w, d_dinv_sqrt, d_sched, sched_bytes, ws,
+                         ws_bytes=None, stream=0):
+    _check(load_library().e2eg_normalize_built(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_val), _ptr(d_deg),
+                                               _ptr(d_deg_w), _ptr(d_dinv_sqrt), _ptr(d_sched),
+                                               _nbytes(d_sched) if sched_bytes is None else sched_bytes, _ptr(ws),
+                                               _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
 
 
 def e2eg_propagate_workspace_bytes(n, nnz, dtype, F, K) -> int:

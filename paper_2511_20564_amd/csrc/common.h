@@ -84,11 +84,17 @@ int32_t radix_sort_u64(uint64_t** src, uint64_t** dst, int64_t count, int lo, in
 int bits_for(int64_t count);  // bits needed to represent ids 0 .. count-1 (at least 1)
 
 // ---- schedule shared by normalize.hip (writer) and propagate.hip (reader) ------------------
-// The propagation kernels work on a private copy of the graph with renumbered nodes ("internal"
-// ids): the kTopNodes nodes of highest degree come first, by descending degree (ties in node
-// order); all other nodes follow in node order.  Popular nodes, whose feature rows are read most
-// often, so have the lowest ids, sit at the front of every neighbour list, and their feature rows
-// are one contiguous block.
+// Two forms, chosen by the number of stored entries alone (sched_is_small), so that writer and
+// readers agree without asking the device.
+//
+// Large graphs: the propagation kernels work on a private copy of the graph with renumbered nodes
+// ("internal" ids): kTopNodes nodes of highest degree come first, by descending degree (ties in
+// node order); all other nodes follow in node order.  Popular nodes, whose feature rows are read
+// most often, so have the lowest ids, sit at the front of every neighbour list, and their feature
+// rows are one contiguous block.
+// Small graphs (the subgraph of a mini-batch step, used once): rows keep their node ids, and only the
+// neighbour lists are copied, popular neighbours first as above.  A feature table of a few tens of MB
+// gains nothing from renumbered rows, and making them costs more than the layers that use them.
 //
 // Work is cut in two ways.  Rows with at most kShortMax entries ("short") are listed in
 // `short_rows`, ordered by length inside blocks of kSortBlock consecutive rows: a wavefront
@@ -99,8 +105,7 @@ int bits_for(int64_t count);  // bits needed to represent ids 0 .. count-1 (at l
 constexpr int kShortMax = 128;         // longest row summed by a single lane group
 constexpr int kSegLen = 512;           // longest run of CSR entries summed by one wavefront
 constexpr int kSortBlock = 4096;       // short rows are ordered by length within such blocks
-constexpr int kHotBytes = 128 * 1024;
-constexpr int kTopNodes = kHotBytes / 16;  // nodes renumbered to the front, by descending degree
+constexpr int kTopNodes = 8192;        // nodes renumbered to the front, by descending degree
 // The longest rows ("wide": among the first kMaxWide internal rows, and at least
 // kWideFactor entries per window on average) are cut at the boundaries of windows of kWindow
 // consecutive internal ids before they are cut by length: a segment then reads feature rows of
@@ -109,6 +114,9 @@ constexpr int kWindow = 8192;
 constexpr int kMaxWide = 1024;
 constexpr int kWideFactor = 16;
 constexpr int kXcds = 8;
+constexpr int64_t kSmallNnz = 1 << 20;   // up to here the small form
+
+inline bool sched_is_small(int64_t nnz) { return nnz <= kSmallNnz; }
 
 struct alignas(16) Segment {
     int32_t row;   // internal row
@@ -119,8 +127,8 @@ struct alignas(16) Segment {
 
 struct SchedHeader {
     int32_t n_short;   // rows with at most kShortMax entries
-    int32_t n_seg;     // all segments
-    int32_t n_slot;    // segments of rows cut into several = partial-sum slots = the first n_slot of `segs`
+    int32_t n_single;  // rows of one segment
+    int32_t n_slot;    // segments of rows cut into several = partial-sum slots
     int32_t n_multi;   // rows cut into several segments
     int32_t n;
     int32_t nnz;
@@ -128,7 +136,9 @@ struct SchedHeader {
     int32_t pad;
     int32_t xcd_first[kXcds + 1];  // the slotted segments dealt out by equal entry counts: XCD x
                                    // owns segs[xcd_first[x] .. xcd_first[x + 1])
-    int32_t pad2[7];
+    int32_t n_slot_plain;          // those of the n_slot that belong to rows cut by length only
+    int32_t n_chunks;              // large form: pieces of split rows (see normalize.hip)
+    int32_t pad2[5];
 };
 
 // header.flags: the stored structure holds an entry (i, j) without (j, i); the values of a weighted
@@ -138,19 +148,21 @@ constexpr int32_t kSchedValuesNotSymmetric = 2;
 
 struct SchedView {
     SchedHeader* header;
-    int32_t* orig;        // [n] node at internal position p
-    int32_t* zpos;        // [n] internal position of node i
-    int32_t* zrow_ptr;    // [n + 1] row pointers of the internal CSR
-    int32_t* zcol;        // [nnz] internal column ids, ascending within each row
+    int32_t* orig;        // [n] node at internal position p (small form: null, p itself)
+    int32_t* zpos;        // [n] internal position of node i (small form: null)
+    int32_t* zrow_ptr;    // [n + 1] row pointers of the internal CSR (small form: the caller's)
+    int32_t* zcol;        // [nnz] internal column ids; in each row the popular ones first, by popularity, then
+                          // the others in the caller's order (small form: the same array as znode)
     int32_t* short_rows;  // [n] internal rows with at most kShortMax entries, processing order
     int32_t* multi_row;   // [max_multi] internal rows cut into several segments, ascending
     int32_t* slot_base;   // [max_multi] first slot of each such row
     int32_t* slot_cnt;    // [max_multi] number of slots
-    Segment* segs;        // [max_seg]: slotted segments ordered by first column, then one-segment rows
+    Segment* singles;     // [max_plain] rows of one segment, in row order
+    Segment* segs;        // [max_slot] slotted segments, by the window of their first column (small form: by row)
     float* zval;          // [nnz] entry values in zcol order (weighted schedules only, else null)
     int32_t* znode;       // [nnz] orig[zcol[e]]: the column of entry e as a node id
     float* zs;            // [nnz] d~^-1/2 of that node (times the entry's value on a weighted graph)
-    int64_t max_plain, max_seg, max_multi, max_slot;
+    int64_t max_plain, max_multi, max_slot;
 };
 
 // Upper bounds that depend on (n, nnz) only, so that launches need no device read-back.
@@ -159,14 +171,17 @@ inline int64_t sched_wide_threshold(int64_t n) {
     const int64_t t = (int64_t)kWideFactor * sched_windows(n);
     return t > kSegLen ? t : kSegLen + 1;
 }
-inline int64_t sched_max_wide_rows(int64_t n) { return n < kMaxWide ? n : kMaxWide; }
-inline int64_t sched_max_pairs(int64_t n) { return sched_max_wide_rows(n) * sched_windows(n); }
+inline int64_t sched_max_wide_rows(int64_t n, int64_t nnz) {
+    if (sched_is_small(nnz)) return 0;
+    return n < kMaxWide ? n : kMaxWide;
+}
+inline int64_t sched_max_pairs(int64_t n, int64_t nnz) { return sched_max_wide_rows(n, nnz) * sched_windows(n); }
 inline int64_t sched_max_plain(int64_t nnz) { return nnz / (kShortMax + 1) + 1; }  // rows cut by length only
 inline int64_t sched_max_multi(int64_t nnz) { return nnz / (kSegLen + 1) + 1; }
 inline int64_t sched_max_slot(int64_t n, int64_t nnz) {
-    return nnz / kSegLen + sched_max_multi(nnz) + sched_max_pairs(n) + 1;
+    return nnz / kSegLen + sched_max_multi(nnz) + sched_max_pairs(n, nnz) + 1;
 }
-inline int64_t sched_max_seg(int64_t n, int64_t nnz) { return sched_max_slot(n, nnz) + sched_max_plain(nnz); }
-size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool weighted = false);
+// row_ptr: the caller's, which a small schedule refers to.
+size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool weighted, const int32_t* row_ptr);
 
 }  // namespace e2eg

@@ -164,6 +164,12 @@ __device__ __forceinline__ float row_scale(const LayerArgs<T>& a, int32_t node, 
     return refuse ? __builtin_nanf("") : a.dinv_sqrt[node];
 }
 
+// The node at an internal row (a small schedule keeps node order and has no array for it).
+template <typename T>
+__device__ __forceinline__ int32_t node_of(const LayerArgs<T>& a, int32_t zrow) {
+    return a.sched.orig ? a.sched.orig[zrow] : zrow;
+}
+
 // Accumulators of one lane: acc[v] holds this lane's 16-byte chunk as fp32.
 template <typename T>
 struct Sum {
@@ -281,7 +287,7 @@ __device__ __forceinline__ void run_segment(const LayerArgs<T>& a, const Segment
     int32_t node = 0;
     float s = 0.0f;
     if (seg.slot < 0) {  // requested now, needed after the gathers
-        node = a.sched.orig[seg.row];
+        node = node_of(a, seg.row);
         s = row_scale<T>(a, node, refuse);
     }
     // What a lane without a neighbour gathers: the all-zero row of a Z buffer; kFirst, whose table has
@@ -436,8 +442,8 @@ constexpr int kShortPerWave = 8;   // short rows a wavefront works through, 64/G
 constexpr int kSingleBlocksPerXcd = 512;  // B-workgroups per XCD (fewer when the graph cannot have that many such rows)
 
 // Three kinds of workgroup.
-// A. Segments of rows cut into several (the first n_slot entries of the ordered segment list,
-//    ordered by first column), one per wavefront.  The schedule deals the list out to the XCDs in
+// A. Segments of rows cut into several (ordered by the window of their first column), one per
+//    wavefront.  The schedule deals the list out to the XCDs in
 //    contiguous stretches of equal entry counts; the A-workgroups of XCD x take the segments of
 //    stretch x in order, so the segments in flight on an XCD are consecutive ones, read the same
 //    window of feature rows, and share it in that XCD's L2.  The launch is sized so that each
@@ -498,18 +504,22 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
     }
     const int64_t o = j - n_a;                           // position among the B- and C-workgroups
     if (o < n_b) {
-        const int64_t lo = h->n_slot, hi = h->n_seg;
+        const int64_t hi = h->n_single;
         const int64_t waves = n_b * kXcds * kWaves;
-        const int64_t per_wave = (hi - lo + waves - 1) / waves;
-        const int64_t first = lo + ((o * kXcds + x) * kWaves + wave) * per_wave;
+        const int64_t per_wave = (hi + waves - 1) / waves;
+        const int64_t first = ((o * kXcds + x) * kWaves + wave) * per_wave;
         const int64_t last = first + per_wave < hi ? first + per_wave : hi;
 #pragma unroll 1
-        for (int64_t t = first; t < last; ++t) run_segment<T, LOG_G, NARROW, MODE>(a, a.sched.segs[t], lane, refuse);
+        for (int64_t t = first; t < last; ++t) run_segment<T, LOG_G, NARROW, MODE>(a, a.sched.singles[t], lane, refuse);
         return;
     }
-    const int64_t rb = (o - n_b) * kXcds + x;
+    // a small schedule lists users before items: from its end, the long item rows come first and the short
+    // user rows fill the gaps (in node order the launch ended with a tail: 62 against 43 us on a sampled
+    // subgraph of 175 k nodes)
+    int64_t rb = (o - n_b) * kXcds + x;
+    if (!a.sched.orig) rb = c_total - 1 - rb;
     const int64_t n_short = a.sched.header->n_short;
-    const int64_t first = ((int64_t)rb * kWaves + wave) * kShortPerWave;
+    const int64_t first = (rb * kWaves + wave) * kShortPerWave;
     if (first >= n_short) return;
     const int n_rows = n_short - first < kShortPerWave ? (int)(n_short - first) : kShortPerWave;
     int32_t my_row = 0, my_beg = 0, my_len = -1, my_node = 0;
@@ -518,7 +528,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
         my_row = a.sched.short_rows[first + lane];
         my_beg = a.sched.zrow_ptr[my_row];
         my_len = a.sched.zrow_ptr[my_row + 1] - my_beg;
-        my_node = a.sched.orig[my_row];
+        my_node = node_of(a, my_row);
         my_s = row_scale<T>(a, my_node, refuse);
     }
     const int c = lane & (G - 1);
@@ -563,7 +573,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_split_rows(const LayerA
     const bool refuse = refused<T>(a);
     for (int32_t m = blockIdx.x; m < n_multi; m += gridDim.x) {
     const int32_t k = a.sched.multi_row[m];  // internal row
-    const int32_t node = a.sched.orig[k];
+    const int32_t node = node_of(a, k);
     const int32_t base = a.sched.slot_base[m];
     const int32_t cnt = a.sched.slot_cnt[m];
     const float s = row_scale<T>(a, node, refuse);
@@ -607,7 +617,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_split_rows(const LayerA
 
 constexpr int kPrescaleThreads = 256;
 
-constexpr int64_t kDirectMaxNnz = 1 << 20;   // see run_layers
+constexpr int64_t kDirectMaxNnz = kSmallNnz;   // see run_layers
 constexpr int kPrescaleRows = 4;   // rows per thread: their dependent loads (row -> node -> x, s) overlap
 
 // Z = S_in X in internal row order: one streaming pass, 16 bytes of kPrescaleRows rows per thread.
@@ -632,7 +642,7 @@ __global__ __launch_bounds__(kPrescaleThreads) void prescale_rows(const typename
 #pragma unroll
     for (int i = 0; i < kPrescaleRows; ++i) {
         const int64_t zrow = group * kPrescaleRows + i;
-        node[i] = zrow < n ? orig[zrow] : -1;
+        node[i] = zrow >= n ? -1 : orig ? orig[zrow] : zrow;
     }
     float v[kPrescaleRows][V];
     float s[kPrescaleRows];
@@ -773,7 +783,7 @@ int32_t run_layers(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t
                    bool weighted, bool transposed, hipStream_t stream) {
     using E = typename T::elem;
     SchedView view;
-    sched_carve(const_cast<void*>(sched), n, nnz, &view, weighted);
+    sched_carve(const_cast<void*>(sched), n, nnz, &view, weighted, row_ptr);
     // Layer l > 1 reads Z(l-1), which layer l-1 wrote into one of the two Z buffers (each launch also
     // writes the all-zero row of the buffer it fills).  Layer 1 reads either Z(0), made by a streaming
     // pre-scale pass, or the caller's rows themselves (kFirst).  The direct form saves that pass
@@ -872,7 +882,7 @@ int32_t run_aggregate(int32_t mode, int32_t n, int64_t nnz, const int32_t* row_p
                       const AggWs& w, hipStream_t stream) {
     using E = typename T::elem;
     SchedView view;
-    sched_carve(const_cast<void*>(sched), n, nnz, &view);
+    sched_carve(const_cast<void*>(sched), n, nnz, &view, false, row_ptr);
     aggregate_scales<<<dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, stream>>>(row_ptr, n, mode, w.scale_in,
                                                                                 w.scale_out);
     E2EG_LAUNCH_CHECK("aggregate_scales");

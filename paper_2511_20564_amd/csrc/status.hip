@@ -49,26 +49,34 @@ int32_t fail(int32_t status, const char* fmt, ...) {
     return status;
 }
 
-size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool weighted) {
+size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool weighted, const int32_t* row_ptr) {
     Carver c(base);
     SchedView v;
+    const bool small = sched_is_small(nnz);
+    const int64_t entries = nnz > 0 ? nnz : 1;
     v.max_plain = sched_max_plain(nnz);
-    v.max_seg = sched_max_seg(n, nnz);
     v.max_multi = sched_max_multi(nnz);
     v.max_slot = sched_max_slot(n, nnz);
     v.header = c.take<SchedHeader>(1);
-    v.orig = c.take<int32_t>(n > 0 ? n : 1);
-    v.zpos = c.take<int32_t>(n > 0 ? n : 1);
-    v.zrow_ptr = c.take<int32_t>(n + 1);
-    v.zcol = c.take<int32_t>(nnz > 0 ? nnz : 1);
     v.short_rows = c.take<int32_t>(n > 0 ? n : 1);
     v.multi_row = c.take<int32_t>(v.max_multi);
     v.slot_base = c.take<int32_t>(v.max_multi);
     v.slot_cnt = c.take<int32_t>(v.max_multi);
-    v.segs = c.take<Segment>(v.max_seg);
-    v.znode = c.take<int32_t>(nnz > 0 ? nnz : 1);
-    v.zs = c.take<float>(nnz > 0 ? nnz : 1);
-    v.zval = weighted ? c.take<float>(nnz > 0 ? nnz : 1) : nullptr;  // last: the rest of the layout is shared
+    v.singles = c.take<Segment>(v.max_plain);
+    v.segs = c.take<Segment>(v.max_slot);
+    v.znode = c.take<int32_t>(entries);
+    v.zs = c.take<float>(entries);
+    if (small) {
+        v.orig = v.zpos = nullptr;
+        v.zrow_ptr = const_cast<int32_t*>(row_ptr);
+        v.zcol = v.znode;
+    } else {
+        v.orig = c.take<int32_t>(n > 0 ? n : 1);
+        v.zpos = c.take<int32_t>(n > 0 ? n : 1);
+        v.zrow_ptr = c.take<int32_t>(n + 1);
+        v.zcol = c.take<int32_t>(entries);
+    }
+    v.zval = weighted ? c.take<float>(entries) : nullptr;  // last: the rest of the layout is shared
     if (view) *view = v;
     return c.size();
 }

@@ -48,7 +48,7 @@ class Graph:
     deg_w: torch.Tensor | None = None  # float32 [n]: d~ of a weighted graph (then `deg` is the row length)
 
 
-def normalize(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.Tensor):
+def normalize(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.Tensor, _built: bool = False):
     """e2eg_normalize on an existing CSR -> (deg, dinv_sqrt, sched)."""
     _require_gpu()
     dev = row_ptr.device
@@ -56,7 +56,10 @@ def normalize(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.Tensor):
     dinv = torch.empty(n, dtype=torch.float32, device=dev)
     sched = _bytes(B.e2eg_sched_bytes(n, nnz), dev)
     ws = _bytes(B.e2eg_normalize_workspace_bytes(n, nnz), dev)
-    B.e2eg_normalize(n, nnz, row_ptr, col_idx, deg, dinv, sched, None, ws, None, _stream())
+    if _built:
+        B.e2eg_normalize_built(n, nnz, row_ptr, col_idx, None, deg, None, dinv, sched, None, ws, None, _stream())
+    else:
+        B.e2eg_normalize(n, nnz, row_ptr, col_idx, deg, dinv, sched, None, ws, None, _stream())
     return deg, dinv, sched
 
 
@@ -83,11 +86,12 @@ def build_graph(n_users: int, n_items: int, users: torch.Tensor, items: torch.Te
     nnz = B.e2eg_build_csr(n_users, n_items, n_edges, users, items, flags, row_ptr, col, cap, ws, None, _stream())
     del ws
     col_idx = col[:nnz]
-    deg, dinv, sched = normalize(n, nnz, row_ptr, col_idx)
+    deg, dinv, sched = normalize(n, nnz, row_ptr, col_idx, _built=True)
     return Graph(n_users, n_items, n, nnz, row_ptr, col_idx, deg, dinv, sched)
 
 
-def normalize_weighted(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.Tensor, val: torch.Tensor):
+def normalize_weighted(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.Tensor, val: torch.Tensor,
+                       _built: bool = False):
     """e2eg_normalize_weighted on an existing CSR with values -> (deg, deg_w, dinv_sqrt, sched)."""
     _require_gpu()
     assert val.dtype == torch.float32 and val.is_contiguous() and val.numel() >= nnz
@@ -97,7 +101,8 @@ def normalize_weighted(n: int, nnz: int, row_ptr: torch.Tensor, col_idx: torch.T
     dinv = torch.empty(n, dtype=torch.float32, device=dev)
     sched = _bytes(B.e2eg_sched_weighted_bytes(n, nnz), dev)
     ws = _bytes(B.e2eg_normalize_workspace_bytes(n, nnz), dev)
-    B.e2eg_normalize_weighted(n, nnz, row_ptr, col_idx, val, deg, deg_w, dinv, sched, None, ws, None, _stream())
+    fn = B.e2eg_normalize_built if _built else B.e2eg_normalize_weighted
+    fn(n, nnz, row_ptr, col_idx, val, deg, deg_w, dinv, sched, None, ws, None, _stream())
     return deg, deg_w, dinv, sched
 
 
@@ -122,7 +127,7 @@ def build_weighted_graph(n_users: int, n_items: int, users: torch.Tensor, items:
     col_idx = col[:nnz]
     val = torch.empty(max(nnz, 1), dtype=torch.float32, device=dev)[:nnz]
     B.e2eg_edge_weights(n_users, n_items, n_edges, users, items, weights, nnz, row_ptr, col_idx, val, _stream())
-    deg, deg_w, dinv, sched = normalize_weighted(n, nnz, row_ptr, col_idx, val)
+    deg, deg_w, dinv, sched = normalize_weighted(n, nnz, row_ptr, col_idx, val, _built=True)
     return Graph(n_users, n_items, n, nnz, row_ptr, col_idx, deg, dinv, sched, val, deg_w)
 
 
