@@ -2,13 +2,18 @@
 // "Notation"; A_ij > 0 iff (i,j) in E, so repeated pairs are one edge).
 //
 // Design for the GPU: everything is integer work and deterministic.
-//   1. pack each pair into a 64-bit key (user << 32 | item), checking id ranges;
-//   2. LSD radix sort (8-bit digits, only the bits the id ranges use) -> (user, item) order;
-//   3. drop repeats (head flags, prefix sum, compaction) -> E distinct pairs;
-//   4. user rows are read off directly: a user's items are a contiguous, ascending run;
-//   5. swap the key halves and sort stably by item -> (item, user) order gives the item rows;
-//   6. degrees come from run boundaries (no atomics), row_ptr from a prefix sum.
-#include "common.h"
+//   1. LSD radix sort of the keys (user, item), packed into as few bits as the id ranges need; the
+//      first pass reads the caller's pairs and checks the id ranges;
+//   2. drop repeats (heads counted per tile, then compacted) -> distinct pairs; the same pass writes the
+//      user rows (a user's items are a contiguous, ascending run), notes where each user's run starts and
+//      ends, and turns the keys round to (item, user);
+//   3. stable radix sort by item; the last pass writes the item rows and counts them;
+//   4. row_ptr from a prefix sum of the counts, the diagonal beside it.
+// The number of distinct pairs is known on the device only; launches are sized by the number of pairs
+// given, and the host waits once, at the end.
+// Bound by HBM for large graphs (8 sort passes of 16 bytes read and 8 written per pair), by the number
+// of launches for small ones.
+#include "radix.h"
 
 namespace e2eg {
 namespace {
@@ -19,84 +24,220 @@ inline unsigned blocks_for(int64_t count, int per_block) {
     return (unsigned)ceil_div(count > 0 ? count : 1, per_block);
 }
 
-__global__ void fill_i32(int32_t* p, int64_t count, int32_t v) {
+__global__ void zero_i32(int32_t* p, int64_t count) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = v;
+    if (i < count) p[i] = 0;
 }
 
-__global__ void pack_pairs(const int32_t* __restrict__ users, const int32_t* __restrict__ items,
-                           int64_t n_edges, int32_t n_users, int32_t n_items,
-                           uint64_t* __restrict__ keys, int32_t* __restrict__ bad) {
-    int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n_edges) return;
-    int32_t u = users[e], i = items[e];
-    if (u < 0 || u >= n_users || i < 0 || i >= n_items) {
-        atomicOr(bad, 1);
-        u = 0;
-        i = 0;
+// The caller's pairs as keys (user << item_bits | item); ids out of range are reported (once, by the first
+// pass's histogram) and read as 0.
+struct PairsIn {
+    const int32_t* users;
+    const int32_t* items;
+    int32_t n_users, n_items;
+    int item_bits;
+    int32_t* bad;
+    __device__ __forceinline__ bool ok(int32_t u, int32_t i) const {
+        return (uint32_t)u < (uint32_t)n_users && (uint32_t)i < (uint32_t)n_items;
     }
-    keys[e] = ((uint64_t)(uint32_t)u << 32) | (uint32_t)i;
+    __device__ __forceinline__ uint64_t load(int64_t e) const {
+        const int32_t u = users[e], i = items[e];
+        return ok(u, i) ? ((uint64_t)(uint32_t)u << item_bits) | (uint32_t)i : 0ull;
+    }
+    __device__ __forceinline__ void check(int64_t e) const {
+        if (!ok(users[e], items[e])) atomicOr(bad, 1);
+    }
+};
+
+// Sorted (item, user) keys -> item rows: key k of the list lands behind the user rows and the earlier
+// items' diagonal entries.
+struct ItemRowsOut {
+    static constexpr bool kRuns = true;
+    int32_t* col_idx;
+    const int32_t* pairs;   // number of distinct pairs
+    int32_t* counts;        // per item, cleared
+    int64_t n_users;
+    int32_t self;
+    int user_bits;
+    __device__ __forceinline__ int32_t group(uint64_t key) const { return (int32_t)(key >> user_bits); }
+    __device__ __forceinline__ void store(int64_t at, uint64_t key) const {
+        const int64_t row0 = *pairs + (n_users + group(key)) * self;
+        col_idx[row0 + at] = (int32_t)(key & ((1ull << user_bits) - 1));
+    }
+};
+
+// ---- repeats -------------------------------------------------------------------------------------
+constexpr int kHeadThreads = 512;
+constexpr int kHeadRounds = 8;
+constexpr int kHeadTile = kHeadThreads * kHeadRounds;
+constexpr int kHeadWaves = kHeadThreads / 64;
+constexpr int64_t kHeadFew = 1024;   // up to this many tiles every workgroup adds up the counts before it
+
+// Keys that differ from their predecessor, per tile.
+__global__ __launch_bounds__(kHeadThreads) void count_heads(const uint64_t* __restrict__ keys, int64_t count,
+                                                            int32_t* __restrict__ tile_cnt) {
+    __shared__ int32_t red[kHeadWaves];
+    const int64_t base = (int64_t)blockIdx.x * kHeadTile;
+    int32_t heads = 0;
+#pragma unroll
+    for (int r = 0; r < kHeadRounds; ++r) {
+        const int64_t k = base + r * kHeadThreads + threadIdx.x;
+        heads += __popcll(__ballot(k < count && (k == 0 || keys[k] != keys[k - 1])));
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = heads;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int w = 0; w < kHeadWaves; ++w) t += red[w];
+        tile_cnt[blockIdx.x] = t;
+    }
 }
 
-__global__ void head_flags(const uint64_t* __restrict__ keys, int64_t count,
-                           int32_t* __restrict__ flags) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count) flags[k] = (k == 0 || keys[k] != keys[k - 1]) ? 1 : 0;
+// The distinct pairs: turned round for the second sort, and as user rows (pair k lands behind its user's
+// diagonal entry).  SCANNED: tile_cnt holds the counts before each tile, else the tiles' own.
+template <bool SCANNED>
+__global__ __launch_bounds__(kHeadThreads) void emit_pairs(const uint64_t* __restrict__ keys, int64_t count,
+                                                           const int32_t* __restrict__ tile_cnt, int user_bits,
+                                                           int item_bits, int32_t n_users, int32_t self,
+                                                           uint64_t* __restrict__ turned, int32_t* __restrict__ col_idx,
+                                                           int32_t* __restrict__ run_start, int32_t* __restrict__ run_end,
+                                                           int32_t* __restrict__ n_pairs) {
+    __shared__ int32_t red[kHeadWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    int32_t before = 0;
+    if (SCANNED) {
+        before = tile_cnt[blockIdx.x];
+    } else {
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kHeadThreads) before += tile_cnt[t];
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        if (lane == 0) red[wave] = before;
+        __syncthreads();
+        before = 0;
+#pragma unroll
+        for (int w = 0; w < kHeadWaves; ++w) before += red[w];
+        __syncthreads();
+    }
+    const int64_t base = (int64_t)blockIdx.x * kHeadTile + (int64_t)wave * (64 * kHeadRounds);
+    uint64_t key[kHeadRounds], bal[kHeadRounds];
+    bool first_of_user[kHeadRounds], last_of_user[kHeadRounds];
+    int32_t mine = 0;
+#pragma unroll
+    for (int r = 0; r < kHeadRounds; ++r) {
+        const int64_t k = base + r * 64 + lane;
+        key[r] = k < count ? keys[k] : 0ull;
+        const uint64_t prev = k > 0 && k < count ? keys[k - 1] : 0ull;
+        const uint64_t next = k + 1 < count ? keys[k + 1] : 0ull;
+        bal[r] = __ballot(k < count && (k == 0 || key[r] != prev));
+        first_of_user[r] = k < count && (k == 0 || (prev >> item_bits) != (key[r] >> item_bits));
+        last_of_user[r] = k < count && (k + 1 == count || (next >> item_bits) != (key[r] >> item_bits));
+        mine += __popcll(bal[r]);
+    }
+    if (lane == 0) red[wave] = mine;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kHeadWaves; ++w)
+        if (w < wave) before += red[w];
+#pragma unroll
+    for (int r = 0; r < kHeadRounds; ++r) {
+        const int64_t k = base + r * 64 + lane;
+        const int32_t pos = before + __popcll(bal[r] & lt_mask);
+        const bool head = (bal[r] >> lane) & 1;
+        before += __popcll(bal[r]);
+        const uint32_t u = (uint32_t)(key[r] >> item_bits);
+        const uint32_t i = (uint32_t)(key[r] & ((1ull << item_bits) - 1));
+        if (head) {
+            turned[pos] = ((uint64_t)i << user_bits) | u;
+            col_idx[pos + (int64_t)(u + 1) * self] = n_users + (int32_t)i;
+        }
+        if (first_of_user[r]) run_start[u] = pos;
+        if (last_of_user[r]) run_end[u] = pos + (head ? 1 : 0);
+        if (k == count - 1) *n_pairs = pos + (head ? 1 : 0);
+    }
 }
 
-__global__ void compact_heads(const uint64_t* __restrict__ keys, int64_t count,
-                              const int32_t* __restrict__ pos, uint64_t* __restrict__ out) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count && (k == 0 || keys[k] != keys[k - 1])) out[pos[k]] = keys[k];
+// ---- row pointers ----------------------------------------------------------------------------------
+// Row v holds run_end[v] - run_start[v] entries (items: the count is in run_end, run_start is 0) and the
+// diagonal.  Tiles of kRowTile rows; SCANNED as above.
+constexpr int kRowThreads = 256;
+constexpr int kRowItems = 8;
+constexpr int kRowTile = kRowThreads * kRowItems;
+constexpr int64_t kRowFew = 2048;
+
+__global__ __launch_bounds__(kRowThreads) void row_sums(const int32_t* __restrict__ start, const int32_t* __restrict__ end,
+                                                        int64_t n, int32_t self, int32_t* __restrict__ tile_sum) {
+    __shared__ int32_t red[kRowThreads / 64];
+    const int64_t base = (int64_t)blockIdx.x * kRowTile;
+    int32_t sum = 0;
+#pragma unroll
+    for (int r = 0; r < kRowItems; ++r) {
+        const int64_t v = base + r * kRowThreads + threadIdx.x;
+        if (v < n) sum += end[v] - start[v] + self;
+    }
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int w = 0; w < kRowThreads / 64; ++w) t += red[w];
+        tile_sum[blockIdx.x] = t;
+    }
 }
 
-// Keys sorted by their upper half: record where each id's run starts and ends.
-__global__ void run_bounds(const uint64_t* __restrict__ keys, int64_t count,
-                           int32_t* __restrict__ start, int32_t* __restrict__ end) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= count) return;
-    const uint32_t id = (uint32_t)(keys[k] >> 32);
-    if (k == 0 || (uint32_t)(keys[k - 1] >> 32) != id) start[id] = (int32_t)k;
-    if (k == count - 1 || (uint32_t)(keys[k + 1] >> 32) != id) end[id] = (int32_t)(k + 1);
-}
-
-// User rows: pair k of the (user, item)-sorted list lands behind its user's diagonal entry.
-// Also rewrites the key as (item << 32 | user) for the second sort.
-__global__ void fill_user_rows(uint64_t* __restrict__ keys, int64_t count, int32_t n_users,
-                               int32_t self, int32_t* __restrict__ col_idx) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= count) return;
-    const uint64_t key = keys[k];
-    const uint32_t u = (uint32_t)(key >> 32), i = (uint32_t)key;
-    col_idx[k + (int64_t)(u + 1) * self] = n_users + (int32_t)i;
-    keys[k] = ((uint64_t)i << 32) | u;
-}
-
-__global__ void fill_item_rows(const uint64_t* __restrict__ keys, int64_t count, int32_t n_users,
-                               int32_t self, int32_t* __restrict__ col_idx) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= count) return;
-    const uint64_t key = keys[k];
-    const uint32_t i = (uint32_t)(key >> 32), u = (uint32_t)key;
-    col_idx[count + (int64_t)n_users * self + (int64_t)i * self + k] = (int32_t)u;
-}
-
-// counts[v] = run length (+1 with self-loops); counts[n] = 0 so the scan yields row_ptr[n].
-// (in place: `end` becomes the counts)
-__global__ void row_counts(const int32_t* __restrict__ start, int32_t* end, int64_t n,
-                           int32_t self) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < n) end[v] = end[v] - start[v] + self;
-    if (v == n) end[v] = 0;
-}
-
-__global__ void fill_diagonal(const int32_t* __restrict__ row_ptr, int64_t n, int32_t n_users,
-                              int32_t* __restrict__ col_idx) {
-    int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= n) return;
-    // user row: itself first (items have larger ids); item row: itself last
-    const int64_t at = v < n_users ? (int64_t)row_ptr[v] : (int64_t)row_ptr[v + 1] - 1;
-    col_idx[at] = (int32_t)v;
+template <bool SCANNED>
+__global__ __launch_bounds__(kRowThreads) void row_pointers(const int32_t* __restrict__ start, const int32_t* __restrict__ end,
+                                                            int64_t n, int32_t n_users, int32_t self,
+                                                            const int32_t* __restrict__ tile_sum, int32_t* __restrict__ row_ptr,
+                                                            int32_t* __restrict__ col_idx) {
+    constexpr int kWaves = kRowThreads / 64;
+    __shared__ int32_t red[kWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t before = 0;
+    if (SCANNED) {
+        before = tile_sum[blockIdx.x];
+    } else {
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kRowThreads) before += tile_sum[t];
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        if (lane == 0) red[wave] = before;
+        __syncthreads();
+        before = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) before += red[w];
+        __syncthreads();
+    }
+    const int64_t base = (int64_t)blockIdx.x * kRowTile + (int64_t)wave * (64 * kRowItems);
+    int32_t cnt[kRowItems], inc[kRowItems], run = 0;
+#pragma unroll
+    for (int r = 0; r < kRowItems; ++r) {
+        const int64_t v = base + r * 64 + lane;
+        cnt[r] = v < n ? end[v] - start[v] + self : 0;
+    }
+#pragma unroll
+    for (int r = 0; r < kRowItems; ++r) {
+        int32_t t = cnt[r];
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const int32_t o = __shfl_up(t, dlt, 64);
+            if (lane >= dlt) t += o;
+        }
+        inc[r] = run + t;
+        run += __shfl(t, 63);
+    }
+    if (lane == 0) red[wave] = run;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+        if (w < wave) before += red[w];
+#pragma unroll
+    for (int r = 0; r < kRowItems; ++r) {
+        const int64_t v = base + r * 64 + lane;
+        if (v >= n) continue;
+        const int32_t last = before + inc[r], first = last - cnt[r];
+        row_ptr[v + 1] = last;
+        if (v == 0) row_ptr[0] = 0;
+        // user row: itself first (items have larger ids); item row: itself last
+        if (self) col_idx[v < n_users ? first : last - 1] = (int32_t)v;
+    }
 }
 
 // Weighted graphs (Section 3, "Notation": A_ij > 0 marks an edge, so its size is free to carry
@@ -141,11 +282,13 @@ __global__ void apply_weights(const int32_t* __restrict__ users, const int32_t* 
 struct BuildWs {
     uint64_t* buf_a;
     uint64_t* buf_b;
-    int32_t* pos;
+    int32_t* tile_cnt;
     void* sort_ws;
+    int32_t* zeroed;     // small[64], run_start[n + 1], run_end[n + 1]
+    int32_t* small;      // [0] distinct-pair count, [1] bad-id flag
     int32_t* run_start;
     int32_t* run_end;
-    int32_t* small;  // [0] distinct-pair count, [1] bad-id flag
+    int64_t zero_count;
     void* scan_ws;
     size_t bytes;
 };
@@ -157,16 +300,68 @@ BuildWs carve_build(void* base, int32_t n_users, int32_t n_items, int64_t n_edge
     BuildWs w;
     w.buf_a = c.take<uint64_t>(e);
     w.buf_b = c.take<uint64_t>(e);
-    w.pos = c.take<int32_t>(e);
+    const int64_t head_tiles = ceil_div(e, kHeadTile), row_tiles = ceil_div(n > 0 ? n : 1, kRowTile);
+    const int64_t tiles = head_tiles > row_tiles ? head_tiles : row_tiles;
+    w.tile_cnt = c.take<int32_t>(tiles);
     w.sort_ws = c.take<char>(radix_sort_workspace_bytes(e));
-    w.run_start = c.take<int32_t>(n + 1);
-    w.run_end = c.take<int32_t>(n + 1);
-    w.small = c.take<int32_t>(64);
-    int64_t longest = e;
-    if (n + 1 > longest) longest = n + 1;
-    w.scan_ws = c.take<char>(scan_workspace_bytes(longest));
+    w.zero_count = 64 + 2 * (n + 1);
+    w.zeroed = c.take<int32_t>(w.zero_count);
+    w.small = w.zeroed;
+    w.run_start = w.zeroed ? w.zeroed + 64 : nullptr;
+    w.run_end = w.zeroed ? w.run_start + (n + 1) : nullptr;
+    w.scan_ws = c.take<char>(scan_workspace_bytes(tiles));
     w.bytes = c.size();
     return w;
+}
+
+// The sort of all pairs by (user, item), the distinct ones as user rows, and their sort by item as item rows.
+int32_t sort_pairs(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t n_edges, const int32_t* users,
+                   const int32_t* items, int32_t self, int32_t* col_idx, hipStream_t stream) {
+    const int user_bits = bits_for(n_users), item_bits = bits_for(n_items);
+    uint64_t* src = w.buf_a;
+    uint64_t* dst = w.buf_b;
+    int passes = sort_passes(n_edges, user_bits + item_bits);
+    for (int p = 0, shift = 0; p < passes; ++p) {
+        const int width = sort_width(user_bits + item_bits, passes, p);
+        const int32_t st = p == 0 ? radix_pass(PairsIn{users, items, n_users, n_items, item_bits, w.small + 1}, KeysOut{dst},
+                                               n_edges, nullptr, shift, width, w.sort_ws, stream)
+                                  : radix_pass(KeysIn{src}, KeysOut{dst}, n_edges, nullptr, shift, width, w.sort_ws, stream);
+        if (st != E2EG_OK) return st;
+        shift += width;
+        uint64_t* t = src;
+        src = dst;
+        dst = t;
+    }
+    const int64_t tiles = ceil_div(n_edges, kHeadTile);
+    const dim3 grid((unsigned)tiles), blk(kHeadThreads);
+    count_heads<<<grid, blk, 0, stream>>>(src, n_edges, w.tile_cnt);
+    E2EG_LAUNCH_CHECK("count_heads");
+    if (tiles > kHeadFew) {
+        E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, tiles, nullptr, w.scan_ws, stream));
+        emit_pairs<true><<<grid, blk, 0, stream>>>(src, n_edges, w.tile_cnt, user_bits, item_bits, n_users, self, dst, col_idx,
+                                                  w.run_start, w.run_end, w.small);
+    } else {
+        emit_pairs<false><<<grid, blk, 0, stream>>>(src, n_edges, w.tile_cnt, user_bits, item_bits, n_users, self, dst, col_idx,
+                                                   w.run_start, w.run_end, w.small);
+    }
+    E2EG_LAUNCH_CHECK("emit_pairs");
+    uint64_t* t = src;
+    src = dst;
+    dst = t;
+    passes = sort_passes(n_edges, item_bits);
+    for (int p = 0, shift = user_bits; p < passes; ++p) {
+        const int width = sort_width(item_bits, passes, p);
+        const int32_t st =
+            p + 1 < passes ? radix_pass(KeysIn{src}, KeysOut{dst}, n_edges, w.small, shift, width, w.sort_ws, stream)
+                           : radix_pass(KeysIn{src}, ItemRowsOut{col_idx, w.small, w.run_end + n_users, n_users, self, user_bits},
+                                        n_edges, w.small, shift, width, w.sort_ws, stream);
+        if (st != E2EG_OK) return st;
+        shift += width;
+        t = src;
+        src = dst;
+        dst = t;
+    }
+    return E2EG_OK;
 }
 
 }  // namespace
@@ -208,62 +403,34 @@ extern "C" int32_t e2eg_build_csr(int32_t n_users, int32_t n_items, int64_t n_ed
 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     BuildWs w = carve_build(ws, n_users, n_items, n_edges);
-    const dim3 blk(kThreads);
-
-    fill_i32<<<dim3(1), dim3(64), 0, stream>>>(w.small, 64, 0);
-    E2EG_LAUNCH_CHECK("fill_i32");
-    fill_i32<<<dim3(blocks_for(n + 1, kThreads)), blk, 0, stream>>>(w.run_start, n + 1, 0);
-    fill_i32<<<dim3(blocks_for(n + 1, kThreads)), blk, 0, stream>>>(w.run_end, n + 1, 0);
-    E2EG_LAUNCH_CHECK("fill_i32");
-
-    uint64_t* src = w.buf_a;
-    uint64_t* dst = w.buf_b;
-    int32_t host_small[2] = {0, 0};
+    zero_i32<<<dim3(blocks_for(w.zero_count, kThreads)), dim3(kThreads), 0, stream>>>(w.zeroed, w.zero_count);
+    E2EG_LAUNCH_CHECK("zero_i32");
     if (n_edges > 0) {
-        pack_pairs<<<dim3(blocks_for(n_edges, kThreads)), blk, 0, stream>>>(
-            d_user_ids, d_item_ids, n_edges, n_users, n_items, src, w.small + 1);
-        E2EG_LAUNCH_CHECK("pack_pairs");
-        int32_t st = radix_sort_u64(&src, &dst, n_edges, 0, bits_for(n_items), w.sort_ws, stream);
+        const int32_t st = sort_pairs(w, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_col_idx, stream);
         if (st != E2EG_OK) return st;
-        st = radix_sort_u64(&src, &dst, n_edges, 32, bits_for(n_users), w.sort_ws, stream);
-        if (st != E2EG_OK) return st;
-        head_flags<<<dim3(blocks_for(n_edges, kThreads)), blk, 0, stream>>>(src, n_edges, w.pos);
-        E2EG_LAUNCH_CHECK("head_flags");
-        E2EG_HIP_TRY(exclusive_scan_i32(w.pos, w.pos, n_edges, w.small, w.scan_ws, stream));
-        compact_heads<<<dim3(blocks_for(n_edges, kThreads)), blk, 0, stream>>>(src, n_edges, w.pos, dst);
-        E2EG_LAUNCH_CHECK("compact_heads");
-        uint64_t* t = src;
-        src = dst;
-        dst = t;
+    }
+    if (n > 0) {
+        const int64_t tiles = ceil_div(n, kRowTile);
+        const dim3 grid((unsigned)tiles), blk(kRowThreads);
+        row_sums<<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, self, w.tile_cnt);
+        E2EG_LAUNCH_CHECK("row_sums");
+        if (tiles > kRowFew) {
+            E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, tiles, nullptr, w.scan_ws, stream));
+            row_pointers<true><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, d_row_ptr, d_col_idx);
+        } else {
+            row_pointers<false><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, d_row_ptr, d_col_idx);
+        }
+        E2EG_LAUNCH_CHECK("row_pointers");
+    } else {
+        zero_i32<<<dim3(1), dim3(64), 0, stream>>>(d_row_ptr, 1);
+        E2EG_LAUNCH_CHECK("zero_i32");
+    }
+    int32_t host_small[2] = {0, 0};
+    if (n_edges > 0)
         E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.small, sizeof(host_small), hipMemcpyDeviceToHost, stream));
-    }
-    E2EG_HIP_TRY(hipStreamSynchronize(stream));  // the one wait: the pair count sizes what follows
+    E2EG_HIP_TRY(hipStreamSynchronize(stream));  // the one wait: the pair count is the caller's to know
     if (host_small[1] != 0) return fail(E2EG_ERR_BAD_INDEX, "build_csr: a user or item id is out of range");
-    const int64_t pairs = host_small[0];
-    const int64_t nnz = 2 * pairs + n * self;
-    *h_nnz_out = nnz;
-
-    if (pairs > 0) {
-        const dim3 grid(blocks_for(pairs, kThreads));
-        run_bounds<<<grid, blk, 0, stream>>>(src, pairs, w.run_start, w.run_end);
-        E2EG_LAUNCH_CHECK("run_bounds");
-        fill_user_rows<<<grid, blk, 0, stream>>>(src, pairs, n_users, self, d_col_idx);
-        E2EG_LAUNCH_CHECK("fill_user_rows");
-        int32_t st = radix_sort_u64(&src, &dst, pairs, 32, bits_for(n_items), w.sort_ws, stream);
-        if (st != E2EG_OK) return st;
-        run_bounds<<<grid, blk, 0, stream>>>(src, pairs, w.run_start + n_users, w.run_end + n_users);
-        E2EG_LAUNCH_CHECK("run_bounds");
-        fill_item_rows<<<grid, blk, 0, stream>>>(src, pairs, n_users, self, d_col_idx);
-        E2EG_LAUNCH_CHECK("fill_item_rows");
-    }
-    // row_ptr = exclusive scan of per-row counts
-    row_counts<<<dim3(blocks_for(n + 1, kThreads)), blk, 0, stream>>>(w.run_start, w.run_end, n, self);
-    E2EG_LAUNCH_CHECK("row_counts");
-    E2EG_HIP_TRY(exclusive_scan_i32(w.run_end, d_row_ptr, n + 1, nullptr, w.scan_ws, stream));
-    if (self && n > 0) {
-        fill_diagonal<<<dim3(blocks_for(n, kThreads)), blk, 0, stream>>>(d_row_ptr, n, n_users, d_col_idx);
-        E2EG_LAUNCH_CHECK("fill_diagonal");
-    }
+    *h_nnz_out = 2 * (int64_t)host_small[0] + n * self;
     return E2EG_OK;
 }
 
