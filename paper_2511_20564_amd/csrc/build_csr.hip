@@ -11,8 +11,9 @@
 //   4. row_ptr from a prefix sum of the counts, the diagonal beside it.
 // The number of distinct pairs is known on the device only; launches are sized by the number of pairs
 // given, and the host waits once, at the end.
-// Bound by HBM for large graphs (8 sort passes of 16 bytes read and 8 written per pair), by the number
-// of launches for small ones.
+// Bound by HBM for large graphs (8 sort passes of 16 bytes read and 8 written per pair).
+// Small graphs are bound by the number of launches (17 of the above) and take another way, "buckets" below:
+// five launches.
 #include "radix.h"
 
 namespace e2eg {
@@ -240,6 +241,486 @@ __global__ __launch_bounds__(kRowThreads) void row_pointers(const int32_t* __res
     }
 }
 
+// ---- small graphs: buckets ----------------------------------------------------------------------------
+// The pairs are split once into at most 256 ranges of users; a workgroup sorts its range in LDS, drops
+// repeats and counts how its pairs spread over 256 ranges of items; the distinct pairs go to their ranges
+// of items in order, while the same kernel writes the user rows; a workgroup puts its range of items in
+// order, a range of any length, since the users of an item arrive sorted.  Row pointers and the diagonal
+// fall out of the per-range counts.  A range of users with more pairs than fit in LDS (ids in order of activity,
+// say) raises a flag, and the host, which waits at the end anyhow, then takes the general way.
+// Sampled subgraph of 291 k pairs, 173 k nodes: 215 us the general way, launch gaps included.
+constexpr int64_t kBucketMaxPairs = 1 << 20;
+constexpr int kBucketBits = 8;
+constexpr int kBuckets = 1 << kBucketBits;
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketWaves = kBucketThreads / 64;
+constexpr int kBucketRounds = 8;
+constexpr int kBucketCap = kBucketThreads * kBucketRounds;   // pairs of one range of users
+constexpr int kLowBitsMax = 12;                              // ids of one range
+constexpr int kItemThreads = 512;
+constexpr int kItemWaves = kItemThreads / 64;
+
+struct BucketPlan {
+    int user_bits, item_bits;
+    int user_low, item_low;     // bits of an id inside its range
+    int n_user_ranges, n_item_ranges;
+};
+
+bool plan_buckets(int32_t n_users, int32_t n_items, int64_t n_edges, BucketPlan* p) {
+    p->user_bits = bits_for(n_users);
+    p->item_bits = bits_for(n_items);
+    p->user_low = p->user_bits > kBucketBits ? p->user_bits - kBucketBits : 0;
+    p->item_low = p->item_bits > kBucketBits ? p->item_bits - kBucketBits : 0;
+    p->n_user_ranges = 1 << (p->user_bits - p->user_low);
+    p->n_item_ranges = 1 << (p->item_bits - p->item_low);
+    return n_edges > 0 && n_edges <= kBucketMaxPairs && p->user_low <= kLowBitsMax && p->item_low <= kLowBitsMax &&
+           p->user_low + p->item_bits <= 32;
+}
+
+struct BucketWs {
+    int32_t* user_hist;   // [tiles of pairs][kBuckets]
+    int32_t* tile_bad;    // [tiles of pairs] an id out of range
+    int32_t* item_hist;   // [user ranges][kBuckets]
+    int32_t* range_first; // [user ranges] first pair of every range of users
+    int32_t* distinct;    // [user ranges] distinct pairs
+    int32_t* overflow;    // [user ranges]
+    int32_t* item_first;  // [item ranges + 1] first pair of every range of items
+    int32_t* result;      // [4] distinct pairs, bad ids, overflow
+};
+
+BucketWs carve_buckets(Carver& c, int64_t n_edges) {
+    BucketWs w = {};
+    if (n_edges > kBucketMaxPairs) return w;
+    const int64_t tiles = ceil_div(n_edges > 0 ? n_edges : 1, SplitSort::kTile);
+    w.user_hist = c.take<int32_t>(tiles * kBuckets);
+    w.tile_bad = c.take<int32_t>(tiles);
+    w.item_hist = c.take<int32_t>(kBuckets * kBuckets);
+    w.range_first = c.take<int32_t>(kBuckets);
+    w.distinct = c.take<int32_t>(kBuckets);
+    w.overflow = c.take<int32_t>(kBuckets);
+    w.item_first = c.take<int32_t>(kBuckets + 1);
+    w.result = c.take<int32_t>(4);
+    return w;
+}
+
+// Pairs per range of users, in every tile.
+__global__ __launch_bounds__(SplitSort::kThreads) void count_ranges(PairsIn in, int64_t count, int shift, int bins,
+                                                                    BucketWs w) {
+    __shared__ int h[kBuckets];
+    __shared__ int bad;
+    for (int k = threadIdx.x; k < kBuckets; k += SplitSort::kThreads) h[k] = 0;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * SplitSort::kTile;
+    int32_t u[SplitSort::kItems], i[SplitSort::kItems];
+#pragma unroll
+    for (int k = 0; k < SplitSort::kItems; ++k) {
+        const int64_t e = base + k * SplitSort::kThreads + threadIdx.x;
+        u[k] = e < count ? in.users[e] : 0;
+        i[k] = e < count ? in.items[e] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < SplitSort::kItems; ++k) {
+        const int64_t e = base + k * SplitSort::kThreads + threadIdx.x;
+        if (e < count) {
+            const bool ok = in.ok(u[k], i[k]);
+            if (!ok) bad = 1;
+            atomicAdd(&h[ok ? (int)((((uint64_t)(uint32_t)u[k] << in.item_bits) | (uint32_t)i[k]) >> shift) : 0], 1);
+        }
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < bins; k += SplitSort::kThreads) w.user_hist[(int64_t)blockIdx.x * bins + k] = h[k];
+    if (threadIdx.x == 0) w.tile_bad[blockIdx.x] = bad;
+}
+
+// Exclusive scan of one value per thread over a workgroup of WAVES wavefronts.
+template <int WAVES>
+__device__ __forceinline__ int32_t scan_block(int32_t v, int32_t* lds, int32_t* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t inc = v;
+#pragma unroll
+    for (int dlt = 1; dlt < 64; dlt <<= 1) {
+        const int32_t t = __shfl_up(inc, dlt, 64);
+        if (lane >= dlt) inc += t;
+    }
+    __syncthreads();
+    if (lane == 63) lds[wave] = inc;
+    __syncthreads();
+    int32_t before = inc - v, all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        if (w < wave) before += lds[w];
+        all += lds[w];
+    }
+    *total = all;
+    return before;
+}
+
+// Ranks of a wavefront's keys by digit, in input order: the running per-wavefront counts are in `cnt`.
+template <int BITS>
+__device__ __forceinline__ int rank_digit(int d, bool valid, int nbits, uint64_t lt_mask, uint16_t* cnt) {
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        if (b < nbits) {
+            const bool bit = (d >> b) & 1;
+            const uint64_t bal = __ballot(valid && bit);
+            peers &= bit ? bal : ~bal;
+        }
+    }
+    const int below = __popcll(peers & lt_mask);
+    const int pre = cnt[d];
+    if (valid && below == 0) cnt[d] = (uint16_t)(pre + __popcll(peers));
+    return pre + below;
+}
+
+// One range of users: sorted by (user, item) in LDS, repeats dropped, turned round to (item, user).
+__global__ __launch_bounds__(kBucketThreads) void sort_ranges(const uint64_t* __restrict__ pairs, int32_t tiles,
+                                                              BucketPlan p, uint64_t* __restrict__ turned, BucketWs w) {
+    __shared__ uint32_t keys[2][kBucketCap];
+    __shared__ uint16_t cnt[kBucketWaves][256];
+    __shared__ int32_t hist[kBuckets];
+    __shared__ int32_t part[kBucketThreads / kBuckets][kBuckets];
+    __shared__ int32_t lds[kBucketWaves];
+    __shared__ int32_t span[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int r = blockIdx.x;
+    {   // where the range's pairs are: totals of all ranges, scanned
+        const int d = threadIdx.x % kBuckets, q = threadIdx.x / kBuckets;
+        int32_t t = 0;
+        if (d < p.n_user_ranges)
+#pragma unroll 8
+            for (int b = q; b < tiles; b += kBucketThreads / kBuckets) t += w.user_hist[(int64_t)b * p.n_user_ranges + d];
+        part[q][d] = t;
+        __syncthreads();
+        t = 0;
+        if (threadIdx.x < kBuckets)
+#pragma unroll
+            for (int k = 0; k < kBucketThreads / kBuckets; ++k) t += part[k][threadIdx.x];
+        int32_t all;
+        const int32_t before = scan_block<kBucketWaves>(t, lds, &all);
+        if ((int)threadIdx.x == r) {
+            span[0] = before;
+            span[1] = t;
+        }
+        if (threadIdx.x < kBuckets) hist[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    const int32_t first = span[0], n = span[1];
+    if (threadIdx.x == 0) {
+        w.range_first[r] = first;
+        w.overflow[r] = n > kBucketCap ? 1 : 0;
+    }
+    if (n > kBucketCap) {
+        if (threadIdx.x == 0) w.distinct[r] = 0;
+        if ((int)threadIdx.x < p.n_item_ranges) w.item_hist[r * p.n_item_ranges + threadIdx.x] = 0;
+        return;
+    }
+    const int key_bits = p.user_low + p.item_bits;
+    const uint64_t key_mask = (1ull << key_bits) - 1;
+    for (int k = threadIdx.x; k < n; k += kBucketThreads) keys[0][k] = (uint32_t)(pairs[first + k] & key_mask);
+    const int rounds = (n + kBucketThreads - 1) / kBucketThreads;   // a wavefront's keys: 64 * rounds consecutive ones
+    const int chunk = wave * 64 * rounds;
+    const int passes = (key_bits + 7) / 8;
+    int cur = 0;
+    for (int pass = 0; pass < passes; ++pass) {
+        const int shift = key_bits * pass / passes, nbits = key_bits * (pass + 1) / passes - shift;
+        const int bins = 1 << nbits;
+        for (int k = threadIdx.x; k < kBucketWaves * 128; k += kBucketThreads) reinterpret_cast<uint32_t*>(&cnt[0][0])[k] = 0;
+        __syncthreads();
+        uint32_t key[kBucketRounds];
+        int rank[kBucketRounds];
+#pragma unroll
+        for (int q = 0; q < kBucketRounds; ++q) {
+            if (q >= rounds) break;
+            const int at = chunk + q * 64 + lane;
+            key[q] = at < n ? keys[cur][at] : 0u;
+            rank[q] = rank_digit<8>((int)(key[q] >> shift) & (bins - 1), at < n, nbits, lt_mask, cnt[wave]);
+        }
+        __syncthreads();
+        {   // digit t of thread t < 256: counts of the wavefronts become first places
+            int32_t mine = 0;
+            if (threadIdx.x < 256)
+#pragma unroll
+                for (int v = 0; v < kBucketWaves; ++v) mine += cnt[v][threadIdx.x];
+            int32_t all;
+            int32_t at = scan_block<kBucketWaves>(mine, lds, &all);
+            if (threadIdx.x < 256)
+#pragma unroll
+                for (int v = 0; v < kBucketWaves; ++v) {
+                    const int c = cnt[v][threadIdx.x];
+                    cnt[v][threadIdx.x] = (uint16_t)at;
+                    at += c;
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kBucketRounds; ++q) {
+            if (q >= rounds) break;
+            if (chunk + q * 64 + lane < n) keys[1 - cur][cnt[wave][(int)(key[q] >> shift) & (bins - 1)] + rank[q]] = key[q];
+        }
+        cur = 1 - cur;
+        __syncthreads();
+    }
+    // repeats
+    int32_t heads = 0;
+    uint64_t bal[kBucketRounds];
+#pragma unroll
+    for (int q = 0; q < kBucketRounds; ++q) {
+        bal[q] = 0;
+        if (q >= rounds) break;
+        const int at = chunk + q * 64 + lane;
+        bal[q] = __ballot(at < n && (at == 0 || keys[cur][at] != keys[cur][at - 1]));
+        heads += __popcll(bal[q]);
+    }
+    if (lane == 0) lds[wave] = heads;
+    __syncthreads();
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int v = 0; v < kBucketWaves; ++v) {
+        if (v < wave) before += lds[v];
+        all += lds[v];
+    }
+#pragma unroll
+    for (int q = 0; q < kBucketRounds; ++q) {
+        if (q >= rounds) break;
+        if ((bal[q] >> lane) & 1) {
+            const uint32_t key = keys[cur][chunk + q * 64 + lane];
+            const uint32_t item = key & (uint32_t)((1ull << p.item_bits) - 1);
+            const uint32_t user = ((uint32_t)r << p.user_low) | (uint32_t)((uint64_t)key >> p.item_bits);
+            turned[first + before + __popcll(bal[q] & lt_mask)] = ((uint64_t)item << p.user_bits) | user;
+            atomicAdd(&hist[item >> p.item_low], 1);
+        }
+        before += __popcll(bal[q]);
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < p.n_item_ranges) w.item_hist[r * p.n_item_ranges + threadIdx.x] = hist[threadIdx.x];
+    if (threadIdx.x == 0) w.distinct[r] = all;
+}
+
+// One range of users: its rows, row pointers and diagonal entries, and its pairs to their ranges of items.
+__global__ __launch_bounds__(kBucketThreads) void spread_ranges(const uint64_t* __restrict__ turned, BucketPlan p,
+                                                                int32_t n_users, int32_t self, uint64_t* __restrict__ by_item,
+                                                                int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+                                                                BucketWs w) {
+    constexpr int kLow = 1 << kLowBitsMax;
+    constexpr int kPer = kLow / kBucketThreads;
+    __shared__ uint16_t cnt[kBucketWaves][256];
+    __shared__ int32_t users[kLow];
+    __shared__ int32_t part[2][kBucketThreads / kBuckets][kBuckets];
+    __shared__ int32_t base[kBuckets];
+    __shared__ int32_t lds[kBucketWaves];
+    __shared__ int32_t pairs_before;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int r = blockIdx.x;
+    const int32_t n = w.distinct[r], first = w.range_first[r];
+    const int rounds = (n + kBucketThreads - 1) / kBucketThreads;
+    const int chunk = wave * 64 * rounds;
+    uint64_t key[kBucketRounds];
+#pragma unroll
+    for (int q = 0; q < kBucketRounds; ++q) {
+        const int at = chunk + q * 64 + lane;
+        key[q] = q < rounds && at < n ? turned[first + at] : 0ull;
+    }
+    for (int k = threadIdx.x; k < kBucketWaves * 128; k += kBucketThreads) reinterpret_cast<uint32_t*>(&cnt[0][0])[k] = 0;
+    for (int k = threadIdx.x; k < kLow; k += kBucketThreads) users[k] = 0;
+    {   // where this range's pairs go in every range of items
+        const int d = threadIdx.x % kBuckets, q = threadIdx.x / kBuckets;
+        int32_t before = 0, total = 0;
+        if (d < p.n_item_ranges)
+#pragma unroll 16
+            for (int b = q; b < p.n_user_ranges; b += kBucketThreads / kBuckets) {
+                const int32_t c = w.item_hist[b * p.n_item_ranges + d];
+                if (b < r) before += c;
+                total += c;
+            }
+        part[0][q][d] = before;
+        part[1][q][d] = total;
+        __syncthreads();
+        before = total = 0;
+        if (threadIdx.x < kBuckets)
+#pragma unroll
+            for (int k = 0; k < kBucketThreads / kBuckets; ++k) {
+                before += part[0][k][threadIdx.x];
+                total += part[1][k][threadIdx.x];
+            }
+        int32_t all;
+        const int32_t lower = scan_block<kBucketWaves>(total, lds, &all);
+        if (threadIdx.x < kBuckets) base[threadIdx.x] = lower + before;
+        if (r == 0 && threadIdx.x < kBuckets) {
+            if ((int)threadIdx.x < p.n_item_ranges) w.item_first[threadIdx.x] = lower;
+            if (threadIdx.x == 0) w.item_first[p.n_item_ranges] = all;
+        }
+        const int32_t dist = (int)threadIdx.x < p.n_user_ranges ? w.distinct[threadIdx.x] : 0;
+        const int32_t earlier = scan_block<kBucketWaves>(dist, lds, &all);
+        if ((int)threadIdx.x == r) pairs_before = earlier;
+        __syncthreads();
+    }
+    const uint64_t user_mask = (1ull << p.user_bits) - 1;
+    const uint32_t low_mask = (1u << p.user_low) - 1;
+    const int shift = p.user_bits + p.item_low, nbits = p.item_bits - p.item_low;
+    int rank[kBucketRounds];
+#pragma unroll
+    for (int q = 0; q < kBucketRounds; ++q) {
+        if (q >= rounds) break;
+        const int at = chunk + q * 64 + lane;
+        const bool valid = at < n;
+        rank[q] = rank_digit<kBucketBits>((int)(key[q] >> shift), valid, nbits, lt_mask, cnt[wave]);
+        if (valid) {
+            const uint32_t user = (uint32_t)(key[q] & user_mask);
+            const int32_t item = (int32_t)(key[q] >> p.user_bits);
+            atomicAdd(&users[user & low_mask], 1);
+            col_idx[(int64_t)pairs_before + at + (int64_t)(user + 1) * self] = n_users + item;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < kBuckets) {
+        int run = 0;
+#pragma unroll
+        for (int v = 0; v < kBucketWaves; ++v) {
+            const int c = cnt[v][threadIdx.x];
+            cnt[v][threadIdx.x] = (uint16_t)run;
+            run += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kBucketRounds; ++q) {
+        if (q >= rounds) break;
+        if (chunk + q * 64 + lane < n) {
+            const int d = (int)(key[q] >> shift);
+            by_item[base[d] + cnt[wave][d] + rank[q]] = key[q];
+        }
+    }
+    // row pointers of the range's users
+    int32_t mine[kPer], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        mine[k] = users[threadIdx.x * kPer + k];
+        sum += mine[k];
+    }
+    int32_t all;
+    int32_t at = scan_block<kBucketWaves>(sum, lds, &all) + pairs_before;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const uint32_t low = threadIdx.x * kPer + k;
+        const int64_t u = ((int64_t)r << p.user_low) + low;
+        if (low <= low_mask && u < n_users) {
+            const int32_t row = at + (int32_t)u * self;
+            row_ptr[u] = row;
+            if (self) col_idx[row] = (int32_t)u;   // user row: itself first (items have larger ids)
+        }
+        at += mine[k];
+    }
+}
+
+// One range of items: its rows, row pointers and diagonal entries.  Any number of pairs: a tile of them at a
+// time, each item's place moving on from tile to tile.  Workgroup 0 also writes the result for the host.
+__global__ __launch_bounds__(kItemThreads) void item_ranges(const uint64_t* __restrict__ by_item, BucketPlan p,
+                                                            int32_t n_users, int32_t n_items, int32_t self, int32_t tiles,
+                                                            int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+                                                            BucketWs w) {
+    constexpr int kLow = 1 << kLowBitsMax;
+    constexpr int kPer = kLow / kItemThreads;
+    constexpr int kRounds = 4;
+    __shared__ uint16_t cnt[kItemWaves][kLow];
+    __shared__ int32_t place[kLow];   // where the item's next user goes in col_idx
+    __shared__ int32_t lds[kItemWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int r = blockIdx.x;
+    const int32_t first = w.item_first[r], end = w.item_first[r + 1], pairs = w.item_first[p.n_item_ranges];
+    const int ids = 1 << p.item_low;
+    if (r == 0) {
+        int32_t bad = 0, over = 0, all;
+        for (int t = threadIdx.x; t < tiles; t += kItemThreads) bad |= w.tile_bad[t];
+        for (int t = threadIdx.x; t < p.n_user_ranges; t += kItemThreads) over |= w.overflow[t];
+        scan_block<kItemWaves>(bad, lds, &all);
+        if (threadIdx.x == 0) w.result[1] = all;
+        scan_block<kItemWaves>(over, lds, &all);
+        if (threadIdx.x == 0) {
+            w.result[0] = pairs;
+            w.result[2] = all;
+            row_ptr[n_users + n_items] = 2 * pairs + (n_users + n_items) * self;
+        }
+    }
+    for (int k = threadIdx.x; k < ids; k += kItemThreads) place[k] = 0;
+    __syncthreads();
+    const uint32_t low_mask = (uint32_t)ids - 1;
+#pragma unroll 4
+    for (int32_t k = first + (int32_t)threadIdx.x; k < end; k += kItemThreads)
+        atomicAdd(&place[(uint32_t)(by_item[k] >> p.user_bits) & low_mask], 1);
+    __syncthreads();
+    {
+        int32_t mine[kPer], sum = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int id = threadIdx.x * kPer + k;
+            mine[k] = id < ids ? place[id] : 0;
+            sum += mine[k];
+        }
+        int32_t all;
+        int32_t at = scan_block<kItemWaves>(sum, lds, &all) + pairs + n_users * self + first;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int id = threadIdx.x * kPer + k;
+            const int64_t i = ((int64_t)r << p.item_low) + id;
+            if (id < ids && i < n_items) {
+                const int32_t row = at + (int32_t)i * self;
+                row_ptr[n_users + i] = row;
+                place[id] = row;
+                if (self) col_idx[row + mine[k]] = n_users + (int32_t)i;   // item row: itself last
+            }
+            at += mine[k];
+        }
+    }
+    __syncthreads();
+    const uint64_t user_mask = (1ull << p.user_bits) - 1;
+    for (int32_t t0 = first; t0 < end; t0 += kRounds * kItemThreads) {
+        for (int k = threadIdx.x; k < ids; k += kItemThreads)
+#pragma unroll
+            for (int v = 0; v < kItemWaves; ++v) cnt[v][k] = 0;
+        __syncthreads();
+        uint64_t key[kRounds];
+        int rank[kRounds];
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t k = t0 + wave * 64 * kRounds + q * 64 + lane;
+            key[q] = k < end ? by_item[k] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t k = t0 + wave * 64 * kRounds + q * 64 + lane;
+            rank[q] = rank_digit<kLowBitsMax>((int)((uint32_t)(key[q] >> p.user_bits) & low_mask), k < end, p.item_low,
+                                              lt_mask, cnt[wave]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRounds; ++q) {
+            const int32_t k = t0 + wave * 64 * kRounds + q * 64 + lane;
+            if (k < end) {
+                const int d = (int)((uint32_t)(key[q] >> p.user_bits) & low_mask);
+                int32_t at = place[d] + rank[q];
+#pragma unroll
+                for (int v = 0; v < kItemWaves; ++v)
+                    if (v < wave) at += cnt[v][d];
+                col_idx[at] = (int32_t)(key[q] & user_mask);
+            }
+        }
+        __syncthreads();
+        if (t0 + kRounds * kItemThreads < end)
+            for (int k = threadIdx.x; k < ids; k += kItemThreads) {
+                int32_t sum = 0;
+#pragma unroll
+                for (int v = 0; v < kItemWaves; ++v) sum += cnt[v][k];
+                place[k] += sum;
+            }
+        __syncthreads();
+    }
+}
+
 // Weighted graphs (Section 3, "Notation": A_ij > 0 marks an edge, so its size is free to carry
 // a strength).  Stored values of A~: 1 on the diagonal, 0 until a listed pair brings its weight.
 __global__ void init_values(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
@@ -290,6 +771,7 @@ struct BuildWs {
     int32_t* run_end;
     int64_t zero_count;
     void* scan_ws;
+    BucketWs buckets;
     size_t bytes;
 };
 
@@ -310,6 +792,7 @@ BuildWs carve_build(void* base, int32_t n_users, int32_t n_items, int64_t n_edge
     w.run_start = w.zeroed ? w.zeroed + 64 : nullptr;
     w.run_end = w.zeroed ? w.run_start + (n + 1) : nullptr;
     w.scan_ws = c.take<char>(scan_workspace_bytes(tiles));
+    w.buckets = carve_buckets(c, n_edges);
     w.bytes = c.size();
     return w;
 }
@@ -364,6 +847,58 @@ int32_t sort_pairs(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t n
     return E2EG_OK;
 }
 
+// The general way.
+int32_t build_sorted(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t n_edges, const int32_t* users,
+                     const int32_t* items, int32_t self, int32_t* row_ptr, int32_t* col_idx, hipStream_t stream) {
+    const int64_t n = (int64_t)n_users + n_items;
+    zero_i32<<<dim3(blocks_for(w.zero_count, kThreads)), dim3(kThreads), 0, stream>>>(w.zeroed, w.zero_count);
+    E2EG_LAUNCH_CHECK("zero_i32");
+    if (n_edges > 0) {
+        const int32_t st = sort_pairs(w, n_users, n_items, n_edges, users, items, self, col_idx, stream);
+        if (st != E2EG_OK) return st;
+    }
+    if (n == 0) {
+        zero_i32<<<dim3(1), dim3(64), 0, stream>>>(row_ptr, 1);
+        E2EG_LAUNCH_CHECK("zero_i32");
+        return E2EG_OK;
+    }
+    const int64_t tiles = ceil_div(n, kRowTile);
+    const dim3 grid((unsigned)tiles), blk(kRowThreads);
+    row_sums<<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, self, w.tile_cnt);
+    E2EG_LAUNCH_CHECK("row_sums");
+    if (tiles > kRowFew) {
+        E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, tiles, nullptr, w.scan_ws, stream));
+        row_pointers<true><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, row_ptr, col_idx);
+    } else {
+        row_pointers<false><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, row_ptr, col_idx);
+    }
+    E2EG_LAUNCH_CHECK("row_pointers");
+    return E2EG_OK;
+}
+
+int32_t build_bucketed(const BuildWs& w, const BucketPlan& p, int32_t n_users, int32_t n_items, int64_t n_edges,
+                       const int32_t* users, const int32_t* items, int32_t self, int32_t* row_ptr, int32_t* col_idx,
+                       hipStream_t stream) {
+    const PairsIn in{users, items, n_users, n_items, p.item_bits, nullptr};
+    const int32_t tiles = (int32_t)ceil_div(n_edges, SplitSort::kTile);
+    const int shift = p.item_bits + p.user_low;
+    const dim3 split_grid((unsigned)tiles), split_blk(SplitSort::kThreads);
+    const dim3 user_grid((unsigned)p.n_user_ranges), user_blk(kBucketThreads);
+    count_ranges<<<split_grid, split_blk, 0, stream>>>(in, n_edges, shift, p.n_user_ranges, w.buckets);
+    E2EG_LAUNCH_CHECK("count_ranges");
+    sort_scatter<SplitSort, PairsIn, KeysOut, true><<<split_grid, split_blk, 0, stream>>>(
+        in, KeysOut{w.buf_a}, n_edges, nullptr, shift, p.user_bits - p.user_low, w.buckets.user_hist, tiles);
+    E2EG_LAUNCH_CHECK("sort_scatter");
+    sort_ranges<<<user_grid, user_blk, 0, stream>>>(w.buf_a, tiles, p, w.buf_b, w.buckets);
+    E2EG_LAUNCH_CHECK("sort_ranges");
+    spread_ranges<<<user_grid, user_blk, 0, stream>>>(w.buf_b, p, n_users, self, w.buf_a, row_ptr, col_idx, w.buckets);
+    E2EG_LAUNCH_CHECK("spread_ranges");
+    item_ranges<<<dim3((unsigned)p.n_item_ranges), dim3(kItemThreads), 0, stream>>>(w.buf_a, p, n_users, n_items, self, tiles,
+                                                                                 row_ptr, col_idx, w.buckets);
+    E2EG_LAUNCH_CHECK("item_ranges");
+    return E2EG_OK;
+}
+
 }  // namespace
 }  // namespace e2eg
 
@@ -403,32 +938,23 @@ extern "C" int32_t e2eg_build_csr(int32_t n_users, int32_t n_items, int64_t n_ed
 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     BuildWs w = carve_build(ws, n_users, n_items, n_edges);
-    zero_i32<<<dim3(blocks_for(w.zero_count, kThreads)), dim3(kThreads), 0, stream>>>(w.zeroed, w.zero_count);
-    E2EG_LAUNCH_CHECK("zero_i32");
-    if (n_edges > 0) {
-        const int32_t st = sort_pairs(w, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_col_idx, stream);
+    // The one wait is at the end: the pair count is the caller's to know.
+    int32_t host_small[3] = {0, 0, 0};   // distinct pairs, bad ids, buckets overflowed
+    BucketPlan plan;
+    const bool bucketed = plan_buckets(n_users, n_items, n_edges, &plan);
+    if (bucketed) {
+        const int32_t st = build_bucketed(w, plan, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
         if (st != E2EG_OK) return st;
+        E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.buckets.result, sizeof(host_small), hipMemcpyDeviceToHost, stream));
+        E2EG_HIP_TRY(hipStreamSynchronize(stream));
     }
-    if (n > 0) {
-        const int64_t tiles = ceil_div(n, kRowTile);
-        const dim3 grid((unsigned)tiles), blk(kRowThreads);
-        row_sums<<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, self, w.tile_cnt);
-        E2EG_LAUNCH_CHECK("row_sums");
-        if (tiles > kRowFew) {
-            E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, tiles, nullptr, w.scan_ws, stream));
-            row_pointers<true><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, d_row_ptr, d_col_idx);
-        } else {
-            row_pointers<false><<<grid, blk, 0, stream>>>(w.run_start, w.run_end, n, n_users, self, w.tile_cnt, d_row_ptr, d_col_idx);
-        }
-        E2EG_LAUNCH_CHECK("row_pointers");
-    } else {
-        zero_i32<<<dim3(1), dim3(64), 0, stream>>>(d_row_ptr, 1);
-        E2EG_LAUNCH_CHECK("zero_i32");
+    if (!bucketed || (host_small[1] == 0 && host_small[2] != 0)) {
+        const int32_t st = build_sorted(w, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
+        if (st != E2EG_OK) return st;
+        if (n_edges > 0)
+            E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.small, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+        E2EG_HIP_TRY(hipStreamSynchronize(stream));
     }
-    int32_t host_small[2] = {0, 0};
-    if (n_edges > 0)
-        E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.small, sizeof(host_small), hipMemcpyDeviceToHost, stream));
-    E2EG_HIP_TRY(hipStreamSynchronize(stream));  // the one wait: the pair count is the caller's to know
     if (host_small[1] != 0) return fail(E2EG_ERR_BAD_INDEX, "build_csr: a user or item id is out of range");
     *h_nnz_out = 2 * (int64_t)host_small[0] + n * self;
     return E2EG_OK;

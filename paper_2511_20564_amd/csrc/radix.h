@@ -13,15 +13,17 @@ namespace e2eg {
 // of launches: digits of up to 11 bits (two launches a pass while the table is so small that every workgroup
 // adds up its own offsets).
 struct LargeSort {
-    static constexpr int kThreads = 512, kItems = 16, kBits = 8, kCopies = 4;
+    static constexpr int kThreads = 512, kItems = 16, kBits = 8, kCopies = 4, kTile = kThreads * kItems;
 };
 struct SmallSort {
-    static constexpr int kThreads = 1024, kItems = 8, kBits = 11, kCopies = 1;
+    static constexpr int kThreads = 1024, kItems = 8, kBits = 11, kCopies = 1, kTile = kThreads * kItems;
 };
-constexpr int kSortTile = 8192;   // keys per tile, either shape
+// One 8-bit digit of a small list (the bucketed CSR build): more, smaller tiles.
+struct SplitSort {
+    static constexpr int kThreads = 512, kItems = 8, kBits = 8, kCopies = 1, kTile = kThreads * kItems;
+};
 constexpr int64_t kLargeSortMin = 4 << 20;
 constexpr int kFusedTiles = 64;   // up to this many tiles the scatter adds up its offsets itself
-static_assert(LargeSort::kThreads * LargeSort::kItems == kSortTile && SmallSort::kThreads * SmallSort::kItems == kSortTile, "tile");
 
 struct KeysIn {
     const uint64_t* keys;
@@ -46,7 +48,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, int64_t cou
     for (int k = threadIdx.x; k < S::kCopies << S::kBits; k += S::kThreads) (&h[0][0])[k] = 0;
     __syncthreads();
     if (d_count) count = *d_count;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
+    const int64_t base = (int64_t)blockIdx.x * S::kTile;
     int* mine = h[(threadIdx.x >> 6) % S::kCopies];
     uint64_t key[S::kItems];
 #pragma unroll
@@ -89,10 +91,10 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
     __shared__ uint16_t wave_cnt[kWaves][kBins];   // keys of digit d in wavefront w, then their first place in the tile
     __shared__ int wave_tot[kWaves];
     __shared__ int shift_by[kBins];                // where the tile's keys of digit d go, less their first place in the tile
-    __shared__ uint64_t tile[kSortTile];
+    __shared__ uint64_t tile[S::kTile];
     const int bins = 1 << nbits;
     if (d_count) count = *d_count;
-    const int64_t tile_base = (int64_t)blockIdx.x * kSortTile;
+    const int64_t tile_base = (int64_t)blockIdx.x * S::kTile;
     if (tile_base >= count) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -162,14 +164,30 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
             int before[kPer], total[kPer], all = 0;
 #pragma unroll
             for (int p = 0; p < kPer; ++p) before[p] = total[p] = 0;
-            if (d0 < bins) {
+            // with more threads than digits, kParts threads share a digit's tiles
+            constexpr int kParts = S::kThreads / kBins > 1 ? S::kThreads / kBins : 1;
+            __shared__ int part_sum[kParts > 1 ? kParts : 1][2][kParts > 1 ? kBins : 1];
+            const int dd = kParts > 1 ? threadIdx.x % kBins : d0, part = kParts > 1 ? threadIdx.x / kBins : 0;
+            if (dd < bins) {
 #pragma unroll 16
-                for (int b = 0; b < tiles; ++b)
+                for (int b = part; b < tiles; b += kParts)
 #pragma unroll
                     for (int p = 0; p < kPer; ++p) {
-                        const int c = d0 + p < bins ? offs[(int64_t)b * bins + d0 + p] : 0;
+                        const int c = dd + p < bins ? offs[(int64_t)b * bins + dd + p] : 0;
                         if (b < (int)blockIdx.x) before[p] += c;
                         total[p] += c;
+                    }
+            }
+            if constexpr (kParts > 1) {
+                part_sum[part][0][dd] = before[0];
+                part_sum[part][1][dd] = total[0];
+                __syncthreads();
+                before[0] = total[0] = 0;
+                if (d0 < kBins)
+#pragma unroll
+                    for (int q = 0; q < kParts; ++q) {
+                        before[0] += part_sum[q][0][d0];
+                        total[0] += part_sum[q][1][d0];
                     }
             }
 #pragma unroll
@@ -209,7 +227,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
     }
     __syncthreads();
     const int64_t left = count - tile_base;
-    const int valid_keys = left < kSortTile ? (int)left : kSortTile;
+    const int valid_keys = left < S::kTile ? (int)left : S::kTile;
 #pragma unroll 4
     for (int p = threadIdx.x; p < valid_keys; p += S::kThreads) {
         const uint64_t k = tile[p];
@@ -231,7 +249,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
 template <typename S, typename In, typename Out>
 int32_t radix_pass_as(In in, Out out, int64_t count, const int32_t* d_count, int shift, int nbits, void* ws,
                       hipStream_t stream) {
-    const int32_t tiles = (int32_t)ceil_div(count, kSortTile);
+    const int32_t tiles = (int32_t)ceil_div(count, S::kTile);
     const dim3 grid((unsigned)tiles), blk(S::kThreads);
     int32_t* hist = static_cast<int32_t*>(ws);
     if (tiles <= kFusedTiles) {

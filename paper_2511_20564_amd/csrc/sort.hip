@@ -5,8 +5,9 @@
 namespace e2eg {
 
 size_t radix_sort_workspace_bytes(int64_t count) {
-    const int64_t tiles = ceil_div(count > 0 ? count : 1, kSortTile);
-    const int64_t cells = tiles << (sorts_large(count) ? LargeSort::kBits : SmallSort::kBits);
+    if (count < 1) count = 1;
+    const int64_t cells = sorts_large(count) ? ceil_div(count, LargeSort::kTile) << LargeSort::kBits
+                                             : ceil_div(count, SmallSort::kTile) << SmallSort::kBits;
     return align_up((size_t)cells * sizeof(int32_t)) + scan_workspace_bytes(cells);
 }
 
