@@ -10,12 +10,15 @@
 //     One thread per entry throughout, so that a row of a million entries is no wavefront's loop.
 //   * a draw is one thread: 64 random bits from the counter-based generator Philox4x32-10 (Salmon,
 //     Moraes, Dror, Shaw, SC 2011; counter = (draw, node, hop, 0), key = the seed), scaled to the
-//     row total by a 64x64->128-bit multiply, then a binary search in the row's slice of the table.
-//   * visited nodes are marked with an integer compare-and-swap (all writers of one hop write the
-//     same value); frontiers, the node list and the edge list are compacted with prefix sums, so
-//     their order is ascending node id / draw order and does not depend on scheduling.
+//     row total by a 64x64->128-bit multiply, then a search in the row's slice of the table.
+//   * the nodes reached at each hop are a bitmap (set by integer OR); frontiers, the node list and the edge
+//     list are compacted with prefix sums, so their order is ascending node id / draw order and does not
+//     depend on scheduling.  A node's local id is its rank in the union of the bitmaps.
 //   * launch sizes come from upper bounds (seeds x fan-outs); the real frontier sizes stay on the
 //     device.  The one wait is at the end, for the three counts handed to the host.
+// A two-hop sample is bound by the number of launches and by the latency of the draws' dependent reads.
+// 4096 seeds, fan-outs 25 and 10, graph of 1.5 M nodes: 23 launches and 178 us with one mark per node and
+// scans over all of them; eight launches now.
 #include "common.h"
 
 namespace e2eg {
@@ -116,7 +119,35 @@ __global__ void fill_i32(int32_t* __restrict__ p, int64_t count, int32_t v) {
     if (i < count) p[i] = v;
 }
 
-__global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, int32_t n, int32_t* hop_of,
+// ---- node sets -----------------------------------------------------------------------------------------
+// levels[h] (words 64-bit words each): h = 0 the seeds, h > 0 the nodes picked at hop h - 1, whether or not
+// they were reached before.
+constexpr int kSetThreads = 1024;   // one word a thread
+constexpr int64_t kSetFew = 64;     // up to this many tiles of words a workgroup counts what is before its own
+
+struct Levels {
+    uint64_t* bits;
+    int64_t words;
+    // the nodes first reached at level h
+    __device__ __forceinline__ uint64_t fresh(int h, int64_t w) const {
+        uint64_t v = bits[h * words + w];
+        for (int k = 0; k < h; ++k) v &= ~bits[k * words + w];
+        return v;
+    }
+    // all nodes of levels 0 .. h
+    __device__ __forceinline__ uint64_t all(int h, int64_t w) const {
+        uint64_t v = bits[w];
+        for (int k = 1; k <= h; ++k) v |= bits[k * words + w];
+        return v;
+    }
+    __device__ __forceinline__ void add(int h, int32_t v) const {
+        uint64_t* word = bits + h * words + (v >> 6);
+        const uint64_t bit = 1ull << (v & 63);
+        if (!(*word & bit)) atomicOr(reinterpret_cast<unsigned long long*>(word), (unsigned long long)bit);
+    }
+};
+
+__global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, int32_t n, Levels levels,
                            int32_t* __restrict__ bad) {
     const int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n_seeds) return;
@@ -125,25 +156,79 @@ __global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, i
         atomicOr(bad, 1);
         return;
     }
-    hop_of[v] = 1;
+    levels.add(0, v);
 }
 
-// flags[i] = 1 where hop_of[i] matches (`level` > 0: equal to it; `level` == 0: any visited node);
-// flags[n] = 0 closes the scan.
-__global__ void level_flags(const int32_t* __restrict__ hop_of, int32_t n, int32_t level, int32_t* __restrict__ flags) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i > n) return;
-    int32_t f = 0;
-    if (i < n) f = level > 0 ? (hop_of[i] == level) : (hop_of[i] > 0);
-    flags[i] = f;
+template <typename V>
+__device__ __forceinline__ V sum_block(V v, V* lds) {   // over kSetThreads threads, in every thread
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    V t = 0;
+#pragma unroll
+    for (int w = 0; w < kSetThreads / 64; ++w) t += lds[w];
+    return t;
 }
 
-__global__ void scatter_level(const int32_t* __restrict__ hop_of, int32_t n, int32_t level,
-                              const int32_t* __restrict__ pos, int32_t* __restrict__ out, int64_t capacity) {
-    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const bool hit = level > 0 ? (hop_of[i] == level) : (hop_of[i] > 0);
-    if (hit && pos[i] < capacity) out[pos[i]] = i;
+// Nodes per tile of words (large node counts only).
+__global__ __launch_bounds__(kSetThreads) void count_set(Levels levels, int level, bool all, int32_t* __restrict__ tile_cnt) {
+    __shared__ int32_t lds[kSetThreads / 64];
+    const int64_t w = (int64_t)blockIdx.x * kSetThreads + threadIdx.x;
+    const int32_t c = w < levels.words ? __popcll(all ? levels.all(level, w) : levels.fresh(level, w)) : 0;
+    const int32_t t = sum_block(c, lds);
+    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = t;
+}
+
+// The set as an ascending list, and its size in *total.  RANKS (the set of all nodes): rank[w] = nodes before
+// word w, for words + 1 words, and `boundary` is the rank of node n_users.  COUNTED: tile_cnt holds the number of nodes
+// before each tile, else it is counted here.
+template <bool RANKS, bool COUNTED>
+__global__ __launch_bounds__(kSetThreads) void list_set(Levels levels, int level, const int32_t* __restrict__ tile_cnt,
+                                                        int32_t* __restrict__ out, int64_t capacity,
+                                                        int32_t* __restrict__ total, int32_t* __restrict__ rank,
+                                                        uint64_t* __restrict__ set, int32_t n_users,
+                                                        int32_t* __restrict__ boundary) {
+    __shared__ int32_t lds[kSetThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto word = [&](int64_t w) { return RANKS ? levels.all(level, w) : levels.fresh(level, w); };
+    const int64_t w = (int64_t)blockIdx.x * kSetThreads + threadIdx.x;
+    uint64_t bits = w < levels.words ? word(w) : 0ull;
+    int32_t before = 0;
+    if (COUNTED) {
+        before = tile_cnt[blockIdx.x];
+    } else {
+#pragma unroll 4
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x * kSetThreads; t += kSetThreads) before += __popcll(word(t));
+        before = sum_block(before, lds);
+    }
+    const int32_t c = __popcll(bits);
+    int32_t inc = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int32_t t = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += t;
+    }
+    __syncthreads();
+    if (lane == 63) lds[wave] = inc;
+    __syncthreads();
+    int32_t at = before + inc - c;
+#pragma unroll
+    for (int v = 0; v < kSetThreads / 64; ++v)
+        if (v < wave) at += lds[v];
+    if (w >= levels.words) return;
+    if (RANKS) {
+        rank[w] = at;
+        set[w] = bits;
+        if (w == n_users >> 6) *boundary = at + __popcll(bits & ((1ull << (n_users & 63)) - 1));
+    }
+    if (w == levels.words - 1) *total = at + c;
+    while (bits) {
+        const int b = __ffsll((unsigned long long)bits) - 1;
+        if (at < capacity) out[at] = (int32_t)(w * 64 + b);
+        ++at;
+        bits &= bits - 1;
+    }
 }
 
 struct Philox {
@@ -167,20 +252,52 @@ __device__ __forceinline__ Philox philox4x32_10(Philox x, uint32_t k0, uint32_t 
     return x;
 }
 
-// One thread per (frontier position f, draw t) of hop `hop`, for the upper bound `front_cap` of the
-// frontier's size; the real size is *front_count.  Every slot of the hop is written: the source
-// node, the picked neighbour (or -1: no pick) and the index of the stored entry.
-__global__ void draw_picks(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                           const uint64_t* __restrict__ cum, const int32_t* __restrict__ frontier,
-                           const int32_t* __restrict__ front_count, int64_t front_cap, int32_t k, int32_t hop,
-                           uint32_t seed_lo, uint32_t seed_hi, int32_t* hop_of, int32_t* __restrict__ slot_src,
-                           int32_t* __restrict__ slot_dst, int32_t* __restrict__ slot_ent) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= front_cap * k) return;
-    const int64_t f = s / k;
-    const int32_t t = (int32_t)(s - f * k);
+// Smallest e in [beg, end) with cum[e + 1] - base > r, which is known to exist.  Seven pivots a step, their
+// loads in flight together: a step costs the latency of one read, and a row of 2000 takes four of them
+// instead of eleven.
+__device__ __forceinline__ int32_t pick_entry(const uint64_t* __restrict__ cum, int32_t beg, int32_t end, uint64_t base,
+                                              uint64_t r) {
+    int32_t lo = beg, hi = end - 1;
+    while (hi - lo >= 8) {
+        const int32_t step = (int32_t)(((int64_t)hi - lo + 1) >> 3);
+        int below = 0;
+#pragma unroll
+        for (int k = 1; k < 8; ++k) below += cum[lo + k * step] - base > r ? 0 : 1;
+        if (below < 7) hi = lo + (below + 1) * step - 1;
+        lo += below * step;
+    }
+    int below = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k)
+        if (lo + k <= hi) below += cum[lo + k] - base > r ? 0 : 1;
+    return lo + below;
+}
+
+// One thread per (frontier position f, draw t) of hop `hop`, for the upper bound of the frontier's size that
+// sized the launch; the real size is *front_count.  Every slot of a tile that has any is written: the source
+// node, the picked neighbour (or -1: no pick) and the index of the stored entry; and the tile's number of picks.
+constexpr int kDrawThreads = 512;   // slots per tile
+__global__ __launch_bounds__(kDrawThreads) void draw_picks(const int32_t* __restrict__ row_ptr,
+                                                           const int32_t* __restrict__ col_idx,
+                                                           const uint64_t* __restrict__ cum,
+                                                           const int32_t* __restrict__ frontier,
+                                                           const int32_t* __restrict__ front_count, int32_t k, int32_t hop,
+                                                           uint32_t seed_lo, uint32_t seed_hi, Levels levels,
+                                                           int32_t* __restrict__ slot_src, int32_t* __restrict__ slot_dst,
+                                                           int32_t* __restrict__ slot_ent, int32_t* __restrict__ tile_cnt) {
+    __shared__ int32_t picks;
+    const int64_t s = (int64_t)blockIdx.x * kDrawThreads + threadIdx.x;
+    const int64_t slots = (int64_t)*front_count * k;
+    if ((int64_t)blockIdx.x * kDrawThreads >= slots) {
+        if (threadIdx.x == 0) tile_cnt[blockIdx.x] = 0;
+        return;
+    }
+    if (threadIdx.x == 0) picks = 0;
+    __syncthreads();
     int32_t u = -1, v = -1, ent = -1;
-    if (f < *front_count) {
+    if (s < slots) {
+        const int64_t f = s / k;
+        const int32_t t = (int32_t)(s - f * k);
         u = frontier[f];
         const int32_t beg = row_ptr[u], end = row_ptr[u + 1];
         // A node with at most k neighbours keeps every one that can be drawn at all.  Its row may
@@ -210,64 +327,83 @@ __global__ void draw_picks(const int32_t* __restrict__ row_ptr, const int32_t* _
                 x.c[3] = 0u;
                 x = philox4x32_10(x, seed_lo, seed_hi);
                 const uint64_t bits = (uint64_t)x.c[0] | ((uint64_t)x.c[1] << 32);
-                const uint64_t r = __umul64hi(bits, total);  // uniform on [0, total)
-                int32_t lo = beg, hi = end - 1;              // smallest e with cum[e + 1] - base > r
-                while (lo < hi) {
-                    const int32_t mid = lo + ((hi - lo) >> 1);
-                    if (cum[mid + 1] - base > r) hi = mid; else lo = mid + 1;
-                }
-                ent = lo;
+                ent = pick_entry(cum, beg, end, base, __umul64hi(bits, total));  // uniform on [0, total)
             }
         }
         if (ent >= 0) {
             v = col_idx[ent];
-            atomicCAS(hop_of + v, 0, hop + 2);
+            levels.add(hop + 1, v);
         }
     }
     slot_src[s] = u;
     slot_dst[s] = v;
     slot_ent[s] = ent;
-}
-
-__global__ void slot_flags(const int32_t* __restrict__ slot_dst, int64_t slots, int32_t* __restrict__ flags) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s > slots) return;
-    flags[s] = (s < slots && slot_dst[s] >= 0) ? 1 : 0;
+    const int32_t c = __popcll(__ballot(v >= 0));
+    if ((threadIdx.x & 63) == 0 && c > 0) atomicAdd(&picks, c);
+    __syncthreads();
+    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = picks;
 }
 
 // Picks in slot order -> (local user, local item[, weight]); an entry that joins two nodes of the
-// same side is reported through `bad`.
-__global__ void emit_edges(const int32_t* __restrict__ slot_src, const int32_t* __restrict__ slot_dst,
-                           const int32_t* __restrict__ slot_ent, const int32_t* __restrict__ pos, int64_t slots,
-                           const int32_t* __restrict__ local_of, int32_t n_users, const float* __restrict__ val,
-                           int32_t* __restrict__ edge_users, int32_t* __restrict__ edge_items,
-                           float* __restrict__ edge_w, int32_t* __restrict__ bad) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= slots) return;
+// same side is reported through counts[3].  Local ids are ranks in the set of all nodes.  SCANNED: tile_cnt holds the
+// number of picks before each tile, else the tiles' own.
+struct Ranks {
+    const uint64_t* set;
+    const int32_t* rank;
+    __device__ __forceinline__ int32_t of(int32_t v) const {
+        return rank[v >> 6] + __popcll(set[v >> 6] & ((1ull << (v & 63)) - 1));
+    }
+};
+template <bool SCANNED>
+__global__ __launch_bounds__(kDrawThreads) void emit_edges(const int32_t* __restrict__ slot_src,
+                                                           const int32_t* __restrict__ slot_dst,
+                                                           const int32_t* __restrict__ slot_ent,
+                                                           const int32_t* __restrict__ tile_cnt, Ranks ranks,
+                                                           int32_t n_users, const float* __restrict__ val,
+                                                           int32_t* __restrict__ edge_users, int32_t* __restrict__ edge_items,
+                                                           float* __restrict__ edge_w, int32_t* __restrict__ n_edges,
+                                                           const int32_t* __restrict__ boundary, int32_t* __restrict__ bad) {
+    __shared__ int32_t lds[kDrawThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int32_t own = SCANNED ? tile_cnt[blockIdx.x + 1] - tile_cnt[blockIdx.x] : tile_cnt[blockIdx.x];
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (own == 0 && !last) return;
+    int32_t at = 0;
+    if (SCANNED) {
+        at = tile_cnt[blockIdx.x];
+    } else {
+#pragma unroll 4
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kDrawThreads) at += tile_cnt[t];
+        for (int off = 32; off > 0; off >>= 1) at += __shfl_xor(at, off);
+        if (lane == 0) lds[wave] = at;
+        __syncthreads();
+        at = 0;
+#pragma unroll
+        for (int w = 0; w < kDrawThreads / 64; ++w) at += lds[w];
+        __syncthreads();
+    }
+    if (last && threadIdx.x == 0) *n_edges = at + own;
+    if (own == 0) return;
+    const int64_t s = (int64_t)blockIdx.x * kDrawThreads + threadIdx.x;
     const int32_t a = slot_src[s], b = slot_dst[s];
+    const uint64_t bal = __ballot(b >= 0);
+    if (lane == 0) lds[wave] = __popcll(bal);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kDrawThreads / 64; ++w)
+        if (w < wave) at += lds[w];
     if (b < 0) return;
+    at += __popcll(bal & ((1ull << lane) - 1));
     const int32_t user = a < b ? a : b, item = a < b ? b : a;
-    const int32_t at = pos[s];
     if (user >= n_users || item < n_users) {
         atomicOr(bad, 2);
         edge_users[at] = 0;
         edge_items[at] = 0;
     } else {
-        edge_users[at] = local_of[user];
-        edge_items[at] = local_of[item] - local_of[n_users];
+        edge_users[at] = ranks.of(user);
+        edge_items[at] = ranks.of(item) - *boundary;
     }
     if (edge_w) edge_w[at] = val[slot_ent[s]];
-}
-
-__global__ void gather_counts(const int32_t* __restrict__ local_of, int32_t n_users, int32_t n,
-                              const int32_t* __restrict__ n_edges, const int32_t* __restrict__ bad,
-                              int32_t* __restrict__ out) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        out[0] = local_of[n_users];
-        out[1] = local_of[n] - local_of[n_users];
-        out[2] = *n_edges;
-        out[3] = *bad;
-    }
 }
 
 // Upper bounds that size the launches: cap_front[h] >= size of the frontier of hop h, slots[h] =
@@ -296,33 +432,77 @@ int32_t check_plan(const char* who, int32_t n, int32_t n_seeds, int32_t L, const
 }
 
 struct SampleWs {
-    int32_t* hop_of;    // [n + 1]
-    int32_t* local_of;  // [n + 1] flags, then their prefix sums
+    int32_t* small;     // [64]: [0] local users, [1] nodes, [2] edges, [3] bad; [8 ..] frontier sizes
+    uint64_t* bits;     // [L + 1][words], behind `small` so that one launch clears both
+    int64_t words;
+    int64_t zero_count; // in int32
+    uint64_t* set;      // [words] all nodes
+    int32_t* rank;      // [words]
     int32_t* frontier;  // [max cap_front]
-    int32_t* slot_src;  // [slots]
+    int32_t* slot_src;  // [slot tiles * kDrawThreads]
     int32_t* slot_dst;
     int32_t* slot_ent;
-    int32_t* slot_pos;  // [slots + 1]
-    int32_t* small;     // [64]: [0..7] frontier sizes, [8] nodes, [9] edges, [10] bad, [16..19] counts for the host
+    int32_t* tile_cnt;  // [slot tiles + 1]
+    int32_t* set_cnt;   // [tiles of words]
     void* scan_ws;
     size_t bytes;
 };
 
-SampleWs carve_sample(void* base, int64_t n, int64_t max_front, int64_t slots) {
+constexpr int64_t kDrawFew = 4096;   // up to this many slot tiles emit_edges adds up the counts before its own
+
+int64_t slot_tiles(int32_t L, const int64_t* cap_front, const int32_t* fanout, int64_t* tile_base) {
+    int64_t tiles = 0;
+    for (int32_t h = 0; h < L; ++h) {
+        tile_base[h] = tiles;
+        tiles += ceil_div(cap_front[h] * fanout[h], kDrawThreads);
+    }
+    return tiles;
+}
+
+SampleWs carve_sample(void* base, int64_t n, int32_t L, int64_t max_front, int64_t tiles) {
     Carver c(base);
     SampleWs w;
-    w.hop_of = c.take<int32_t>(n + 1);
-    w.local_of = c.take<int32_t>(n + 1);
+    w.words = n / 64 + 1;   // one bit past the last node, whose rank is asked for
+    char* zeroed = c.take<char>(64 * sizeof(int32_t) + (size_t)(L + 1) * (size_t)w.words * sizeof(uint64_t));
+    w.small = reinterpret_cast<int32_t*>(zeroed);
+    w.bits = zeroed ? reinterpret_cast<uint64_t*>(zeroed + 64 * sizeof(int32_t)) : nullptr;
+    w.zero_count = 64 + 2 * (int64_t)(L + 1) * w.words;
+    w.set = c.take<uint64_t>(w.words);
+    w.rank = c.take<int32_t>(w.words);
     w.frontier = c.take<int32_t>(max_front > 0 ? max_front : 1);
-    w.slot_src = c.take<int32_t>(slots > 0 ? slots : 1);
-    w.slot_dst = c.take<int32_t>(slots > 0 ? slots : 1);
-    w.slot_ent = c.take<int32_t>(slots > 0 ? slots : 1);
-    w.slot_pos = c.take<int32_t>(slots + 1);
-    w.small = c.take<int32_t>(64);
-    const int64_t longest = (n + 1 > slots + 1) ? n + 1 : slots + 1;
+    w.slot_src = c.take<int32_t>(tiles * kDrawThreads + 1);
+    w.slot_dst = c.take<int32_t>(tiles * kDrawThreads + 1);
+    w.slot_ent = c.take<int32_t>(tiles * kDrawThreads + 1);
+    w.tile_cnt = c.take<int32_t>(tiles + 1);
+    const int64_t set_tiles = ceil_div(w.words, kSetThreads);
+    w.set_cnt = c.take<int32_t>(set_tiles);
+    const int64_t longest = set_tiles > tiles + 1 ? set_tiles : tiles + 1;
     w.scan_ws = c.take<char>(scan_workspace_bytes(longest));
     w.bytes = c.size();
     return w;
+}
+
+// The nodes of one level (or of all levels up to it: `ranks`) as a list.
+int32_t run_list(const SampleWs& w, const Levels& levels, int level, bool ranks, int32_t* out, int64_t capacity, int32_t* total,
+                 int32_t n_users, hipStream_t stream) {
+    const int64_t tiles = ceil_div(levels.words, kSetThreads);
+    const dim3 grid((unsigned)tiles), blk(kSetThreads);
+    const bool counted = tiles > kSetFew;
+    if (counted) {
+        count_set<<<grid, blk, 0, stream>>>(levels, level, ranks, w.set_cnt);
+        E2EG_LAUNCH_CHECK("count_set");
+        E2EG_HIP_TRY(exclusive_scan_i32(w.set_cnt, w.set_cnt, tiles, nullptr, w.scan_ws, stream));
+    }
+    if (ranks && counted)
+        list_set<true, true><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
+    else if (ranks)
+        list_set<true, false><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
+    else if (counted)
+        list_set<false, true><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
+    else
+        list_set<false, false><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
+    E2EG_LAUNCH_CHECK("list_set");
+    return E2EG_OK;
 }
 
 }  // namespace
@@ -400,7 +580,8 @@ extern "C" size_t e2eg_sample_subgraph_workspace_bytes(int32_t n, int32_t n_seed
     if (slots < 0) return 0;
     int64_t max_front = 0;
     for (int32_t h = 0; h < L; ++h) max_front = cap_front[h] > max_front ? cap_front[h] : max_front;
-    return carve_sample(nullptr, n, max_front, slots).bytes;
+    int64_t tile_base[kMaxHops];
+    return carve_sample(nullptr, n, L, max_front, slot_tiles(L, cap_front, h_fanout, tile_base)).bytes;
 }
 
 extern "C" int32_t e2eg_sample_subgraph(int32_t n_users, int32_t n, int64_t nnz, const int32_t* d_row_ptr,
@@ -430,57 +611,56 @@ extern "C" int32_t e2eg_sample_subgraph(int32_t n_users, int32_t n, int64_t nnz,
         return fail(E2EG_ERR_NULL_PTR, "%s: null output pointer", who);
     int64_t max_front = 0;
     for (int32_t h = 0; h < L; ++h) max_front = cap_front[h] > max_front ? cap_front[h] : max_front;
-    const size_t need = carve_sample(nullptr, n, max_front, slots).bytes;
+    int64_t tile_base[kMaxHops];
+    const int64_t tiles = slot_tiles(L, cap_front, h_fanout, tile_base);
+    const size_t need = carve_sample(nullptr, n, L, max_front, tiles).bytes;
     if (!ws || !aligned_to(ws, kAlign) || ws_bytes < need)
         return fail(E2EG_ERR_WORKSPACE, "%s: workspace needs %zu bytes, 256-byte aligned", who, need);
     h_counts[0] = h_counts[1] = h_counts[2] = 0;
     if (n == 0 || n_seeds == 0) return E2EG_OK;
 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    const SampleWs w = carve_sample(ws, n, max_front, slots);
+    const SampleWs w = carve_sample(ws, n, L, max_front, tiles);
     const uint64_t* cum = static_cast<const uint64_t*>(d_table);
     const dim3 blk(kThreads);
-    fill_i32<<<grid_for((int64_t)n + 1), blk, 0, stream>>>(w.hop_of, (int64_t)n + 1, 0);
+    const Levels levels{w.bits, w.words};
+    fill_i32<<<grid_for(w.zero_count), blk, 0, stream>>>(w.small, w.zero_count, 0);
     E2EG_LAUNCH_CHECK("fill_i32");
-    fill_i32<<<dim3(1), dim3(64), 0, stream>>>(w.small, 64, 0);
-    E2EG_LAUNCH_CHECK("fill_i32");
-    mark_seeds<<<grid_for(n_seeds), blk, 0, stream>>>(d_seeds, n_seeds, n, w.hop_of, w.small + 10);
+    mark_seeds<<<grid_for(n_seeds), blk, 0, stream>>>(d_seeds, n_seeds, n, levels, w.small + 3);
     E2EG_LAUNCH_CHECK("mark_seeds");
     for (int32_t h = 0; h < L; ++h) {
-        // the frontier of hop h, ascending: nodes whose mark is h + 1
-        level_flags<<<grid_for((int64_t)n + 1), blk, 0, stream>>>(w.hop_of, n, h + 1, w.local_of);
-        E2EG_LAUNCH_CHECK("level_flags");
-        E2EG_HIP_TRY(exclusive_scan_i32(w.local_of, w.local_of, (int64_t)n + 1, w.small + h, w.scan_ws, stream));
-        scatter_level<<<grid_for(n), blk, 0, stream>>>(w.hop_of, n, h + 1, w.local_of, w.frontier, cap_front[h]);
-        E2EG_LAUNCH_CHECK("scatter_level");
-        draw_picks<<<grid_for(cap_front[h] * h_fanout[h]), blk, 0, stream>>>(
-            d_row_ptr, d_col_idx, cum, w.frontier, w.small + h, cap_front[h], h_fanout[h], h, (uint32_t)seed,
-            (uint32_t)(seed >> 32), w.hop_of, w.slot_src + slot_base[h], w.slot_dst + slot_base[h],
-            w.slot_ent + slot_base[h]);
+        // the frontier of hop h, ascending: nodes first reached at level h
+        int32_t* size = w.small + 8 + h;
+        if ((st = run_list(w, levels, h, false, w.frontier, cap_front[h], size, n_users, stream)) != E2EG_OK) return st;
+        const int64_t at = tile_base[h] * kDrawThreads;
+        draw_picks<<<dim3((unsigned)ceil_div(cap_front[h] * h_fanout[h], kDrawThreads)), dim3(kDrawThreads), 0, stream>>>(
+            d_row_ptr, d_col_idx, cum, w.frontier, size, h_fanout[h], h, (uint32_t)seed, (uint32_t)(seed >> 32), levels,
+            w.slot_src + at, w.slot_dst + at, w.slot_ent + at, w.tile_cnt + tile_base[h]);
         E2EG_LAUNCH_CHECK("draw_picks");
     }
-    // local numbering: visited nodes in ascending order (users first, as in the parent)
-    level_flags<<<grid_for((int64_t)n + 1), blk, 0, stream>>>(w.hop_of, n, 0, w.local_of);
-    E2EG_LAUNCH_CHECK("level_flags");
-    E2EG_HIP_TRY(exclusive_scan_i32(w.local_of, w.local_of, (int64_t)n + 1, w.small + 8, w.scan_ws, stream));
-    scatter_level<<<grid_for(n), blk, 0, stream>>>(w.hop_of, n, 0, w.local_of, d_nodes, node_capacity);
-    E2EG_LAUNCH_CHECK("scatter_level");
+    // local numbering: all nodes in ascending order (users first, as in the parent)
+    if ((st = run_list(w, levels, L, true, d_nodes, node_capacity, w.small + 1, n_users, stream)) != E2EG_OK) return st;
     // the picks, without the empty slots, in slot order
-    slot_flags<<<grid_for(slots + 1), blk, 0, stream>>>(w.slot_dst, slots, w.slot_pos);
-    E2EG_LAUNCH_CHECK("slot_flags");
-    E2EG_HIP_TRY(exclusive_scan_i32(w.slot_pos, w.slot_pos, slots + 1, w.small + 9, w.scan_ws, stream));
-    emit_edges<<<grid_for(slots), blk, 0, stream>>>(w.slot_src, w.slot_dst, w.slot_ent, w.slot_pos, slots, w.local_of,
-                                                     n_users, d_val, d_edge_users, d_edge_items, d_edge_w, w.small + 10);
+    const dim3 edge_grid((unsigned)tiles), edge_blk(kDrawThreads);
+    const Ranks ranks{w.set, w.rank};
+    if (tiles > kDrawFew) {
+        fill_i32<<<dim3(1), dim3(64), 0, stream>>>(w.tile_cnt + tiles, 1, 0);
+        E2EG_LAUNCH_CHECK("fill_i32");
+        E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, tiles + 1, nullptr, w.scan_ws, stream));
+        emit_edges<true><<<edge_grid, edge_blk, 0, stream>>>(w.slot_src, w.slot_dst, w.slot_ent, w.tile_cnt, ranks, n_users, d_val,
+                                                            d_edge_users, d_edge_items, d_edge_w, w.small + 2, w.small, w.small + 3);
+    } else {
+        emit_edges<false><<<edge_grid, edge_blk, 0, stream>>>(w.slot_src, w.slot_dst, w.slot_ent, w.tile_cnt, ranks, n_users, d_val,
+                                                             d_edge_users, d_edge_items, d_edge_w, w.small + 2, w.small, w.small + 3);
+    }
     E2EG_LAUNCH_CHECK("emit_edges");
-    gather_counts<<<dim3(1), dim3(64), 0, stream>>>(w.local_of, n_users, n, w.small + 9, w.small + 10, w.small + 16);
-    E2EG_LAUNCH_CHECK("gather_counts");
     int32_t host[4] = {0, 0, 0, 0};
-    E2EG_HIP_TRY(hipMemcpyAsync(host, w.small + 16, sizeof(host), hipMemcpyDeviceToHost, stream));
+    E2EG_HIP_TRY(hipMemcpyAsync(host, w.small, sizeof(host), hipMemcpyDeviceToHost, stream));
     E2EG_HIP_TRY(hipStreamSynchronize(stream));  // the one wait: the counts size what the caller does next
     if (host[3] & 1) return fail(E2EG_ERR_BAD_INDEX, "%s: a seed is out of range", who);
     if (host[3] & 2) return fail(E2EG_ERR_BAD_INDEX, "%s: a stored entry joins two users or two items", who);
     h_counts[0] = host[0];
-    h_counts[1] = host[1];
+    h_counts[1] = host[1] - host[0];
     h_counts[2] = host[2];
     return E2EG_OK;
 }
