@@ -50,11 +50,15 @@ inline dim3 grid_for(int64_t count) { return dim3((unsigned)ceil_div(count > 0 ?
 // ---- row tiles ---------------------------------------------------------------------------------
 // Row work goes by tiles of kSortBlock rows, one workgroup each; every workgroup adds up what the
 // tiles before it counted, which saves the launches of a scan (a few thousand tiles at most).
-constexpr int kTileRows = kSortBlock;
+// (Small form: tiles of a quarter of that, or a graph of 170 k nodes fills 43 compute units.)
+template <bool SMALL>
+constexpr int kTileRows = SMALL ? kSortBlock / 4 : kSortBlock;
 constexpr int kTileThreads = 512;
 constexpr int kTileWaves = kTileThreads / 64;
-constexpr int kWaveRows = kTileRows / kTileWaves;   // consecutive rows of one wavefront
-constexpr int kRowRounds = kWaveRows / 64;
+template <bool SMALL>
+constexpr int kWaveRows = kTileRows<SMALL> / kTileWaves;   // consecutive rows of one wavefront
+template <bool SMALL>
+constexpr int kRowRounds = kWaveRows<SMALL> / 64;
 constexpr int kTotals = 8;   // per tile: entries, short rows, one-segment rows, split rows, slots, chunks
 enum { kTotEntries, kTotShort, kTotSingle, kTotMulti, kTotSlots, kTotChunks, kTotUsed };
 constexpr int kChunk = 2048;   // large form: entries of a split row that one workgroup puts in place
@@ -119,9 +123,9 @@ __global__ __launch_bounds__(kTileThreads) void row_stats(const int32_t* __restr
     __syncthreads();
     const int lane = threadIdx.x & 63;
     int32_t tot[kTotUsed] = {};
-    const int64_t base = (int64_t)blockIdx.x * kTileRows;
+    const int64_t base = (int64_t)blockIdx.x * kTileRows<SMALL>;
 #pragma unroll
-    for (int r = 0; r < kTileRows / kTileThreads; ++r) {
+    for (int r = 0; r < kTileRows<SMALL> / kTileThreads; ++r) {
         const int64_t i = base + r * kTileThreads + threadIdx.x;
         int c = -1;
         if (i < n) {
@@ -163,9 +167,9 @@ __global__ __launch_bounds__(kTileThreads) void row_totals(const int32_t* __rest
                                                            int32_t* __restrict__ totals) {
     __shared__ int32_t red[kTileWaves][kTotUsed];
     int32_t tot[kTotUsed] = {};
-    const int64_t base = (int64_t)blockIdx.x * kTileRows;
+    const int64_t base = (int64_t)blockIdx.x * kTileRows<false>;
 #pragma unroll
-    for (int r = 0; r < kTileRows / kTileThreads; ++r) {
+    for (int r = 0; r < kTileRows<false> / kTileThreads; ++r) {
         const int64_t p = base + r * kTileThreads + threadIdx.x;
         if (p < n) count_row(zdeg[p], p, wide_rows, wide_min, tot);
     }
@@ -215,7 +219,7 @@ __device__ __forceinline__ Threshold find_threshold(const int32_t* classes, int3
 }
 
 // Per tile of nodes: how many lie above the threshold class, how many in it.
-template <int OCT>
+template <bool SMALL, int OCT>
 __global__ __launch_bounds__(kTileThreads) void count_top(const int32_t* __restrict__ row_ptr, int64_t n,
                                                           const int32_t* __restrict__ classes,
                                                           int32_t* __restrict__ top_totals) {
@@ -223,9 +227,9 @@ __global__ __launch_bounds__(kTileThreads) void count_top(const int32_t* __restr
     __shared__ int32_t lds[kTileWaves];
     const Threshold th = find_threshold<OCT>(classes, lds);
     int32_t v[2] = {0, 0};
-    const int64_t base = (int64_t)blockIdx.x * kTileRows;
+    const int64_t base = (int64_t)blockIdx.x * kTileRows<SMALL>;
 #pragma unroll
-    for (int r = 0; r < kTileRows / kTileThreads; ++r) {
+    for (int r = 0; r < kTileRows<SMALL> / kTileThreads; ++r) {
         const int64_t i = base + r * kTileThreads + threadIdx.x;
         if (i < n) {
             const int c = degree_class<OCT>(row_ptr[i + 1] - row_ptr[i]);
@@ -259,12 +263,12 @@ __device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr,
     const int32_t n_top = n < kTopNodes ? (int32_t)n : kTopNodes;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t base = (int64_t)blockIdx.x * kTileRows + wave * kWaveRows;
-    int32_t d[kRowRounds];
-    uint64_t above[kRowRounds], tied[kRowRounds];
+    const int64_t base = (int64_t)blockIdx.x * kTileRows<SMALL> + wave * kWaveRows<SMALL>;
+    int32_t d[kRowRounds<SMALL>];
+    uint64_t above[kRowRounds<SMALL>], tied[kRowRounds<SMALL>];
     int32_t run[2] = {0, 0};
 #pragma unroll
-    for (int r = 0; r < kRowRounds; ++r) {
+    for (int r = 0; r < kRowRounds<SMALL>; ++r) {
         const int64_t i = base + r * 64 + lane;
         d[r] = i < n ? row_ptr[i + 1] - row_ptr[i] : 0;
         const int c = i < n ? degree_class<SMALL ? kSmallOct : kLargeOct>(d[r]) : -2;
@@ -286,7 +290,7 @@ __device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr,
             before[1] += red[w][1];
         }
 #pragma unroll
-    for (int r = 0; r < kRowRounds; ++r) {
+    for (int r = 0; r < kRowRounds<SMALL>; ++r) {
         const int64_t i = base + r * 64 + lane;
         const int32_t a = before[0] + __popcll(above[r] & lt_mask), t = before[1] + __popcll(tied[r] & lt_mask);
         const int32_t top_before = a + (t < room ? t : room);
@@ -352,14 +356,17 @@ __global__ __launch_bounds__(kRankThreads) void rank_top(int32_t n_top, SchedVie
     const int c = blockIdx.x * (kRankThreads / kRankLanes) + (int)threadIdx.x / kRankLanes;
     const int32_t d = c < n_top ? deg[c] : 0;
     int32_t rank = 0;
+    // One comparison each: node k comes before node c iff deg[k] + (k < c) > d, and k < c is the same for a whole
+    // group of four but the one that holds c.
+    const int c4 = c & ~3;
 #pragma unroll 8
     for (int k = 4 * (threadIdx.x % kRankLanes); k < n_top; k += 4 * kRankLanes) {
         const int4 v = *reinterpret_cast<const int4*>(deg + k);
-        rank += v.x > d || (v.x == d && k < c) ? 1 : 0;
-        rank += v.y > d || (v.y == d && k + 1 < c) ? 1 : 0;
-        rank += v.z > d || (v.z == d && k + 2 < c) ? 1 : 0;
-        rank += v.w > d || (v.w == d && k + 3 < c) ? 1 : 0;
+        const int32_t bar = k < c4 ? d - 1 : d;
+        rank += (v.x > bar ? 1 : 0) + (v.y > bar ? 1 : 0) + (v.z > bar ? 1 : 0) + (v.w > bar ? 1 : 0);
     }
+    if (threadIdx.x % kRankLanes == 0 && c < n_top)
+        for (int k = c4; k < c; ++k) rank += deg[k] == d ? 1 : 0;
 #pragma unroll
     for (int off = kRankLanes / 2; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
     if (c < n_top && threadIdx.x % kRankLanes == 0) {
@@ -399,18 +406,18 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
     __shared__ int32_t red[kTileWaves][2 * kTotUsed];
     __shared__ int32_t wave_cnt[kTileWaves][kDigits];
     __shared__ int32_t first[kDigits];     // place of the digit's first row in the tile
-    __shared__ uint16_t sorted[kTileRows]; // rows of the tile in digit order
-    __shared__ int32_t beg[kTileRows];     // first entry of every row of the tile
-    __shared__ int32_t slot0[kTileRows];   // split rows: first slot, and first piece (large form)
-    __shared__ int32_t chunk0[SMALL ? 1 : kTileRows];
+    __shared__ uint16_t sorted[kTileRows<SMALL>]; // rows of the tile in digit order
+    __shared__ int32_t beg[kTileRows<SMALL>];     // first entry of every row of the tile
+    __shared__ int32_t slot0[kTileRows<SMALL>];   // split rows: first slot, and first piece (large form)
+    __shared__ int32_t chunk0[SMALL ? 1 : kTileRows<SMALL>];
     __shared__ int32_t wave_chunks[kTileWaves];
     constexpr int kThreadSegs = 8;
     __shared__ int32_t wave_tot[kTileWaves];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t base = (int64_t)blockIdx.x * kTileRows;
-    const int rows = n - base < kTileRows ? (int)(n - base) : kTileRows;
+    const int64_t base = (int64_t)blockIdx.x * kTileRows<SMALL>;
+    const int rows = n - base < kTileRows<SMALL> ? (int)(n - base) : kTileRows<SMALL>;
 
     int32_t before[kTotUsed] = {};
     for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kTileThreads)
@@ -423,11 +430,11 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
 
     for (int k = threadIdx.x; k < kTileWaves * kDigits; k += kTileThreads) (&wave_cnt[0][0])[k] = 0;
     __syncthreads();
-    int32_t len[kRowRounds], rank[kRowRounds];
-    int digit[kRowRounds];
+    int32_t len[kRowRounds<SMALL>], rank[kRowRounds<SMALL>];
+    int digit[kRowRounds<SMALL>];
 #pragma unroll
-    for (int r = 0; r < kRowRounds; ++r) {
-        const int at = wave * kWaveRows + r * 64 + lane;
+    for (int r = 0; r < kRowRounds<SMALL>; ++r) {
+        const int at = wave * kWaveRows<SMALL> + r * 64 + lane;
         const bool valid = at < rows;
         int32_t d = 0;
         if (valid) {
@@ -486,9 +493,9 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
     }
     if (!SMALL) {   // zrow_ptr: a wavefront's rows are consecutive, 64 a round
         int32_t run = 0;
-        int32_t inc[kRowRounds];
+        int32_t inc[kRowRounds<SMALL>];
 #pragma unroll
-        for (int r = 0; r < kRowRounds; ++r) {
+        for (int r = 0; r < kRowRounds<SMALL>; ++r) {
             int32_t v = len[r];
 #pragma unroll
             for (int dlt = 1; dlt < 64; dlt <<= 1) {
@@ -506,8 +513,8 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
         for (int w = 0; w < kTileWaves; ++w)
             if (w < wave) off += wave_tot[w];
 #pragma unroll
-        for (int r = 0; r < kRowRounds; ++r) {
-            const int at = wave * kWaveRows + r * 64 + lane;
+        for (int r = 0; r < kRowRounds<SMALL>; ++r) {
+            const int at = wave * kWaveRows<SMALL> + r * 64 + lane;
             if (at < rows) {
                 beg[at] = off + inc[r];
                 s.zrow_ptr[base + at] = off + inc[r];
@@ -517,8 +524,8 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kRowRounds; ++r) {
-        const int at = wave * kWaveRows + r * 64 + lane;
+    for (int r = 0; r < kRowRounds<SMALL>; ++r) {
+        const int at = wave * kWaveRows<SMALL> + r * 64 + lane;
         if (at < rows) sorted[wave_cnt[wave][digit[r]] + rank[r]] = (uint16_t)at;
     }
     __syncthreads();
@@ -1534,14 +1541,14 @@ struct NormWs {
     void* sort_ws;
     size_t bytes;
 };
-constexpr int64_t kFewTiles = 128;   // up to here a workgroup reads all tiles' class histograms (0.4 MB)
+constexpr int64_t kFewTiles = 256;   // up to here a workgroup reads all tiles' class histograms (0.27 MB)
 constexpr int kAsymAt = (kClasses<kLargeOct> + 63) / 64 * 64;
 constexpr int kZeroed = kAsymAt + (kSymCounters + 1) * kSymStride;
 
 NormWs carve_norm(void* base, int64_t n, int64_t nnz) {
     Carver c(base);
     NormWs w = {};
-    const int64_t tiles = ceil_div(n > 0 ? n : 1, kTileRows);
+    const int64_t tiles = ceil_div(n > 0 ? n : 1, sched_is_small(nnz) ? kTileRows<true> : kTileRows<false>);
     w.totals = c.take<int32_t>(tiles * kTotals);
     w.zeroed = c.take<int32_t>(kZeroed);
     w.top_totals = c.take<int32_t>(2 * tiles);
@@ -1584,7 +1591,7 @@ int32_t run_weighted_degrees(int64_t n, int64_t nnz, const int32_t* row_ptr, con
 
 int32_t normalize_small(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, const float* val, int32_t* deg,
                         float* deg_w, float* dinv, const SchedView& view, const NormWs& w, bool test, hipStream_t stream) {
-    const dim3 tiles((unsigned)ceil_div(n > 0 ? n : 1, kTileRows)), tile_blk(kTileThreads), blk(kThreads);
+    const dim3 tiles((unsigned)ceil_div(n > 0 ? n : 1, kTileRows<true>)), tile_blk(kTileThreads), blk(kThreads);
     if (w.tile_classes) {
         row_stats<true, true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, deg, dinv, w.totals, w.tile_classes);
         E2EG_LAUNCH_CHECK("row_stats");
@@ -1599,7 +1606,7 @@ int32_t normalize_small(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
         emit_rows<true, false><<<tiles, tile_blk, 0, stream>>>(row_ptr, nullptr, n, nnz, 0, 0, w.totals, view, view.segs,
                                                               w.chunks, nullptr, w.top);
         E2EG_LAUNCH_CHECK("emit_rows");
-        count_top<kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, w.zeroed, w.top_totals);
+        count_top<true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, w.zeroed, w.top_totals);
         E2EG_LAUNCH_CHECK("count_top");
         number_nodes<true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, w.zeroed, w.top_totals, view, w.top);
         E2EG_LAUNCH_CHECK("number_nodes");
@@ -1631,7 +1638,7 @@ int32_t normalize_small(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
 int32_t normalize_large(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, const float* val, int32_t* deg,
                         float* deg_w, float* dinv, const SchedView& view, const NormWs& w, bool test, hipStream_t stream) {
     const dim3 blk(kThreads), tile_blk(kTileThreads);
-    const dim3 tiles((unsigned)ceil_div(n > 0 ? n : 1, kTileRows));
+    const dim3 tiles((unsigned)ceil_div(n > 0 ? n : 1, kTileRows<false>));
     const int32_t wide_rows = (int32_t)sched_max_wide_rows(n, nnz);
     const int32_t wide_min = (int32_t)sched_wide_threshold(n);
     const int32_t nwin = (int32_t)sched_windows(n);
@@ -1643,7 +1650,7 @@ int32_t normalize_large(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
     E2EG_LAUNCH_CHECK("fill_words");
     row_stats<false, false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, deg, dinv, nullptr, classes);
     E2EG_LAUNCH_CHECK("row_stats");
-    count_top<kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, classes, w.top_totals);
+    count_top<false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, classes, w.top_totals);
     E2EG_LAUNCH_CHECK("count_top");
     number_nodes<false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, classes, w.top_totals, view, w.top);
     E2EG_LAUNCH_CHECK("number_nodes");

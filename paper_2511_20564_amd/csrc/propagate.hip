@@ -126,12 +126,13 @@ __device__ __forceinline__ void store_one<BF16>(uint16_t* p, float v) { *p = (ui
 // ---- one layer --------------------------------------------------------------------------------
 template <typename T>
 struct LayerArgs {
-    const float* dinv_sqrt;       // by node id
+    const float* dinv_sqrt;       // row scales by node id; null: `unit_scale` decides
+    int32_t unit_scale;           // no scale array: rows are scaled by 1, or else by the inverse of their length
     SchedView sched;              // internal graph (see common.h)
     const typename T::elem* zin;  // Z(l) = S H(l), [n + 1][F] in internal order, row n all zero; kFirst: H(0) by node id
     int64_t ld_in;                // leading dimension of zin in elements (F for a Z buffer)
     const int32_t* cols;          // column of every entry: zcol (rows of Z), or znode for kFirst
-    const float* vals;            // value of every entry: null (kPlain), zval (kValues), zs (kFirst)
+    const float* vals;            // value of every entry: null (kPlain), zval (kValues), zs (kFirst), null (kCaller)
     int32_t transposed;           // the call computes with the transpose of the stored operator
     int32_t stream_out;           // results leave through streaming stores (tables far larger than the caches)
     typename T::elem* out_h;      // H(l+1) by node id, or null
@@ -147,8 +148,13 @@ struct LayerArgs {
 };
 
 // What a gathered row is multiplied by: nothing (inner layers), the entry's value (inner layers of a
-// weighted graph), or s_j times that value while the rows come from the caller's H(0) (first layer).
-constexpr int kPlain = 0, kValues = 1, kFirst = 2;
+// weighted graph), s_j times that value while the rows come from the caller's H(0) (first layer), or nothing
+// while they come from the caller's X (aggregation).
+constexpr int kPlain = 0, kValues = 1, kFirst = 2, kCaller = 3;
+constexpr bool from_caller(int mode) { return mode == kFirst || mode == kCaller; }   // gathered by node id, no zero row
+
+// 1 / d of the mean aggregator, 0 for an empty row.
+__device__ __forceinline__ float inverse_length(int32_t d) { return d > 0 ? (float)(1.0 / (double)d) : 0.0f; }
 
 // The backward entry points apply the stored operator itself, which is its transpose only if structure
 // and values are symmetric; a schedule that e2eg_normalize found not to be is refused on the device,
@@ -160,8 +166,10 @@ __device__ __forceinline__ bool refused(const LayerArgs<T>& a) {
     return a.transposed && a.sched.header->flags != 0;
 }
 template <typename T>
-__device__ __forceinline__ float row_scale(const LayerArgs<T>& a, int32_t node, bool refuse) {
-    return refuse ? __builtin_nanf("") : a.dinv_sqrt[node];
+__device__ __forceinline__ float row_scale(const LayerArgs<T>& a, int32_t node, int32_t len, bool refuse) {
+    if (refuse) return __builtin_nanf("");
+    if (a.dinv_sqrt) return a.dinv_sqrt[node];
+    return a.unit_scale ? 1.0f : inverse_length(len);
 }
 
 // The node at an internal row (a small schedule keeps node order and has no array for it).
@@ -262,6 +270,13 @@ __device__ __forceinline__ uint4 gather16(const LayerArgs<T>& a, int32_t j, uint
     }
 }
 
+// What entry e's row is multiplied by.
+template <typename T, int MODE>
+__device__ __forceinline__ float entry_value(const LayerArgs<T>& a, int32_t e) {
+    if (MODE == kCaller) return 1.0f;
+    return a.vals[e];
+}
+
 constexpr int kInFlight = 8;  // independent 16-byte gathers in flight per lane
 // The column indices (and entry values) are streamed once, but they are read with ordinary loads:
 // measured, non-temporal loads for them cost 6 % (500 M-edge graph, 128-byte rows) to 9 % (2 M-edge
@@ -288,18 +303,18 @@ __device__ __forceinline__ void run_segment(const LayerArgs<T>& a, const Segment
     float s = 0.0f;
     if (seg.slot < 0) {  // requested now, needed after the gathers
         node = node_of(a, seg.row);
-        s = row_scale<T>(a, node, refuse);
+        s = row_scale<T>(a, node, seg.end - seg.beg, refuse);
     }
     // What a lane without a neighbour gathers: the all-zero row of a Z buffer; kFirst, whose table has
     // no such row: the segment's own first neighbour, with weight 0 (adds 0, and NaN only where that
     // neighbour makes the sum NaN anyway).
     int32_t idx_first = lane < seg.end - seg.beg ? *(a.cols + seg.beg + lane) : a.n;
-    const int32_t none = MODE == kFirst ? __builtin_amdgcn_readfirstlane(idx_first) : a.n;
-    if constexpr (MODE == kFirst)
+    const int32_t none = from_caller(MODE) ? __builtin_amdgcn_readfirstlane(idx_first) : a.n;
+    if constexpr (from_caller(MODE))
         if (lane >= seg.end - seg.beg) idx_first = none;
     float wgt_first = 0.0f;  // VALS: the entries' values travel with their column indices
     if constexpr (VALS)
-        if (lane < seg.end - seg.beg) wgt_first = *(a.vals + seg.beg + lane);
+        if (lane < seg.end - seg.beg) wgt_first = entry_value<T, MODE>(a, seg.beg + lane);
 
     for (int cb = 0; cb < chunks; cb += G) {   // more than one pass only for rows wider than 1 KiB
         const int cc = cb + c;
@@ -315,7 +330,7 @@ __device__ __forceinline__ void run_segment(const LayerArgs<T>& a, const Segment
             float wgt_next = 0.0f;
             if (base + 64 < seg.end && lane < seg.end - base - 64) {
                 idx_next = *(a.cols + base + 64 + lane);
-                if constexpr (VALS) wgt_next = *(a.vals + base + 64 + lane);
+                if constexpr (VALS) wgt_next = entry_value<T, MODE>(a, base + 64 + lane);
             }
             int t = 0;
             for (; t + U * NB <= cnt; t += U * NB) {   // full batches: every lane has a neighbour
@@ -386,11 +401,11 @@ __device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const int3
     const int chunks = a.F / V;
     const uint32_t row_bytes = (uint32_t)a.ld_in * (uint32_t)sizeof(typename T::elem);
     int32_t none = a.n;
-    if constexpr (MODE == kFirst) {   // lane 0 of the group holds the row's first neighbour (row 0 for an empty row)
+    if constexpr (from_caller(MODE)) {   // lane 0 of the group holds the row's first neighbour (row 0 for an empty row)
         none = __shfl(idx_first, group_base);
         if (len <= 0) none = 0;
     }
-    const int32_t idx_start = (MODE == kFirst && c >= len) ? none : idx_first;
+    const int32_t idx_start = (from_caller(MODE) && c >= len) ? none : idx_first;
     int maxlen = len;  // longest row of the batch (wave-uniform)
 #pragma unroll
     for (int off = G; off < 64; off <<= 1) {
@@ -412,7 +427,7 @@ __device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const int3
             float wgt_next = 0.0f;
             if (base + G + c < len) {
                 idx_next = *(a.cols + beg + base + G + c);
-                if constexpr (VALS) wgt_next = *(a.vals + beg + base + G + c);
+                if constexpr (VALS) wgt_next = entry_value<T, MODE>(a, beg + base + G + c);
             }
             const int steps = maxlen - base < G ? maxlen - base : G;
             for (int t = 0; t < steps; t += U) {
@@ -431,7 +446,7 @@ __device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const int3
             idx = idx_next;
             wgt = wgt_next;
         }
-        if constexpr (MODE == kFirst)
+        if constexpr (from_caller(MODE))
             if (len == 0) sum.clear();   // an empty row gathered row 0 with weight 0: its sum is 0 whatever row 0 holds
         if (active && len >= 0) finish_vec<T>(a, zrow, node, s, cc * V, sum.acc);
     }
@@ -493,7 +508,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
     if (n_a > a.a_blocks) n_a = a.a_blocks;   // a longer stretch than the launch was sized for: go round again
     const int64_t c_total = ((int64_t)h->n_short + kWaves * kShortPerWave - 1) / (kWaves * kShortPerWave);
     const int64_t n_b = a.b_blocks;                      // a fixed number, with equal shares of the rows
-    const int64_t n_c = (c_total + kXcds - 1 - x) / kXcds;
+    const int64_t n_c = (c_total + kXcds - 1) / kXcds;
     const int64_t total = n_a + n_b + n_c;
     if (j >= total) return;
     if (j < n_a) {
@@ -513,10 +528,14 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
         for (int64_t t = first; t < last; ++t) run_segment<T, LOG_G, NARROW, MODE>(a, a.sched.singles[t], lane, refuse);
         return;
     }
+    // The rows are sorted by length in blocks of a whole number of octets of workgroups, so the longest rows of
+    // every block would fall to the same XCD; each octet is dealt out from another XCD on.
+    const int64_t octet = o - n_b;
+    int64_t rb = octet * kXcds + ((x + octet + (octet >> 2) + (octet >> 4)) & (kXcds - 1));
+    if (rb >= c_total) return;
     // a small schedule lists users before items: from its end, the long item rows come first and the short
     // user rows fill the gaps (in node order the launch ended with a tail: 62 against 43 us on a sampled
     // subgraph of 175 k nodes)
-    int64_t rb = (o - n_b) * kXcds + x;
     if (!a.sched.orig) rb = c_total - 1 - rb;
     const int64_t n_short = a.sched.header->n_short;
     const int64_t first = (rb * kWaves + wave) * kShortPerWave;
@@ -529,16 +548,16 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
         my_beg = a.sched.zrow_ptr[my_row];
         my_len = a.sched.zrow_ptr[my_row + 1] - my_beg;
         my_node = node_of(a, my_row);
-        my_s = row_scale<T>(a, my_node, refuse);
+        my_s = row_scale<T>(a, my_node, my_len, refuse);
     }
     const int c = lane & (G - 1);
     const int g = lane >> LOG_G;
-    const int32_t none = MODE == kFirst ? 0 : a.n;
+    const int32_t none = from_caller(MODE) ? 0 : a.n;
     int32_t beg = __shfl(my_beg, g), len = __shfl(my_len, g);
     int32_t idx_cur = c < len ? *(a.cols + beg + c) : none;
     float wgt_cur = 0.0f;
     if constexpr (VALS)
-        if (c < len) wgt_cur = *(a.vals + beg + c);
+        if (c < len) wgt_cur = entry_value<T, MODE>(a, beg + c);
 #pragma unroll 1
     for (int r0 = 0; r0 < n_rows; r0 += NB) {
         const int src = r0 + g;      // the row of this lane's group (lanes >= n_rows hold len -1)
@@ -548,7 +567,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
         const int32_t idx_nxt = c < nlen ? *(a.cols + nbeg + c) : none;
         float wgt_nxt = 0.0f;
         if constexpr (VALS)
-            if (c < nlen) wgt_nxt = *(a.vals + nbeg + c);
+            if (c < nlen) wgt_nxt = entry_value<T, MODE>(a, nbeg + c);
         run_short_rows<T, LOG_G, NARROW, MODE>(a, beg, len, __shfl(my_row, src), __shfl(my_node, src),
                                                    __shfl(my_s, src), idx_cur, wgt_cur, lane);
         beg = nbeg;
@@ -576,7 +595,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_split_rows(const LayerA
     const int32_t node = node_of(a, k);
     const int32_t base = a.sched.slot_base[m];
     const int32_t cnt = a.sched.slot_cnt[m];
-    const float s = row_scale<T>(a, node, refuse);
+    const float s = row_scale<T>(a, node, a.dinv_sqrt ? 0 : a.sched.zrow_ptr[k + 1] - a.sched.zrow_ptr[k], refuse);
     const int quads = a.F / 4;
     for (int q0 = 0; q0 < quads; q0 += kThreads) {
         const int width = quads - q0 < kThreads ? quads - q0 : kThreads;
@@ -621,15 +640,16 @@ constexpr int64_t kDirectMaxNnz = kSmallNnz;   // see run_layers
 constexpr int kPrescaleRows = 4;   // rows per thread: their dependent loads (row -> node -> x, s) overlap
 
 // Z = S_in X in internal row order: one streaming pass, 16 bytes of kPrescaleRows rows per thread.
-// Also clears the zero row (index n) of the Z buffer (of both, if z_other is given).  Used for Z(0) of a
-// multi-layer propagation (see run_layers) and by e2eg_aggregate, whose input scales depend on the mode.
+// Also clears the zero row (index n) of the Z buffer.  Used for Z(0) of a multi-layer propagation (see
+// run_layers) and by e2eg_aggregate where the mode scales the rows that go in; without a scale array, by the inverse of their
+// length in the caller's CSR.
 template <typename T>
 __global__ __launch_bounds__(kPrescaleThreads) void prescale_rows(const typename T::elem* __restrict__ x,
                                                                    int64_t ldx,
                                                                    const float* __restrict__ dinv_sqrt,
+                                                                   const int32_t* __restrict__ row_ptr,
                                                                    const int32_t* __restrict__ orig,
                                                                    typename T::elem* __restrict__ z,
-                                                                   typename T::elem* __restrict__ z_other,
                                                                    int64_t n, int32_t F, bool stream) {
     constexpr int V = T::kVec;
     const int chunks = F / V;
@@ -653,7 +673,7 @@ __global__ __launch_bounds__(kPrescaleThreads) void prescale_rows(const typename
         for (int k = 0; k < V; ++k) v[i][k] = 0.0f;
         if (node[i] >= 0) {
             load_vec<T>(x + node[i] * ldx + col, v[i]);
-            s[i] = dinv_sqrt[node[i]];
+            s[i] = dinv_sqrt ? dinv_sqrt[node[i]] : inverse_length(row_ptr[node[i] + 1] - row_ptr[node[i]]);
         }
     }
 #pragma unroll
@@ -663,7 +683,6 @@ __global__ __launch_bounds__(kPrescaleThreads) void prescale_rows(const typename
 #pragma unroll
         for (int k = 0; k < V; ++k) v[i][k] *= s[i];   // the zero row: 0 * 0
         store_vec<T>(z + zrow * F + col, v[i], stream);
-        if (zrow == n && z_other) store_vec<T>(z_other + zrow * F + col, v[i], stream);
     }
 }
 
@@ -686,7 +705,8 @@ constexpr uint64_t kStreamOutBytes = 64ull << 20;
 inline bool streams_out(uint64_t table_bytes) { return table_bytes > kStreamOutBytes; }
 
 // `mode`: kPlain / kValues for a layer that reads a Z buffer (a.cols = zcol, a.vals = null / zval),
-// kFirst for one that reads the caller's rows (a.cols = znode, a.vals = zs, a.ld_in = their leading dimension).
+// kFirst / kCaller for one that reads the caller's rows (a.cols = znode, a.vals = zs / null, a.ld_in = their
+// leading dimension).
 template <typename T>
 int32_t launch_layer(LayerArgs<T>& a, int mode, int64_t n, int64_t nnz, hipStream_t stream) {
     const int chunks = a.F / T::kVec;
@@ -712,6 +732,9 @@ int32_t launch_layer(LayerArgs<T>& a, int mode, int64_t n, int64_t nnz, hipStrea
     if (mode == kFirst) {
         if (narrow) launch_spmm<T, true, kFirst>(log_g, grid, a, stream);
         else launch_spmm<T, false, kFirst>(log_g, grid, a, stream);
+    } else if (mode == kCaller) {
+        if (narrow) launch_spmm<T, true, kCaller>(log_g, grid, a, stream);
+        else launch_spmm<T, false, kCaller>(log_g, grid, a, stream);
     } else if (mode == kValues) {
         if (narrow) launch_spmm<T, true, kValues>(log_g, grid, a, stream);
         else launch_spmm<T, false, kValues>(log_g, grid, a, stream);
@@ -800,8 +823,8 @@ int32_t run_layers(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t
     if (!direct) {
         const int chunks = F / T::kVec;
         prescale_rows<T><<<dim3((unsigned)ceil_div(ceil_div((int64_t)n + 1, kPrescaleRows) * chunks, kPrescaleThreads)),
-                           dim3(kPrescaleThreads), 0, stream>>>(static_cast<const E*>(in), ld_in, dinv, view.orig,
-                                                                z_bufs[0], nullptr, n, F,
+                           dim3(kPrescaleThreads), 0, stream>>>(static_cast<const E*>(in), ld_in, dinv, row_ptr, view.orig,
+                                                                z_bufs[0], n, F,
                                                                 streams_out((uint64_t)(n + 1) * F * sizeof(E)));
         E2EG_LAUNCH_CHECK("prescale_rows");
         cur = 0;
@@ -809,6 +832,7 @@ int32_t run_layers(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t
     for (int32_t l = 1; l <= K; ++l) {
         LayerArgs<T> a;
         a.dinv_sqrt = dinv;
+        a.unit_scale = 0;
         a.sched = view;
         a.transposed = transposed ? 1 : 0;
         int mode;
@@ -840,27 +864,18 @@ int32_t run_layers(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t
     return E2EG_OK;
 }
 
-// Per-node input and output scales of e2eg_aggregate, from the row lengths of the caller's CSR.
-__global__ void aggregate_scales(const int32_t* __restrict__ row_ptr, int64_t n, int32_t mode,
-                                 float* __restrict__ scale_in, float* __restrict__ scale_out) {
+// The scales of e2eg_aggregate's symmetric mode, d^-1/2 of the row lengths of the caller's CSR.
+__global__ void symmetric_scales(const int32_t* __restrict__ row_ptr, int64_t n, float* __restrict__ scale) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t d = row_ptr[i + 1] - row_ptr[i];
-    const float inv = d > 0 ? (float)(1.0 / (double)d) : 0.0f;
-    const float rs = d > 0 ? (float)(1.0 / sqrt((double)d)) : 0.0f;
-    float in = 1.0f, out = 1.0f;
-    if (mode == E2EG_AGG_SYM) in = out = rs;
-    else if (mode == E2EG_AGG_MEAN) out = inv;
-    else if (mode == E2EG_AGG_MEAN_T) in = inv;
-    scale_in[i] = in;
-    scale_out[i] = out;
+    scale[i] = d > 0 ? (float)(1.0 / sqrt((double)d)) : 0.0f;
 }
 
 struct AggWs {
     void* z;
     float* partial;
-    float* scale_in;
-    float* scale_out;
+    float* scale;
     size_t bytes;
 };
 
@@ -870,8 +885,7 @@ AggWs carve_agg(void* base, int64_t n, int64_t nnz, int32_t dtype, int32_t F) {
     const size_t esz = dtype == E2EG_F32 ? 4 : 2;
     w.z = c.take<char>((size_t)(n + 1) * (size_t)F * esz);
     w.partial = c.take<float>((size_t)sched_max_slot(n, nnz) * (size_t)F);
-    w.scale_in = c.take<float>(n > 0 ? n : 1);
-    w.scale_out = c.take<float>(n > 0 ? n : 1);
+    w.scale = c.take<float>(n > 0 ? n : 1);
     w.bytes = c.size();
     return w;
 }
@@ -883,21 +897,29 @@ int32_t run_aggregate(int32_t mode, int32_t n, int64_t nnz, const int32_t* row_p
     using E = typename T::elem;
     SchedView view;
     sched_carve(const_cast<void*>(sched), n, nnz, &view, false, row_ptr);
-    aggregate_scales<<<dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, stream>>>(row_ptr, n, mode, w.scale_in,
-                                                                                w.scale_out);
-    E2EG_LAUNCH_CHECK("aggregate_scales");
-    const int chunks = F / T::kVec;
-    prescale_rows<T><<<dim3((unsigned)ceil_div(ceil_div((int64_t)n + 1, kPrescaleRows) * chunks, kPrescaleThreads)),
-                       dim3(kPrescaleThreads), 0, stream>>>(static_cast<const E*>(x), ldx, w.scale_in, view.orig,
-                                                            static_cast<E*>(w.z), nullptr, n, F,
-                                                            streams_out((uint64_t)(n + 1) * F * sizeof(E)));
-    E2EG_LAUNCH_CHECK("prescale_rows");
+    // The modes that do not scale what goes in gather the caller's rows themselves; the others gather a table
+    // pre-scaled by a streaming pass.  Row scales that follow from the length are formed in the kernels.
+    const bool direct = mode == E2EG_AGG_MEAN || mode == E2EG_AGG_SUM;
+    const bool symmetric = mode == E2EG_AGG_SYM;
+    if (symmetric) {
+        symmetric_scales<<<dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, stream>>>(row_ptr, n, w.scale);
+        E2EG_LAUNCH_CHECK("symmetric_scales");
+    }
+    if (!direct) {
+        const int chunks = F / T::kVec;
+        prescale_rows<T><<<dim3((unsigned)ceil_div(ceil_div((int64_t)n + 1, kPrescaleRows) * chunks, kPrescaleThreads)),
+                           dim3(kPrescaleThreads), 0, stream>>>(static_cast<const E*>(x), ldx, symmetric ? w.scale : nullptr,
+                                                                row_ptr, view.orig, static_cast<E*>(w.z), n, F,
+                                                                streams_out((uint64_t)(n + 1) * F * sizeof(E)));
+        E2EG_LAUNCH_CHECK("prescale_rows");
+    }
     LayerArgs<T> a;
-    a.dinv_sqrt = w.scale_out;
+    a.dinv_sqrt = symmetric ? w.scale : nullptr;
+    a.unit_scale = mode == E2EG_AGG_MEAN ? 0 : 1;
     a.sched = view;
-    a.zin = static_cast<const E*>(w.z);
-    a.ld_in = F;
-    a.cols = view.zcol;
+    a.zin = direct ? static_cast<const E*>(x) : static_cast<const E*>(w.z);
+    a.ld_in = direct ? ldx : F;
+    a.cols = direct ? view.znode : view.zcol;
     a.vals = nullptr;
     a.transposed = mode == E2EG_AGG_MEAN_T ? 1 : 0;
     a.out_h = static_cast<E*>(y);
@@ -907,7 +929,7 @@ int32_t run_aggregate(int32_t mode, int32_t n, int64_t nnz, const int32_t* row_p
     a.ld_add = ld_add;
     a.partial = w.partial;
     a.F = F;
-    return launch_layer<T>(a, kPlain, n, nnz, stream);
+    return launch_layer<T>(a, direct ? kCaller : kPlain, n, nnz, stream);
 }
 
 constexpr int kMaxLayers = 64;

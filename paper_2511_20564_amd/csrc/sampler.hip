@@ -11,14 +11,16 @@
 //   * a draw is one thread: 64 random bits from the counter-based generator Philox4x32-10 (Salmon,
 //     Moraes, Dror, Shaw, SC 2011; counter = (draw, node, hop, 0), key = the seed), scaled to the
 //     row total by a 64x64->128-bit multiply, then a search in the row's slice of the table.
-//   * the nodes reached at each hop are a bitmap (set by integer OR); frontiers, the node list and the edge
-//     list are compacted with prefix sums, so their order is ascending node id / draw order and does not
-//     depend on scheduling.  A node's local id is its rank in the union of the bitmaps.
+//   * the nodes reached at each hop are marked with plain byte stores (all writers write the same value);
+//     bitmaps are made of the marks, and frontiers, the node list and the edge list are compacted with prefix
+//     sums, so their order is ascending node id / draw order and does not depend on scheduling.  A node's local
+//     id is its rank in the bitmap of all nodes.
 //   * launch sizes come from upper bounds (seeds x fan-outs); the real frontier sizes stay on the
 //     device.  The one wait is at the end, for the three counts handed to the host.
 // A two-hop sample is bound by the number of launches and by the latency of the draws' dependent reads.
-// 4096 seeds, fan-outs 25 and 10, graph of 1.5 M nodes: 23 launches and 178 us with one mark per node and
-// scans over all of them; eight launches now.
+// 4096 seeds, fan-outs 25 and 10, graph of 1.5 M nodes: 23 launches and 178 us with flags and scans over all
+// nodes for every hop; 11 launches now.  (Marking by atomic OR into the bitmaps themselves: the 280 k draws
+// of the second hop meet on 190 KB of them and took 52 us.)
 #include "common.h"
 
 namespace e2eg {
@@ -119,35 +121,38 @@ __global__ void fill_i32(int32_t* __restrict__ p, int64_t count, int32_t v) {
     if (i < count) p[i] = v;
 }
 
-// ---- node sets -----------------------------------------------------------------------------------------
-// levels[h] (words 64-bit words each): h = 0 the seeds, h > 0 the nodes picked at hop h - 1, whether or not
-// they were reached before.
-constexpr int kSetThreads = 1024;   // one word a thread
-constexpr int64_t kSetFew = 64;     // up to this many tiles of words a workgroup counts what is before its own
+__global__ void zero16(uint4* __restrict__ p, int64_t count) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
 
-struct Levels {
-    uint64_t* bits;
-    int64_t words;
-    // the nodes first reached at level h
-    __device__ __forceinline__ uint64_t fresh(int h, int64_t w) const {
-        uint64_t v = bits[h * words + w];
-        for (int k = 0; k < h; ++k) v &= ~bits[k * words + w];
-        return v;
-    }
-    // all nodes of levels 0 .. h
-    __device__ __forceinline__ uint64_t all(int h, int64_t w) const {
-        uint64_t v = bits[w];
-        for (int k = 1; k <= h; ++k) v |= bits[k * words + w];
-        return v;
-    }
-    __device__ __forceinline__ void add(int h, int32_t v) const {
-        uint64_t* word = bits + h * words + (v >> 6);
-        const uint64_t bit = 1ull << (v & 63);
-        if (!(*word & bit)) atomicOr(reinterpret_cast<unsigned long long*>(word), (unsigned long long)bit);
+// ---- node sets -----------------------------------------------------------------------------------------
+// marks[h * stride + v]: h = 0 the seeds, h > 0 the nodes picked at hop h - 1, whether or not they were reached
+// before.
+constexpr int kSetThreads = 1024;   // one 64-node word a thread
+constexpr int64_t kSetFew = 4096;   // up to this many tiles of words a workgroup adds up the counts before its own
+
+struct Marks {
+    uint8_t* marks;
+    int64_t stride;
+    __device__ __forceinline__ void add(int h, int32_t v) const { marks[h * stride + v] = 1; }
+    // level h of word w as bits
+    __device__ __forceinline__ uint64_t word(int h, int64_t w) const {
+        const uint4* p = reinterpret_cast<const uint4*>(marks + h * stride + w * 64);
+        uint64_t bits = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 v = p[q];
+            // four 0/1 bytes -> four bits: the products land on bits 24 .. 27 without carries
+            const uint32_t b = ((v.x * 0x01020408u) >> 24 & 15u) | ((v.y * 0x01020408u) >> 24 & 15u) << 4 |
+                               ((v.z * 0x01020408u) >> 24 & 15u) << 8 | ((v.w * 0x01020408u) >> 24 & 15u) << 12;
+            bits |= (uint64_t)b << (16 * q);
+        }
+        return bits;
     }
 };
 
-__global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, int32_t n, Levels levels,
+__global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, int32_t n, Marks marks,
                            int32_t* __restrict__ bad) {
     const int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n_seeds) return;
@@ -156,51 +161,62 @@ __global__ void mark_seeds(const int32_t* __restrict__ seeds, int32_t n_seeds, i
         atomicOr(bad, 1);
         return;
     }
-    levels.add(0, v);
+    marks.add(0, v);
 }
 
-template <typename V>
-__device__ __forceinline__ V sum_block(V v, V* lds) {   // over kSetThreads threads, in every thread
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    V t = 0;
-#pragma unroll
-    for (int w = 0; w < kSetThreads / 64; ++w) t += lds[w];
-    return t;
-}
-
-// Nodes per tile of words (large node counts only).
-__global__ __launch_bounds__(kSetThreads) void count_set(Levels levels, int level, bool all, int32_t* __restrict__ tile_cnt) {
+// The nodes first reached at `level`, or (ALL) those of levels 0 .. level, as a bitmap; and their number per tile.
+template <bool ALL>
+__global__ __launch_bounds__(kSetThreads) void make_set(Marks marks, int level, int64_t words, uint64_t* __restrict__ set,
+                                                        int32_t* __restrict__ tile_cnt) {
     __shared__ int32_t lds[kSetThreads / 64];
     const int64_t w = (int64_t)blockIdx.x * kSetThreads + threadIdx.x;
-    const int32_t c = w < levels.words ? __popcll(all ? levels.all(level, w) : levels.fresh(level, w)) : 0;
-    const int32_t t = sum_block(c, lds);
-    if (threadIdx.x == 0) tile_cnt[blockIdx.x] = t;
+    uint64_t v = 0;
+    if (w < words) {
+        v = marks.word(level, w);
+        for (int k = 0; k < level; ++k) {
+            const uint64_t o = marks.word(k, w);
+            v = ALL ? v | o : v & ~o;
+        }
+        set[w] = v;
+    }
+    int32_t c = __popcll(v);
+    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+        for (int k = 0; k < kSetThreads / 64; ++k) t += lds[k];
+        tile_cnt[blockIdx.x] = t;
+    }
 }
 
-// The set as an ascending list, and its size in *total.  RANKS (the set of all nodes): rank[w] = nodes before
-// word w, for words + 1 words, and `boundary` is the rank of node n_users.  COUNTED: tile_cnt holds the number of nodes
-// before each tile, else it is counted here.
-template <bool RANKS, bool COUNTED>
-__global__ __launch_bounds__(kSetThreads) void list_set(Levels levels, int level, const int32_t* __restrict__ tile_cnt,
-                                                        int32_t* __restrict__ out, int64_t capacity,
-                                                        int32_t* __restrict__ total, int32_t* __restrict__ rank,
-                                                        uint64_t* __restrict__ set, int32_t n_users,
+// The set as an ascending list, and its size in *total.  rank (may be null): nodes before every word, and
+// *boundary = the rank of node n_users.  SCANNED: tile_cnt holds the number of nodes before each tile, else the tiles' own.
+template <bool SCANNED>
+__global__ __launch_bounds__(kSetThreads) void list_set(const uint64_t* __restrict__ set, int64_t words,
+                                                        const int32_t* __restrict__ tile_cnt, int32_t* __restrict__ out,
+                                                        int64_t capacity, int32_t* __restrict__ total,
+                                                        int32_t* __restrict__ rank, int32_t n_users,
                                                         int32_t* __restrict__ boundary) {
-    __shared__ int32_t lds[kSetThreads / 64];
+    constexpr int kWaves = kSetThreads / 64;
+    __shared__ int32_t lds[kWaves];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    auto word = [&](int64_t w) { return RANKS ? levels.all(level, w) : levels.fresh(level, w); };
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int64_t w = (int64_t)blockIdx.x * kSetThreads + threadIdx.x;
-    uint64_t bits = w < levels.words ? word(w) : 0ull;
-    int32_t before = 0;
-    if (COUNTED) {
-        before = tile_cnt[blockIdx.x];
+    const uint64_t bits = w < words ? set[w] : 0ull;
+    int32_t at = 0;
+    if (SCANNED) {
+        at = tile_cnt[blockIdx.x];
     } else {
 #pragma unroll 4
-        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x * kSetThreads; t += kSetThreads) before += __popcll(word(t));
-        before = sum_block(before, lds);
+        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += kSetThreads) at += tile_cnt[t];
+        for (int off = 32; off > 0; off >>= 1) at += __shfl_xor(at, off);
+        if (lane == 0) lds[wave] = at;
+        __syncthreads();
+        at = 0;
+#pragma unroll
+        for (int k = 0; k < kWaves; ++k) at += lds[k];
+        __syncthreads();
     }
     const int32_t c = __popcll(bits);
     int32_t inc = c;
@@ -209,25 +225,28 @@ __global__ __launch_bounds__(kSetThreads) void list_set(Levels levels, int level
         const int32_t t = __shfl_up(inc, d, 64);
         if (lane >= d) inc += t;
     }
-    __syncthreads();
     if (lane == 63) lds[wave] = inc;
     __syncthreads();
-    int32_t at = before + inc - c;
+    at += inc - c;
 #pragma unroll
-    for (int v = 0; v < kSetThreads / 64; ++v)
-        if (v < wave) at += lds[v];
-    if (w >= levels.words) return;
-    if (RANKS) {
-        rank[w] = at;
-        set[w] = bits;
-        if (w == n_users >> 6) *boundary = at + __popcll(bits & ((1ull << (n_users & 63)) - 1));
+    for (int k = 0; k < kWaves; ++k)
+        if (k < wave) at += lds[k];
+    if (w < words) {
+        if (rank) {
+            rank[w] = at;
+            if (w == n_users >> 6) *boundary = at + __popcll(bits & ((1ull << (n_users & 63)) - 1));
+        }
+        if (w == words - 1) *total = at + c;
     }
-    if (w == levels.words - 1) *total = at + c;
-    while (bits) {
-        const int b = __ffsll((unsigned long long)bits) - 1;
-        if (at < capacity) out[at] = (int32_t)(w * 64 + b);
-        ++at;
-        bits &= bits - 1;
+    // a word at a time, a lane per node, so that ids leave side by side
+    uint64_t some = __ballot(c > 0);
+    const int32_t word0 = (int32_t)((int64_t)blockIdx.x * kSetThreads + wave * 64);
+    while (some) {
+        const int k = __ffsll((unsigned long long)some) - 1;
+        some &= some - 1;
+        const uint64_t v = __shfl((unsigned long long)bits, k);
+        const int32_t pos = __shfl(at, k) + __popcll(v & lt_mask);
+        if (((v >> lane) & 1) && pos < capacity) out[pos] = (word0 + k) * 64 + lane;
     }
 }
 
@@ -282,7 +301,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_picks(const int32_t* __rest
                                                            const uint64_t* __restrict__ cum,
                                                            const int32_t* __restrict__ frontier,
                                                            const int32_t* __restrict__ front_count, int32_t k, int32_t hop,
-                                                           uint32_t seed_lo, uint32_t seed_hi, Levels levels,
+                                                           uint32_t seed_lo, uint32_t seed_hi, Marks marks,
                                                            int32_t* __restrict__ slot_src, int32_t* __restrict__ slot_dst,
                                                            int32_t* __restrict__ slot_ent, int32_t* __restrict__ tile_cnt) {
     __shared__ int32_t picks;
@@ -332,7 +351,7 @@ __global__ __launch_bounds__(kDrawThreads) void draw_picks(const int32_t* __rest
         }
         if (ent >= 0) {
             v = col_idx[ent];
-            levels.add(hop + 1, v);
+            marks.add(hop + 1, v);
         }
     }
     slot_src[s] = u;
@@ -433,10 +452,10 @@ int32_t check_plan(const char* who, int32_t n, int32_t n_seeds, int32_t L, const
 
 struct SampleWs {
     int32_t* small;     // [64]: [0] local users, [1] nodes, [2] edges, [3] bad; [8 ..] frontier sizes
-    uint64_t* bits;     // [L + 1][words], behind `small` so that one launch clears both
+    uint8_t* marks;     // [L + 1][64 * words], behind `small` so that one launch clears both
     int64_t words;
     int64_t zero_count; // in int32
-    uint64_t* set;      // [words] all nodes
+    uint64_t* set;      // [words] the set in hand, in the end all nodes
     int32_t* rank;      // [words]
     int32_t* frontier;  // [max cap_front]
     int32_t* slot_src;  // [slot tiles * kDrawThreads]
@@ -463,10 +482,10 @@ SampleWs carve_sample(void* base, int64_t n, int32_t L, int64_t max_front, int64
     Carver c(base);
     SampleWs w;
     w.words = n / 64 + 1;   // one bit past the last node, whose rank is asked for
-    char* zeroed = c.take<char>(64 * sizeof(int32_t) + (size_t)(L + 1) * (size_t)w.words * sizeof(uint64_t));
+    char* zeroed = c.take<char>(64 * sizeof(int32_t) + (size_t)(L + 1) * (size_t)w.words * 64);
     w.small = reinterpret_cast<int32_t*>(zeroed);
-    w.bits = zeroed ? reinterpret_cast<uint64_t*>(zeroed + 64 * sizeof(int32_t)) : nullptr;
-    w.zero_count = 64 + 2 * (int64_t)(L + 1) * w.words;
+    w.marks = zeroed ? reinterpret_cast<uint8_t*>(zeroed + 64 * sizeof(int32_t)) : nullptr;
+    w.zero_count = 64 + 16 * (int64_t)(L + 1) * w.words;
     w.set = c.take<uint64_t>(w.words);
     w.rank = c.take<int32_t>(w.words);
     w.frontier = c.take<int32_t>(max_front > 0 ? max_front : 1);
@@ -482,25 +501,21 @@ SampleWs carve_sample(void* base, int64_t n, int32_t L, int64_t max_front, int64
     return w;
 }
 
-// The nodes of one level (or of all levels up to it: `ranks`) as a list.
-int32_t run_list(const SampleWs& w, const Levels& levels, int level, bool ranks, int32_t* out, int64_t capacity, int32_t* total,
+// The nodes of one level (or of all levels up to it: `all`, with their ranks) as a list.
+int32_t run_list(const SampleWs& w, const Marks& marks, int level, bool all, int32_t* out, int64_t capacity, int32_t* total,
                  int32_t n_users, hipStream_t stream) {
-    const int64_t tiles = ceil_div(levels.words, kSetThreads);
+    const int64_t tiles = ceil_div(w.words, kSetThreads);
     const dim3 grid((unsigned)tiles), blk(kSetThreads);
-    const bool counted = tiles > kSetFew;
-    if (counted) {
-        count_set<<<grid, blk, 0, stream>>>(levels, level, ranks, w.set_cnt);
-        E2EG_LAUNCH_CHECK("count_set");
+    if (all) make_set<true><<<grid, blk, 0, stream>>>(marks, level, w.words, w.set, w.set_cnt);
+    else make_set<false><<<grid, blk, 0, stream>>>(marks, level, w.words, w.set, w.set_cnt);
+    E2EG_LAUNCH_CHECK("make_set");
+    int32_t* rank = all ? w.rank : nullptr;
+    if (tiles > kSetFew) {
         E2EG_HIP_TRY(exclusive_scan_i32(w.set_cnt, w.set_cnt, tiles, nullptr, w.scan_ws, stream));
+        list_set<true><<<grid, blk, 0, stream>>>(w.set, w.words, w.set_cnt, out, capacity, total, rank, n_users, w.small);
+    } else {
+        list_set<false><<<grid, blk, 0, stream>>>(w.set, w.words, w.set_cnt, out, capacity, total, rank, n_users, w.small);
     }
-    if (ranks && counted)
-        list_set<true, true><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
-    else if (ranks)
-        list_set<true, false><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
-    else if (counted)
-        list_set<false, true><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
-    else
-        list_set<false, false><<<grid, blk, 0, stream>>>(levels, level, w.set_cnt, out, capacity, total, w.rank, w.set, n_users, w.small);
     E2EG_LAUNCH_CHECK("list_set");
     return E2EG_OK;
 }
@@ -623,23 +638,23 @@ extern "C" int32_t e2eg_sample_subgraph(int32_t n_users, int32_t n, int64_t nnz,
     const SampleWs w = carve_sample(ws, n, L, max_front, tiles);
     const uint64_t* cum = static_cast<const uint64_t*>(d_table);
     const dim3 blk(kThreads);
-    const Levels levels{w.bits, w.words};
-    fill_i32<<<grid_for(w.zero_count), blk, 0, stream>>>(w.small, w.zero_count, 0);
-    E2EG_LAUNCH_CHECK("fill_i32");
-    mark_seeds<<<grid_for(n_seeds), blk, 0, stream>>>(d_seeds, n_seeds, n, levels, w.small + 3);
+    const Marks marks{w.marks, w.words * 64};
+    zero16<<<grid_for(w.zero_count / 4), blk, 0, stream>>>(reinterpret_cast<uint4*>(w.small), w.zero_count / 4);
+    E2EG_LAUNCH_CHECK("zero16");
+    mark_seeds<<<grid_for(n_seeds), blk, 0, stream>>>(d_seeds, n_seeds, n, marks, w.small + 3);
     E2EG_LAUNCH_CHECK("mark_seeds");
     for (int32_t h = 0; h < L; ++h) {
         // the frontier of hop h, ascending: nodes first reached at level h
         int32_t* size = w.small + 8 + h;
-        if ((st = run_list(w, levels, h, false, w.frontier, cap_front[h], size, n_users, stream)) != E2EG_OK) return st;
+        if ((st = run_list(w, marks, h, false, w.frontier, cap_front[h], size, n_users, stream)) != E2EG_OK) return st;
         const int64_t at = tile_base[h] * kDrawThreads;
         draw_picks<<<dim3((unsigned)ceil_div(cap_front[h] * h_fanout[h], kDrawThreads)), dim3(kDrawThreads), 0, stream>>>(
-            d_row_ptr, d_col_idx, cum, w.frontier, size, h_fanout[h], h, (uint32_t)seed, (uint32_t)(seed >> 32), levels,
+            d_row_ptr, d_col_idx, cum, w.frontier, size, h_fanout[h], h, (uint32_t)seed, (uint32_t)(seed >> 32), marks,
             w.slot_src + at, w.slot_dst + at, w.slot_ent + at, w.tile_cnt + tile_base[h]);
         E2EG_LAUNCH_CHECK("draw_picks");
     }
     // local numbering: all nodes in ascending order (users first, as in the parent)
-    if ((st = run_list(w, levels, L, true, d_nodes, node_capacity, w.small + 1, n_users, stream)) != E2EG_OK) return st;
+    if ((st = run_list(w, marks, L, true, d_nodes, node_capacity, w.small + 1, n_users, stream)) != E2EG_OK) return st;
     // the picks, without the empty slots, in slot order
     const dim3 edge_grid((unsigned)tiles), edge_blk(kDrawThreads);
     const Ranks ranks{w.set, w.rank};
