@@ -7,10 +7,9 @@
 // row / column).  The products are computed transposed, D[out column][row], so that a lane ends
 // up holding runs of 4 consecutive output columns of ONE row and can store them as 8 bytes.
 //   forward : H  = relu(P W)        rows = nodes, k = Fin,  weight tile W^T staged in LDS
-//   dP      : dP = dZ W^T           rows = nodes, k = Fout, weight tile W staged in LDS,
-//             dZ = gH * [H > 0] formed while loading
-//   dW      : dW = P^T dZ           k = nodes: each workgroup reduces a block of nodes into an
-//             fp32 partial [Fin][Fout]; partials are added in block order by a second kernel
+//   backward: dP = dZ W^T, dW = P^T dZ with dZ = gH * [H > 0], in one kernel that reads gH, H and P once:
+//             rows = nodes, k = Fout for dP; k = nodes for dW, each workgroup adding up its share of the
+//             nodes into an fp32 partial [Fin][Fout]; partials are added in block order by a second kernel
 //             (no atomics, reproducible).
 #include "common.h"
 
@@ -19,26 +18,9 @@
 namespace e2eg {
 namespace {
 
-constexpr int kDenseWaves = 8;               // wavefronts per workgroup of dense_rows (4 where a row has more than 8 k-steps
-                                             // and a wavefront needs more than 256 registers): they share one weight tile
-constexpr int kDenseDepth = 1;               // tiles a wavefront of dense_rows requests ahead (2 measured slower: 25.4 against
-                                             // 23.3 us at 200 k rows, 408 against 392 us at 4 M)
-constexpr int kGradWaves = 8;                // wavefronts per workgroup of weight_grad_partial
-constexpr int kGradThreads = 64 * kGradWaves;
 constexpr int kReduceThreads = 256;
 constexpr int kMaxF = 256;
-constexpr int kDenseMaxGroups = 256;         // workgroups of 8 wavefronts of dense_rows per column group: their registers
-                                             // allow one per compute unit
 constexpr int kPad = 8;                      // LDS row padding (elements) against bank conflicts
-constexpr int kWeightLds = 128 * (128 + kPad);  // elements; also fits 64 x (256 + kPad)
-constexpr int kOutLd = 128 + kPad;           // pitch of a wavefront's result rows in LDS (at most 128 columns per workgroup)
-constexpr int kTileRows = 128;               // node rows per step of the dW kernel
-constexpr int kPairPasses = kTileRows / 64;  // a thread stages one pair of rows of every 32 pairs ...
-constexpr int kChunkLanes = kGradThreads / 32;        // ... and one 8-column chunk of every kChunkLanes
-constexpr int kChunkReps = 16 / kChunkLanes;          // (a 128-column tile has 16 chunks)
-constexpr int kGradOSplit = kGradWaves / 4;  // wavefronts that share a 32-column block of P split the dZ columns
-constexpr int kGradOBlocks = 4 / kGradOSplit;
-constexpr int kTileLd = kTileRows + 8;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -69,303 +51,335 @@ __device__ __forceinline__ uint4 mask_vec(uint4 g, uint4 h) {
     return make_uint4(mask_pair(g.x, h.x), mask_pair(g.y, h.y), mask_pair(g.z, h.z), mask_pair(g.w, h.w));
 }
 
-// out[r][c] = act( sum_k A[r][k] * B(c, k) ),  A = rows of `a_rows` (masked by `mask_rows` > 0
-// when MASKED), B(c, k) = TRANS_W ? w[k][c] : w[c][k].
-// grid.x: workgroups that each take `tiles` blocks of 32 WAVES rows, block b + t * gridDim.x in
-// turn t, so that at any moment the workgroups in flight read and write one moving stretch of the
-// tables (the weight tile is staged once per workgroup and serves all its turns); grid.y: groups of
-// `ngroup` output columns.
-// KS: the most k-steps of 16 a row can have (8 for up to 128 input columns).  A wavefront requests
-// the rows of its next kDenseDepth tiles before it multiplies the current one, so that the loads
-// overlap the staging of the weights, the product and the stores.
-// EXACT: kdim == 16 * KS and every workgroup has 128 output columns, so that the loops over
-// k-steps and column blocks have constant bounds and compile to straight-line code.
-template <bool MASKED, bool TRANS_W, bool RELU, int KS, bool EXACT, int WAVES>
-__global__ __launch_bounds__(64 * WAVES) void dense_rows(const uint16_t* __restrict__ a_rows,
-                                                       const uint16_t* __restrict__ mask_rows,
-                                                       const uint16_t* __restrict__ w,
-                                                       uint16_t* __restrict__ out, int32_t n,
-                                                       int32_t kdim, int32_t ndim, int32_t w_ld,
-                                                       int32_t ngroup, int32_t tiles, int32_t stream_out) {
-    __shared__ __attribute__((aligned(16))) uint16_t bt[kWeightLds];  // [ngroup][kdim + kPad]
-    __shared__ __attribute__((aligned(16))) uint16_t ot[WAVES][16 * kOutLd];  // per wavefront: 16 result rows
-    // The weight tile: k contiguous per output column, rows padded by kPad elements, which spreads a
-    // wavefront's 16-byte reads of 32 columns over the banks.  (An unpadded tile with the 16-byte groups of
-    // column c stored at group index ^ (c + c / 8) % 8 was measured too: SQ_LDS_BANK_CONFLICT 0.55 of the
-    // LDS cycles against 0.23 for the padding.)
-    const int ldb = kdim + kPad;
-    const int n0 = blockIdx.y * ngroup;
-    const int ng = ndim - n0 < ngroup ? ndim - n0 : ngroup;
+// ---- forward ----------------------------------------------------------------------------------------
+// out[r][c] = relu( sum_k A[r][k] W[k][c] ).  KB, NB: the most blocks of 32 input and output columns; EXACT: exactly
+// that many.  W^T is staged in LDS once per workgroup, all of it, so that A is read once.  A tile of R rows at a
+// time, taken in turn across the grid (at any moment the workgroups in flight read and write one moving stretch
+// of the tables): the rows stand in LDS, each wavefront forms one block of 32 x 32 results, and these leave
+// through LDS as whole rows.  The rows of the next two tiles are in flight in registers meanwhile.
+// Bound by HBM.  Measured, 3 M rows of 256 x 128: 702 us when each of two groups of 64 columns read A again,
+// 411 now; 200 k of 128 x 128: 22.9 -> 20.2 us (a copy of the bytes: 16.4).
+constexpr int kTileThreads = 1024;   // one workgroup per compute unit
+constexpr int kTileGroups = 256;
+
+template <int KB, int NB>
+struct ForwardTile {
+    static constexpr int kRows = KB * NB <= 16 ? 128 : KB * NB <= 32 ? 64 : 32;
+    static constexpr int kLdA = KB * 32 + kPad;
+    static constexpr int kLdO = NB * 32 + kPad;
+    static constexpr bool kShared = KB * NB > 32;   // results take the place of the rows: there is no room for both
+    static constexpr int kPassesA = kRows * KB * 4 / kTileThreads;   // 16-byte pieces of a tile per thread
+    static constexpr int kPassesO = kRows * NB * 4 / kTileThreads;
+    static constexpr int kOut = kRows * kLdO, kIn = kRows * kLdA;
+};
+
+template <bool RELU, int KB, int NB, bool EXACT>
+__global__ __launch_bounds__(kTileThreads) void dense_forward(const uint16_t* __restrict__ a_rows,
+                                                              const uint16_t* __restrict__ w, uint16_t* __restrict__ out,
+                                                              int32_t n, int32_t kdim_, int32_t ndim_, int32_t stream_out) {
+    using T = ForwardTile<KB, NB>;
+    constexpr int R = T::kRows;
+    __shared__ __attribute__((aligned(16))) uint16_t wt[NB * 32 * T::kLdA];   // [ndim][kdim]
+    __shared__ __attribute__((aligned(16))) uint16_t at[T::kShared ? (T::kIn > T::kOut ? T::kIn : T::kOut) : T::kIn];
+    __shared__ __attribute__((aligned(16))) uint16_t ot_[T::kShared ? 8 : T::kOut];
+    uint16_t* ot = T::kShared ? at : ot_;
+    const int kdim = EXACT ? KB * 32 : kdim_, ndim = EXACT ? NB * 32 : ndim_;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31;
     const int khalf = lane >> 5;
-    const int ksteps = EXACT ? KS : kdim / 16;
-    const int nblocks = EXACT ? 4 : ng / 32;
-    // rows of one tile as this lane feeds them to the matrix core (zeros past the end)
-    auto load_rows = [&](int64_t r, uint4 (&va)[KS], uint4 (&vm)[MASKED ? KS : 1]) {
+    const int kvecs = kdim / 8, nvecs = ndim / 8;
+    int arow[T::kPassesA], acol[T::kPassesA], orow[T::kPassesO], ocol[T::kPassesO];   // this thread's pieces of a tile
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            va[ks] = make_uint4(0u, 0u, 0u, 0u);
-            if (MASKED) vm[ks] = make_uint4(0u, 0u, 0u, 0u);
-            if (ks < ksteps && r < n) {
-                const int64_t at = r * kdim + ks * 16 + khalf * 8;
-                va[ks] = *reinterpret_cast<const uint4*>(a_rows + at);
-                if (MASKED) vm[ks] = *reinterpret_cast<const uint4*>(mask_rows + at);
-            }
+    for (int i = 0; i < T::kPassesA; ++i) {
+        const int e = i * kTileThreads + threadIdx.x;
+        arow[i] = e / kvecs;
+        acol[i] = (e - arow[i] * kvecs) * 8;
+    }
+#pragma unroll
+    for (int i = 0; i < T::kPassesO; ++i) {
+        const int e = i * kTileThreads + threadIdx.x;
+        orow[i] = e / nvecs;
+        ocol[i] = (e - orow[i] * nvecs) * 8;
+    }
+    struct Rows {
+        uint4 v[T::kPassesA];
+    };
+    auto load_tile = [&](Rows& q, int64_t r0) {   // rows past the end: zeros
+#pragma unroll
+        for (int i = 0; i < T::kPassesA; ++i) {
+            q.v[i] = make_uint4(0u, 0u, 0u, 0u);
+            if ((EXACT || arow[i] < R) && r0 + arow[i] < n)
+                q.v[i] = *reinterpret_cast<const uint4*>(a_rows + (r0 + arow[i]) * kdim + acol[i]);
         }
     };
-    constexpr int kDenseThreads = 64 * WAVES;
-    constexpr int kRowsPerBlock = 32 * WAVES;   // one 32-row MFMA tile per wavefront
-    const int64_t row_first = (int64_t)blockIdx.x * kRowsPerBlock + wave * 32 + l32;
-    const int64_t row_step = (int64_t)gridDim.x * kRowsPerBlock;
-    // tiles requested ahead of the one being multiplied (each holds KS, masked 2 KS, 16-byte registers)
-    constexpr int DEPTH = (MASKED || KS > 8) ? 1 : kDenseDepth;
-    uint4 nxt_a[DEPTH][KS], nxt_m[DEPTH][MASKED ? KS : 1];
-#pragma unroll
-    for (int d = 0; d < DEPTH; ++d) load_rows(row_first + d * row_step, nxt_a[d], nxt_m[d]);   // in flight while the weight tile is staged
-    if (TRANS_W) {
-        // Transposing.  A thread takes the same 8 columns of two consecutive rows of W (k = 2 kp, 2 kp + 1),
-        // 16 bytes each, and writes, for each of the 8 columns, the pair as one 4-byte word into that
-        // column's row of the tile.  Consecutive lanes hold consecutive kp: a store instruction fills
-        // consecutive banks.
-        const int cvecs = ng / 8, kpairs = kdim / 2;
-        uint32_t* bt32 = reinterpret_cast<uint32_t*>(bt);
-        const int ldw = ldb / 2;
-        for (int e = threadIdx.x; e < kpairs * cvecs; e += kDenseThreads) {
+    const int64_t step = (int64_t)gridDim.x * R;
+    int64_t r0 = (int64_t)blockIdx.x * R;
+    Rows qa, qb;
+    load_tile(qa, r0);
+    load_tile(qb, r0 + step);
+    {
+        // W^T: a thread takes the same 8 columns of two consecutive rows of W (k = 2 kp, 2 kp + 1), 16 bytes each, and
+        // writes, for each of the 8 columns, the pair as one 4-byte word into that column's row of the tile.
+        // Consecutive lanes hold consecutive kp: a store instruction fills consecutive banks.
+        const int kpairs = kdim / 2;
+        uint32_t* wt32 = reinterpret_cast<uint32_t*>(wt);
+        constexpr int ldw = T::kLdA / 2;
+        for (int e = threadIdx.x; e < kpairs * nvecs; e += kTileThreads) {
             const int ch = e / kpairs, kp = e - ch * kpairs;
-            const uint16_t* src = w + (int64_t)(2 * kp) * w_ld + n0 + ch * 8;
+            const uint16_t* src = w + (int64_t)(2 * kp) * ndim + ch * 8;
             const uint4 q0 = *reinterpret_cast<const uint4*>(src);
-            const uint4 q1 = *reinterpret_cast<const uint4*>(src + w_ld);
+            const uint4 q1 = *reinterpret_cast<const uint4*>(src + ndim);
             const uint32_t w0[4] = {q0.x, q0.y, q0.z, q0.w};
             const uint32_t w1[4] = {q1.x, q1.y, q1.z, q1.w};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int c = ch * 8 + 2 * j;
-                bt32[c * ldw + kp] = (w0[j] & 0xffffu) | (w1[j] << 16);
-                bt32[(c + 1) * ldw + kp] = (w0[j] >> 16) | (w1[j] & 0xffff0000u);
+                wt32[c * ldw + kp] = (w0[j] & 0xffffu) | (w1[j] << 16);
+                wt32[(c + 1) * ldw + kp] = (w0[j] >> 16) | (w1[j] & 0xffff0000u);
             }
         }
-    } else {
-        const int kvecs = kdim / 8;
-        for (int e = threadIdx.x; e < ng * kvecs; e += kDenseThreads) {
-            const int c = e / kvecs, kv = e - c * kvecs;
-            *reinterpret_cast<uint4*>(bt + c * ldb + kv * 8) =
-                *reinterpret_cast<const uint4*>(w + (int64_t)(n0 + c) * w_ld + kv * 8);
-        }
     }
-    __syncthreads();
-
-#pragma unroll 1
-    for (int tile = 0; tile < tiles; ++tile) {
-    const int64_t row = row_first + tile * row_step;
-    if ((int64_t)row - l32 >= n) return;   // the whole wavefront is past the end
-
-    uint4 areg[KS];
+    const int rb = wave % (R / 32), cb = wave / (R / 32);   // this wavefront's block of a tile
+    const bool live = cb < NB && (EXACT || cb * 32 < ndim);
+    const uint16_t* wb = wt + (cb * 32 + l32) * T::kLdA + khalf * 8;
+    const uint16_t* ab = at + (rb * 32 + l32) * T::kLdA + khalf * 8;
+    auto do_tile = [&](Rows& q) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) areg[ks] = MASKED ? mask_vec(nxt_a[0][ks], nxt_m[0][ks]) : nxt_a[0][ks];
+        for (int i = 0; i < T::kPassesA; ++i)
+            if (EXACT || arow[i] < R) *reinterpret_cast<uint4*>(at + arow[i] * T::kLdA + acol[i]) = q.v[i];
+        __syncthreads();
+        if (r0 + 2 * step < n) load_tile(q, r0 + 2 * step);
+        f32x16 d;
+        if (live) {
 #pragma unroll
-    for (int d = 0; d + 1 < DEPTH; ++d) {
+            for (int i = 0; i < 16; ++i) d[i] = 0.0f;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            nxt_a[d][ks] = nxt_a[d + 1][ks];
-            if (MASKED) nxt_m[d][ks] = nxt_m[d + 1][ks];
+            for (int ks = 0; ks < KB * 2; ++ks)
+                if (EXACT || ks * 16 < kdim)
+                    d = mfma(*reinterpret_cast<const uint4*>(wb + ks * 16), *reinterpret_cast<const uint4*>(ab + ks * 16), d);  // D[c][r]
         }
-    }
-    if (tile + DEPTH < tiles) load_rows(row + DEPTH * row_step, nxt_a[DEPTH - 1], nxt_m[DEPTH - 1]);
-    f32x16 acc[4];
+        if (T::kShared) __syncthreads();
+        if (live) {
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
+            for (int g4 = 0; g4 < 4; ++g4) {
+                float v[4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[nb][i] = 0.0f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        if (ks < ksteps) {
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                if (nb < nblocks) {
-                    const uint4 b = *reinterpret_cast<const uint4*>(bt + (nb * 32 + l32) * ldb + ks * 16 + khalf * 8);
-                    acc[nb] = mfma(b, areg[ks], acc[nb]);  // D[out column][row]
+                for (int i = 0; i < 4; ++i) {
+                    v[i] = d[g4 * 4 + i];
+                    if (RELU && !(v[i] > 0.0f)) v[i] = 0.0f;
                 }
+                *reinterpret_cast<uint2*>(ot + (rb * 32 + l32) * T::kLdO + cb * 32 + g4 * 8 + khalf * 4) =
+                    make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
             }
         }
-    }
-    // A lane holds runs of 4 output columns of its row.  Stored from here they would leave as 8-byte
-    // pieces, 16 store instructions that each touch 32 rows; instead the wavefront's results go
-    // through its LDS tile, 16 rows at a time, and leave as whole rows (a store instruction then
-    // writes 4 consecutive rows, 1 KiB in one piece).  Measured at 4 M rows: 634 -> 420 us.
-    uint2 pk[4][4];
+        __syncthreads();
 #pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-            float v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[i] = acc[nb][g4 * 4 + i];
-                if (RELU && !(v[i] > 0.0f)) v[i] = 0.0f;
-            }
-            pk[nb][g4].x = pack_bf16(v[0], v[1]);
-            pk[nb][g4].y = pack_bf16(v[2], v[3]);
-        }
-    }
-    uint16_t* ow = ot[wave];
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        if ((l32 >> 4) == half) {
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) {
-                if (nb < nblocks) {
-#pragma unroll
-                    for (int g4 = 0; g4 < 4; ++g4)
-                        *reinterpret_cast<uint2*>(ow + (l32 & 15) * kOutLd + nb * 32 + g4 * 8 + khalf * 4) = pk[nb][g4];
-                }
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {   // 16 rows x 16 chunks of 16 bytes, 64 lanes per pass (128 output columns)
-            const int r = it * 4 + (lane >> 4), ch = lane & 15;
-            const int64_t grow = row - l32 + half * 16 + r;
-            if (grow < n && ch * 8 < ng)
-            {
-                const uint4 v = *reinterpret_cast<const uint4*>(ow + r * kOutLd + ch * 8);
+        for (int i = 0; i < T::kPassesO; ++i) {
+            if ((EXACT || orow[i] < R) && r0 + orow[i] < n) {
+                const uint4 v = *reinterpret_cast<const uint4*>(ot + orow[i] * T::kLdO + ocol[i]);
+                uint16_t* dst = out + (r0 + orow[i]) * ndim + ocol[i];
                 if (stream_out) {   // tables far larger than the caches: do not let the results displace the inputs
                     const u32x4 w4 = {v.x, v.y, v.z, v.w};
-                    __builtin_nontemporal_store(w4, reinterpret_cast<u32x4*>(out + grow * ndim + n0 + ch * 8));
+                    __builtin_nontemporal_store(w4, reinterpret_cast<u32x4*>(dst));
                 } else {
-                    *reinterpret_cast<uint4*>(out + grow * ndim + n0 + ch * 8) = v;
+                    *reinterpret_cast<uint4*>(dst) = v;
                 }
             }
         }
-        __builtin_amdgcn_wave_barrier();
-    }
+        if (T::kShared) __syncthreads();
+        r0 += step;
+    };
+#pragma unroll 1
+    while (r0 < n) {
+        do_tile(qa);
+        if (r0 < n) do_tile(qb);
     }
 }
 
-// partial[blockIdx.x][c][o] = sum over this block's node rows of P[r][c] * dZ[r][o].
-// grid.y / grid.z: groups of 128 columns of P / of dZ.
-// The node rows are the contraction index, so both operands go through LDS transposed, kTileRows rows a
-// step.  A thread takes the same 8 columns of two consecutive rows and writes, for each column, the pair as
-// one 4-byte word: consecutive lanes hold consecutive row pairs, so a store instruction fills consecutive
-// banks.  The rows of the next two steps are requested while the current one is multiplied.
-template <bool MASKED>
-__global__ __launch_bounds__(kGradThreads) void weight_grad_partial(const uint16_t* __restrict__ p,
-                                                                const uint16_t* __restrict__ gh,
-                                                                const uint16_t* __restrict__ h,
-                                                                float* __restrict__ partial, int32_t n,
-                                                                int32_t fin, int32_t fout,
-                                                                int32_t rows_per_block) {
-    __shared__ __attribute__((aligned(16))) uint16_t pt[128 * kTileLd];  // P^T tile  [c][r]
-    __shared__ __attribute__((aligned(16))) uint16_t zt[128 * kTileLd];  // dZ^T tile [o][r]
-    const int c0 = blockIdx.y * 128, o0 = blockIdx.z * 128;
-    const int cg = fin - c0 < 128 ? fin - c0 : 128;
-    const int og = fout - o0 < 128 ? fout - o0 : 128;
+// ---- backward ---------------------------------------------------------------------------------------
+// Four 16-bit values of one matrix column, from four consecutive rows of a row-major LDS tile: in every group
+// of 16 lanes, lanes 4 k .. 4 k + 3 name the 16 columns of row k (8 bytes each), and lane m gets column m of
+// the four rows.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint2 read_transposed(const uint16_t* p) {
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(const_cast<uint16_t*>(p))));
+}
+
+// dP[r][c] = sum_o dZ[r][o] W[c][o] and partial[blockIdx.x][c][o] = sum over this workgroup's rows of
+// P[r][c] dZ[r][o], with dZ = gH, or gH where H > 0 (MASKED).  FINB, FOUTB: the most blocks of 32 columns of P (of
+// one group, grid.y) and of dZ; EXACT: exactly that many.
+// A tile of R rows at a time, taken in turn across the grid; gH, H and P are read once and stand in LDS row by
+// row.  For dP the contraction runs along a row, for dW down the rows: there the matrix cores' operands come
+// from the same tiles through transposing LDS reads.  Sixteen wavefronts, each with one block of 32 x 32 of dP per
+// tile and one or two of dW for the whole kernel; the next tile's rows are in flight in registers during
+// the products.  (Row pitches: dZ is read both ways; a pitch of 20 banks beyond a multiple of 64 serves rows
+// without conflicts and columns nearly so; P is read down the columns only: 16 banks.)
+// Bound by HBM: 2 x (2 Fout + 2 Fin) bytes a row.  Measured with the reduction behind it: 200 k rows of 128 x 128
+// 69 us when dP and dW were two kernels that both read gH and H, 41 now (a copy of the bytes: 33); 3 M rows of
+// 256 x 128 1722 and 862 us (738).
+constexpr int kBackWaves = kTileThreads / 64;
+
+template <int FINB, int FOUTB>
+struct BackTile {
+    static constexpr int kRows = FINB * FOUTB == 16 ? 128 : 64;
+    static constexpr int kLdW = FOUTB * 32 + kPad;
+    static constexpr int kLdZ = FOUTB * 32 + (FINB == 8 ? 8 : 40);
+    static constexpr int kLdP = FINB * 32 + 32;
+    static constexpr int kLdO = FINB * 32 + kPad;
+    static constexpr int kPassesZ = kRows * FOUTB * 4 / kTileThreads;   // 16-byte pieces of a tile per thread
+    static constexpr int kPassesP = kRows * FINB * 4 / kTileThreads;
+    static constexpr int kAccs = FINB * FOUTB / kBackWaves;             // blocks of dW per wavefront
+};
+
+template <bool MASKED, int FINB, int FOUTB, bool EXACT>
+__global__ __launch_bounds__(kTileThreads) void dense_backward(const uint16_t* __restrict__ p_rows,
+                                                               const uint16_t* __restrict__ w,
+                                                               const uint16_t* __restrict__ h_rows,
+                                                               const uint16_t* __restrict__ gh_rows,
+                                                               uint16_t* __restrict__ gp, float* __restrict__ partial,
+                                                               int32_t n, int32_t fin_, int32_t fout_, int32_t stream_out) {
+    using T = BackTile<FINB, FOUTB>;
+    constexpr int R = T::kRows;
+    __shared__ __attribute__((aligned(16))) uint16_t wt[FINB * 32 * T::kLdW];   // [c][o]
+    __shared__ __attribute__((aligned(16))) uint16_t zt[R * T::kLdZ];           // [r][o]
+    __shared__ __attribute__((aligned(16))) uint16_t pt[R * T::kLdP];           // [r][c]
+    __shared__ __attribute__((aligned(16))) uint16_t ot[R * T::kLdO];           // [r][c]
+    const int fin = EXACT ? FINB * 32 : fin_, fout = EXACT ? FOUTB * 32 : fout_;
+    const int c0 = EXACT ? 0 : blockIdx.y * (FINB * 32);
+    const int cg = EXACT ? FINB * 32 : (fin - c0 < FINB * 32 ? fin - c0 : FINB * 32);   // columns of P in this group
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l32 = lane & 31;
     const int khalf = lane >> 5;
-    const int rp = threadIdx.x & 31;   // row pair of the tile (and every 32nd after it)
-    const int cq = threadIdx.x >> 5;   // 8-column chunk (and every kChunkLanes-th after it)
-    const int oblocks = og / 32;
-    // products: this wavefront owns 32 columns of P and kGradOBlocks blocks of 32 columns of dZ
-    const int cw = wave & 3;
-    const int ob0 = (wave >> 2) * kGradOBlocks;
-    const bool wave_live = cw * 32 < cg && ob0 < oblocks;
-
-    f32x16 acc[kGradOBlocks];
+    // a thread's pieces of a tile: row and first column, the same in every tile
+    const int zvecs = fout / 8, pvecs = cg / 8;
+    int zrow[T::kPassesZ], zcol[T::kPassesZ], prow[T::kPassesP], pcol[T::kPassesP];
 #pragma unroll
-    for (int ob = 0; ob < kGradOBlocks; ++ob)
+    for (int i = 0; i < T::kPassesZ; ++i) {
+        const int e = i * kTileThreads + threadIdx.x;
+        zrow[i] = e / zvecs;
+        zcol[i] = (e - zrow[i] * zvecs) * 8;
+    }
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[ob][i] = 0.0f;
-
-    const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
-    const int64_t r_end = r_begin + rows_per_block < n ? r_begin + rows_per_block : n;
-    // A thread's pieces of one step: for each of its row pairs and column chunks, two rows of P and of dZ
-    // (dZ with its mask still beside it).  Piece i: chunk rep i % kChunkReps, pair pass i / kChunkReps.
-    constexpr int kPieces = kChunkReps * kPairPasses;
-    struct Step {
-        uint4 p0[kPieces], p1[kPieces], z0[kPieces], z1[kPieces], h0[MASKED ? kPieces : 1], h1[MASKED ? kPieces : 1];
-    };
-    auto load_step = [&](Step& q, int64_t r0) {
+    for (int i = 0; i < T::kPassesP; ++i) {
+        const int e = i * kTileThreads + threadIdx.x;
+        prow[i] = e / pvecs;
+        pcol[i] = (e - prow[i] * pvecs) * 8;
+    }
+    uint4 qz[T::kPassesZ], qh[MASKED ? T::kPassesZ : 1], qp[T::kPassesP];
+    auto load_tile = [&](int64_t r0) {   // rows past the end: zeros
+        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int cv = cq + (i % kChunkReps) * kChunkLanes;
-            const int64_t r = r0 + 2 * (rp + (i / kChunkReps) * 32);
-            const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-            q.p0[i] = q.p1[i] = q.z0[i] = q.z1[i] = zero;
-            if (MASKED) q.h0[i] = q.h1[i] = zero;
-            if (r < r_end) {
-                if (cv * 8 < cg) q.p0[i] = *reinterpret_cast<const uint4*>(p + r * fin + c0 + cv * 8);
-                if (cv * 8 < og) {
-                    q.z0[i] = *reinterpret_cast<const uint4*>(gh + r * fout + o0 + cv * 8);
-                    if (MASKED) q.h0[i] = *reinterpret_cast<const uint4*>(h + r * fout + o0 + cv * 8);
-                }
-            }
-            if (r + 1 < r_end) {
-                if (cv * 8 < cg) q.p1[i] = *reinterpret_cast<const uint4*>(p + (r + 1) * fin + c0 + cv * 8);
-                if (cv * 8 < og) {
-                    q.z1[i] = *reinterpret_cast<const uint4*>(gh + (r + 1) * fout + o0 + cv * 8);
-                    if (MASKED) q.h1[i] = *reinterpret_cast<const uint4*>(h + (r + 1) * fout + o0 + cv * 8);
-                }
+        for (int i = 0; i < T::kPassesZ; ++i) {
+            qz[i] = zero;
+            if (MASKED) qh[i] = zero;
+            if ((EXACT || zrow[i] < R) && r0 + zrow[i] < n) {
+                const int64_t at = (r0 + zrow[i]) * fout + zcol[i];
+                qz[i] = *reinterpret_cast<const uint4*>(gh_rows + at);
+                if (MASKED) qh[i] = *reinterpret_cast<const uint4*>(h_rows + at);
             }
         }
-    };
-    uint32_t* pt32 = reinterpret_cast<uint32_t*>(pt);
-    uint32_t* zt32 = reinterpret_cast<uint32_t*>(zt);
-    constexpr int kTileLdw = kTileLd / 2;
-    auto write_pairs = [&](uint32_t* t32, int cv, int pair, const uint4 a, const uint4 b) {
-        const uint32_t wa[4] = {a.x, a.y, a.z, a.w};
-        const uint32_t wb[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            t32[(cv * 8 + 2 * j) * kTileLdw + pair] = (wa[j] & 0xffffu) | (wb[j] << 16);
-            t32[(cv * 8 + 2 * j + 1) * kTileLdw + pair] = (wa[j] >> 16) | (wb[j] & 0xffff0000u);
+        for (int i = 0; i < T::kPassesP; ++i) {
+            qp[i] = zero;
+            if ((EXACT || prow[i] < R) && r0 + prow[i] < n)
+                qp[i] = *reinterpret_cast<const uint4*>(p_rows + (r0 + prow[i]) * fin + c0 + pcol[i]);
         }
     };
-    // one step: its rows into the tiles, the step after next requested into the registers just freed, product
-    auto do_step = [&](Step& q, int64_t r_next) {
+    const int64_t step = (int64_t)gridDim.x * R;
+    int64_t r0 = (int64_t)blockIdx.x * R;
+    load_tile(r0);
+    for (int e = threadIdx.x; e < cg * zvecs; e += kTileThreads) {
+        const int c = e / zvecs, v = e - c * zvecs;
+        *reinterpret_cast<uint4*>(wt + c * T::kLdW + v * 8) = *reinterpret_cast<const uint4*>(w + (int64_t)(c0 + c) * fout + v * 8);
+    }
+    // this wavefront's block of dP in every tile, and its blocks of dW
+    constexpr int kRowBlocks = R / 32;
+    const int prb = wave % kRowBlocks, pcb = wave / kRowBlocks;
+    const bool p_live = gp && pcb < FINB && (EXACT || pcb * 32 < cg);
+    const int wcb = wave * T::kAccs / FOUTB, wob = wave * T::kAccs % FOUTB;   // blocks (wcb, wob), (wcb, wob + 1)
+    const bool w_live = partial && (EXACT || wcb * 32 < cg);
+    const int obs = fout / 32;
+    // offset of this lane in a transposing read of 16 rows x 32 columns (see read_transposed)
+    const int tr_row = khalf * 8 + ((lane & 15) >> 2), tr_col = ((lane >> 4) & 1) * 16 + (lane & 3) * 4;
+    f32x16 acc[T::kAccs];
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int cv = cq + (i % kChunkReps) * kChunkLanes;
-            const int pair = rp + (i / kChunkReps) * 32;
-            write_pairs(pt32, cv, pair, q.p0[i], q.p1[i]);
-            write_pairs(zt32, cv, pair, MASKED ? mask_vec(q.z0[i], q.h0[i]) : q.z0[i],
-                        MASKED ? mask_vec(q.z1[i], q.h1[i]) : q.z1[i]);
-        }
+    for (int u = 0; u < T::kAccs; ++u)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
+
+#pragma unroll 1
+    for (; r0 < n; r0 += step) {
+#pragma unroll
+        for (int i = 0; i < T::kPassesZ; ++i)
+            if (EXACT || zrow[i] < R)
+                *reinterpret_cast<uint4*>(zt + zrow[i] * T::kLdZ + zcol[i]) = MASKED ? mask_vec(qz[i], qh[i]) : qz[i];
+#pragma unroll
+        for (int i = 0; i < T::kPassesP; ++i)
+            if (EXACT || prow[i] < R) *reinterpret_cast<uint4*>(pt + prow[i] * T::kLdP + pcol[i]) = qp[i];
         __syncthreads();
-        if (r_next < r_end) load_step(q, r_next);
-        if (wave_live) {
+        if (r0 + step < n) load_tile(r0 + step);
+        if (p_live) {
+            f32x16 d;
 #pragma unroll
-            for (int ks = 0; ks < kTileRows / 16; ++ks) {
-                const uint4 a = *reinterpret_cast<const uint4*>(pt + (cw * 32 + l32) * kTileLd + ks * 16 + khalf * 8);
+            for (int i = 0; i < 16; ++i) d[i] = 0.0f;
+            const uint16_t* wb = wt + (pcb * 32 + l32) * T::kLdW + khalf * 8;
+            const uint16_t* zb = zt + (prb * 32 + l32) * T::kLdZ + khalf * 8;
 #pragma unroll
-                for (int ob = 0; ob < kGradOBlocks; ++ob) {
-                    if (ob0 + ob < oblocks) {
-                        const uint4 b = *reinterpret_cast<const uint4*>(zt + ((ob0 + ob) * 32 + l32) * kTileLd + ks * 16 + khalf * 8);
-                        acc[ob] = mfma(a, b, acc[ob]);  // D[c][o]
+            for (int ks = 0; ks < FOUTB * 2; ++ks) {
+                if (EXACT || ks * 16 < fout)
+                    d = mfma(*reinterpret_cast<const uint4*>(wb + ks * 16), *reinterpret_cast<const uint4*>(zb + ks * 16), d);  // D[c][r]
+            }
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4)
+                *reinterpret_cast<uint2*>(ot + (prb * 32 + l32) * T::kLdO + pcb * 32 + g4 * 8 + khalf * 4) =
+                    make_uint2(pack_bf16(d[g4 * 4], d[g4 * 4 + 1]), pack_bf16(d[g4 * 4 + 2], d[g4 * 4 + 3]));
+        }
+        if (w_live) {
+            const uint16_t* pb = pt + tr_row * T::kLdP + wcb * 32 + tr_col;
+            const uint16_t* zb = zt + tr_row * T::kLdZ + wob * 32 + tr_col;
+#pragma unroll
+            for (int ks = 0; ks < R / 16; ++ks) {
+                const uint2 a0 = read_transposed(pb + ks * 16 * T::kLdP), a1 = read_transposed(pb + (ks * 16 + 4) * T::kLdP);
+                const uint4 a = make_uint4(a0.x, a0.y, a1.x, a1.y);
+#pragma unroll
+                for (int u = 0; u < T::kAccs; ++u) {
+                    if (EXACT || wob + u < obs) {
+                        const uint16_t* zu = zb + u * 32;
+                        const uint2 b0 = read_transposed(zu + ks * 16 * T::kLdZ), b1 = read_transposed(zu + (ks * 16 + 4) * T::kLdZ);
+                        acc[u] = mfma(a, make_uint4(b0.x, b0.y, b1.x, b1.y), acc[u]);  // D[c][o]
                     }
                 }
             }
         }
         __syncthreads();
-    };
-    Step qa, qb;
-    load_step(qa, r_begin);
-    load_step(qb, r_begin + kTileRows);   // past r_end: zeros, nothing read
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += 2 * kTileRows) {
-        do_step(qa, r0 + 2 * kTileRows);
-        if (r0 + kTileRows < r_end) do_step(qb, r0 + 3 * kTileRows);
+        if (gp) {
+#pragma unroll
+            for (int i = 0; i < T::kPassesP; ++i) {
+                if ((EXACT || prow[i] < R) && r0 + prow[i] < n) {
+                    const uint4 v = *reinterpret_cast<const uint4*>(ot + prow[i] * T::kLdO + pcol[i]);
+                    uint16_t* dst = gp + (r0 + prow[i]) * fin + c0 + pcol[i];
+                    if (stream_out) {
+                        const u32x4 w4 = {v.x, v.y, v.z, v.w};
+                        __builtin_nontemporal_store(w4, reinterpret_cast<u32x4*>(dst));
+                    } else {
+                        *reinterpret_cast<uint4*>(dst) = v;
+                    }
+                }
+            }
+        }
     }
-    if (!wave_live) return;
+    if (!w_live) return;
     float* dst = partial + (int64_t)blockIdx.x * fin * fout;
 #pragma unroll
-    for (int ob = 0; ob < kGradOBlocks; ++ob) {
-        if (ob0 + ob < oblocks) {
+    for (int u = 0; u < T::kAccs; ++u) {
+        if (EXACT || wob + u < obs) {
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const int c = c0 + cw * 32 + (i / 4) * 8 + khalf * 4 + (i % 4);
-                dst[(int64_t)c * fout + o0 + (ob0 + ob) * 32 + l32] = acc[ob][i];
+                const int c = c0 + wcb * 32 + (i / 4) * 8 + khalf * 4 + (i % 4);
+                dst[(int64_t)c * fout + (wob + u) * 32 + l32] = acc[u][i];
             }
         }
     }
@@ -397,41 +411,64 @@ __global__ __launch_bounds__(kReduceThreads) void weight_grad_reduce(const float
     }
 }
 
-// Node rows per workgroup of weight_grad_partial: about one workgroup per compute unit, so that
-// few partial matrices are written and read back.
-int32_t rows_per_block_for(int32_t n) {
-    int64_t r = ceil_div(n > 0 ? n : 1, 256);
-    r = (r + 63) / 64 * 64;
-    return (int32_t)(r < 128 ? 128 : r);
+// Workgroups of dense_backward per group of columns of P, and so partial matrices: one per compute unit, fewer
+// where there are fewer than 128 rows for each.
+int32_t back_groups(int32_t n, int32_t fin, int32_t fout) {
+    const int64_t column_groups = fout > 128 ? ceil_div(fin, 128) : 1;
+    const int64_t most = kTileGroups / column_groups;
+    const int64_t want = ceil_div(n > 0 ? n : 1, 128);
+    return (int32_t)(want < most ? want : most);
 }
 
-template <bool MASKED, bool TRANS_W, bool RELU, int KS, bool EXACT, int WAVES>
-void launch_dense_as(const void* a, const void* mask, const void* w, void* out, int32_t n, int32_t kdim, int32_t ndim,
-                     int32_t w_ld, int32_t ngroup, hipStream_t stream) {
-    // eight wavefronts per compute unit, each taking as many tiles in turn as that leaves it, but no more
-    // workgroups than blocks of rows
-    const int64_t blocks = ceil_div(n, (int64_t)32 * WAVES);
-    int64_t tiles = ceil_div(blocks, (int64_t)kDenseMaxGroups * (8 / WAVES));
-    tiles = tiles < 1 ? 1 : tiles;
-    const dim3 grid((unsigned)ceil_div(blocks, tiles), (unsigned)ceil_div(ndim, ngroup));
-    // streaming stores once the result is far larger than the caches (measured: 5 % at 4 M rows); below
-    // that the next kernel of a mini-batch step finds the rows in the caches if they are written normally
-    const int32_t stream_out = (int64_t)n * ndim * 2 > (64ll << 20) ? 1 : 0;
-    dense_rows<MASKED, TRANS_W, RELU, KS, EXACT, WAVES><<<grid, dim3(64 * WAVES), 0, stream>>>(
-        static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(mask), static_cast<const uint16_t*>(w),
-        static_cast<uint16_t*>(out), n, kdim, ndim, w_ld, ngroup, (int32_t)tiles, stream_out);
-}
+// Streaming stores once the result is far larger than the caches (5 % at 4 M rows); below that the next
+// kernel of a mini-batch step finds the rows in the caches if they are written normally.
+int32_t streams_out(int64_t n, int32_t cols) { return n * cols * 2 > (64ll << 20) ? 1 : 0; }
 
-template <bool MASKED, bool TRANS_W, bool RELU>
-void launch_dense(const void* a, const void* mask, const void* w, void* out, int32_t n, int32_t kdim,
-                  int32_t ndim, int32_t w_ld, hipStream_t stream) {
-    const int32_t ngroup = kdim > 128 ? 64 : 128;
-    if (kdim == 128 && ndim % 128 == 0)
-        launch_dense_as<MASKED, TRANS_W, RELU, 8, true, kDenseWaves>(a, mask, w, out, n, kdim, ndim, w_ld, ngroup, stream);
-    else if (kdim <= 128)
-        launch_dense_as<MASKED, TRANS_W, RELU, 8, false, kDenseWaves>(a, mask, w, out, n, kdim, ndim, w_ld, ngroup, stream);
+template <bool RELU, int KB, int NB>
+void launch_forward_as(const uint16_t* a, const uint16_t* w, uint16_t* out, int32_t n, int32_t kdim, int32_t ndim, hipStream_t stream) {
+    const int64_t tiles = ceil_div(n, ForwardTile<KB, NB>::kRows);
+    const dim3 grid((unsigned)(tiles < kTileGroups ? tiles : kTileGroups)), blk(kTileThreads);
+    const int32_t so = streams_out(n, ndim);
+    if (kdim == KB * 32 && ndim == NB * 32)
+        dense_forward<RELU, KB, NB, true><<<grid, blk, 0, stream>>>(a, w, out, n, kdim, ndim, so);
     else
-        launch_dense_as<MASKED, TRANS_W, RELU, kMaxF / 16, false, 4>(a, mask, w, out, n, kdim, ndim, w_ld, ngroup, stream);
+        dense_forward<RELU, KB, NB, false><<<grid, blk, 0, stream>>>(a, w, out, n, kdim, ndim, so);
+}
+
+template <bool RELU>
+void launch_forward(const void* a_, const void* w_, void* out_, int32_t n, int32_t kdim, int32_t ndim, hipStream_t stream) {
+    const uint16_t* a = static_cast<const uint16_t*>(a_);
+    const uint16_t* w = static_cast<const uint16_t*>(w_);
+    uint16_t* out = static_cast<uint16_t*>(out_);
+    if (kdim <= 128 && ndim <= 128) launch_forward_as<RELU, 4, 4>(a, w, out, n, kdim, ndim, stream);
+    else if (kdim <= 128) launch_forward_as<RELU, 4, 8>(a, w, out, n, kdim, ndim, stream);
+    else if (ndim <= 128) launch_forward_as<RELU, 8, 4>(a, w, out, n, kdim, ndim, stream);
+    else launch_forward_as<RELU, 8, 8>(a, w, out, n, kdim, ndim, stream);
+}
+
+template <bool MASKED, int FINB, int FOUTB>
+void launch_back_as(const uint16_t* p, const uint16_t* w, const uint16_t* h, const uint16_t* gh, uint16_t* gp, float* partial,
+                    int32_t n, int32_t fin, int32_t fout, hipStream_t stream) {
+    const dim3 grid((unsigned)back_groups(n, fin, fout), (unsigned)ceil_div(fin, FINB * 32)), blk(kTileThreads);
+    const int32_t so = streams_out(n, fin);
+    if (fin == FINB * 32 && fout == FOUTB * 32)
+        dense_backward<MASKED, FINB, FOUTB, true><<<grid, blk, 0, stream>>>(p, w, h, gh, gp, partial, n, fin, fout, so);
+    else
+        dense_backward<MASKED, FINB, FOUTB, false><<<grid, blk, 0, stream>>>(p, w, h, gh, gp, partial, n, fin, fout, so);
+}
+
+template <bool MASKED>
+void launch_back(const void* p_, const void* w_, const void* h_, const void* gh_, void* gp_, float* partial, int32_t n,
+                 int32_t fin, int32_t fout, hipStream_t stream) {
+    const uint16_t* p = static_cast<const uint16_t*>(p_);
+    const uint16_t* w = static_cast<const uint16_t*>(w_);
+    const uint16_t* h = static_cast<const uint16_t*>(h_);
+    const uint16_t* gh = static_cast<const uint16_t*>(gh_);
+    uint16_t* gp = static_cast<uint16_t*>(gp_);
+    // wide gradients: groups of 128 columns of P, or W and the tiles do not fit in LDS together
+    if (fout > 128) launch_back_as<MASKED, 4, 8>(p, w, h, gh, gp, partial, n, fin, fout, stream);
+    else if (fin > 128) launch_back_as<MASKED, 8, 4>(p, w, h, gh, gp, partial, n, fin, fout, stream);
+    else launch_back_as<MASKED, 4, 4>(p, w, h, gh, gp, partial, n, fin, fout, stream);
 }
 
 }  // namespace
@@ -443,7 +480,7 @@ extern "C" size_t e2eg_layer_transform_workspace_bytes(int32_t mode, int32_t n, 
                                                        int32_t Fout, int32_t dtype) {
     if (n < 0 || Fin <= 0 || Fout <= 0 || dtype != E2EG_BF16) return 0;
     if (mode != E2EG_TRANSFORM_BWD) return kAlign;
-    const int64_t blocks = ceil_div(n > 0 ? n : 1, rows_per_block_for(n));
+    const int64_t blocks = back_groups(n, Fin, Fout);
     return align_up((size_t)blocks * (size_t)Fin * (size_t)Fout * sizeof(float));
 }
 
@@ -513,31 +550,21 @@ int32_t transform_impl(const char* who, bool static_scratch, int32_t mode, int32
 
     if (mode == E2EG_TRANSFORM_FWD) {
         if (n == 0) return E2EG_OK;
-        if (relu) launch_dense<false, true, true>(d_P, nullptr, d_W, d_H, n, Fin, Fout, Fout, stream);
-        else launch_dense<false, true, false>(d_P, nullptr, d_W, d_H, n, Fin, Fout, Fout, stream);
-        E2EG_LAUNCH_CHECK("dense_rows");
+        if (relu) launch_forward<true>(d_P, d_W, d_H, n, Fin, Fout, stream);
+        else launch_forward<false>(d_P, d_W, d_H, n, Fin, Fout, stream);
+        E2EG_LAUNCH_CHECK("dense_forward");
         return E2EG_OK;
     }
-    if (d_gP && n > 0) {
-        if (relu) launch_dense<true, false, false>(d_gH, d_H, d_W, d_gP, n, Fout, Fin, Fout, stream);
-        else launch_dense<false, false, false>(d_gH, nullptr, d_W, d_gP, n, Fout, Fin, Fout, stream);
-        E2EG_LAUNCH_CHECK("dense_rows");
+    float* partial = d_gW ? static_cast<float*>(ws) : nullptr;
+    if (n > 0 && (d_gP || d_gW)) {
+        if (relu) launch_back<true>(d_P, d_W, d_H, d_gH, d_gP, partial, n, Fin, Fout, stream);
+        else launch_back<false>(d_P, d_W, d_H, d_gH, d_gP, partial, n, Fin, Fout, stream);
+        E2EG_LAUNCH_CHECK("dense_backward");
     }
     if (d_gW) {
-        const int32_t rpb = rows_per_block_for(n);
-        const int32_t blocks = n > 0 ? (int32_t)ceil_div(n, rpb) : 0;
-        float* partial = static_cast<float*>(ws);
-        if (blocks > 0) {
-            const dim3 grid((unsigned)blocks, (unsigned)ceil_div(Fin, 128), (unsigned)ceil_div(Fout, 128));
-            const uint16_t* p = static_cast<const uint16_t*>(d_P);
-            const uint16_t* gh = static_cast<const uint16_t*>(d_gH);
-            const uint16_t* h = static_cast<const uint16_t*>(d_H);
-            if (relu) weight_grad_partial<true><<<grid, dim3(kGradThreads), 0, stream>>>(p, gh, h, partial, n, Fin, Fout, rpb);
-            else weight_grad_partial<false><<<grid, dim3(kGradThreads), 0, stream>>>(p, gh, h, partial, n, Fin, Fout, rpb);
-            E2EG_LAUNCH_CHECK("weight_grad_partial");
-        }
         const int32_t count = Fin * Fout;
-        weight_grad_reduce<<<dim3((unsigned)ceil_div(count, kReduceElems)), dim3(kReduceThreads), 0, stream>>>(partial, blocks, count, d_gW);
+        weight_grad_reduce<<<dim3((unsigned)ceil_div(count, kReduceElems)), dim3(kReduceThreads), 0, stream>>>(
+            partial, n > 0 ? back_groups(n, Fin, Fout) : 0, count, d_gW);
         E2EG_LAUNCH_CHECK("weight_grad_reduce");
     }
     return E2EG_OK;
