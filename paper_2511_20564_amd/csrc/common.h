@@ -125,6 +125,14 @@ struct alignas(16) Segment {
     int32_t slot;  // partial-sum slot, or -1 when the segment is the whole row
 };
 
+// Everything a short row's lane group needs before it can ask for columns and scale, in one load.
+struct alignas(16) ShortRow {
+    int32_t row;   // internal row
+    int32_t beg;   // first entry in zcol
+    int32_t len;   // entries
+    int32_t node;  // the row's node
+};
+
 struct SchedHeader {
     int32_t n_short;   // rows with at most kShortMax entries
     int32_t n_single;  // rows of one segment
@@ -153,7 +161,7 @@ struct SchedView {
     int32_t* zrow_ptr;    // [n + 1] row pointers of the internal CSR (small form: the caller's)
     int32_t* zcol;        // [nnz] internal column ids; in each row the popular ones first, by popularity, then
                           // the others in the caller's order (small form: the same array as znode)
-    int32_t* short_rows;  // [n] internal rows with at most kShortMax entries, processing order
+    ShortRow* short_rows; // [n] rows with at most kShortMax entries, processing order
     int32_t* multi_row;   // [max_multi] internal rows cut into several segments, ascending
     int32_t* slot_base;   // [max_multi] first slot of each such row
     int32_t* slot_cnt;    // [max_multi] number of slots

@@ -534,8 +534,11 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
         if (SMALL) return row_ptr[base + at + 1];
         return at + 1 < rows ? beg[at + 1] : before[kTotEntries] + own[kTotEntries];
     };
-    for (int k = threadIdx.x; k < n_short; k += kTileThreads)
-        s.short_rows[before[kTotShort] + k] = (int32_t)(base + sorted[k]);
+    for (int k = threadIdx.x; k < n_short; k += kTileThreads) {
+        const int at = sorted[k];
+        const int32_t row = (int32_t)(base + at);
+        s.short_rows[before[kTotShort] + k] = ShortRow{row, beg[at], row_end(at) - beg[at], SMALL ? row : s.orig[row]};
+    }
     for (int k = threadIdx.x; k < n_single; k += kTileThreads) {
         const int at = sorted[n_short + k];
         s.singles[before[kTotSingle] + k] = Segment{(int32_t)(base + at), beg[at], row_end(at), -1};

@@ -389,23 +389,36 @@ __device__ __forceinline__ void run_segment(const LayerArgs<T>& a, const Segment
 // within a lane group; len < 0 for a group without a row (an empty row, len = 0, still gets its
 // all-zero result stored).
 template <typename T, int LOG_G, bool NARROW, int MODE>
-__device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const int32_t beg, const int32_t len,
-                                               const int32_t zrow, const int32_t node, const float s,
-                                               const int32_t idx_first, const float wgt_first, const int lane) {
+__device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const ShortRow row, const float s, const int lane) {
     constexpr int G = 1 << LOG_G;
     constexpr int V = T::kVec;
-    constexpr int U = kInFlight < G ? kInFlight : G;
+    constexpr int U = kInFlight;
+    constexpr int R = G < U ? U / G : 1;   // column indices a lane holds
+    constexpr int H = R * G;               // and its group together
     constexpr bool VALS = MODE != kPlain;
     const int c = lane & (G - 1);
     const int group_base = lane & ~(G - 1);
     const int chunks = a.F / V;
     const uint32_t row_bytes = (uint32_t)a.ld_in * (uint32_t)sizeof(typename T::elem);
+    const int32_t len = row.len;
+    int32_t idx_first[R];
+    float wgt_first[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int at = r * G + c;
+        idx_first[r] = at < len ? *(a.cols + row.beg + at) : a.n;
+        wgt_first[r] = 0.0f;
+        if constexpr (VALS)
+            if (at < len) wgt_first[r] = entry_value<T, MODE>(a, row.beg + at);
+    }
     int32_t none = a.n;
     if constexpr (from_caller(MODE)) {   // lane 0 of the group holds the row's first neighbour (row 0 for an empty row)
-        none = __shfl(idx_first, group_base);
+        none = __shfl(idx_first[0], group_base);
         if (len <= 0) none = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r * G + c >= len) idx_first[r] = none;
     }
-    const int32_t idx_start = (from_caller(MODE) && c >= len) ? none : idx_first;
     int maxlen = len;  // longest row of the batch (wave-uniform)
 #pragma unroll
     for (int off = G; off < 64; off <<= 1) {
@@ -420,40 +433,55 @@ __device__ __forceinline__ void run_short_rows(const LayerArgs<T>& a, const int3
         const uint32_t lane_off = active ? (uint32_t)cc * 16u : 0u;
         Sum<T> sum;
         sum.clear();
-        int32_t idx = idx_start;
-        float wgt = wgt_first;
-        for (int base = 0; base < maxlen; base += G) {
-            int32_t idx_next = none;
-            float wgt_next = 0.0f;
-            if (base + G + c < len) {
-                idx_next = *(a.cols + beg + base + G + c);
-                if constexpr (VALS) wgt_next = entry_value<T, MODE>(a, beg + base + G + c);
+        int32_t idx[R];
+        float wgt[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            idx[r] = idx_first[r];
+            wgt[r] = wgt_first[r];
+        }
+        for (int base = 0; base < maxlen; base += H) {
+            int32_t idx_next[R];
+            float wgt_next[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int at = base + H + r * G + c;
+                idx_next[r] = none;
+                wgt_next[r] = 0.0f;
+                if (at < len) {
+                    idx_next[r] = *(a.cols + row.beg + at);
+                    if constexpr (VALS) wgt_next[r] = entry_value<T, MODE>(a, row.beg + at);
+                }
             }
-            const int steps = maxlen - base < G ? maxlen - base : G;
-            for (int t = 0; t < steps; t += U) {
+            const int steps = maxlen - base < H ? maxlen - base : H;
+            for (int t = 0; t < steps; t += U) {   // R > 1: H is U, one round
                 const int live = steps - t < U ? steps - t : U;
                 uint4 q[U];
                 float wq[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
                     if (u < live) {
-                        q[u] = gather16<T, NARROW>(a, __shfl(idx, group_base + t + u), row_bytes, lane_off);
-                        if constexpr (VALS) wq[u] = __shfl(wgt, group_base + t + u);
+                        const int r = R > 1 ? u / G : 0;
+                        const int src = group_base + (R > 1 ? u % G : t + u);
+                        q[u] = gather16<T, NARROW>(a, __shfl(idx[r], src), row_bytes, lane_off);
+                        if constexpr (VALS) wq[u] = __shfl(wgt[r], src);
                     }
                 if constexpr (VALS) sum.template add_batch_scaled<U>(q, wq, live);
                 else sum.template add_batch<U>(q, live);
             }
-            idx = idx_next;
-            wgt = wgt_next;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                idx[r] = idx_next[r];
+                wgt[r] = wgt_next[r];
+            }
         }
         if constexpr (from_caller(MODE))
             if (len == 0) sum.clear();   // an empty row gathered row 0 with weight 0: its sum is 0 whatever row 0 holds
-        if (active && len >= 0) finish_vec<T>(a, zrow, node, s, cc * V, sum.acc);
+        if (active && len >= 0) finish_vec<T>(a, row.row, row.node, s, cc * V, sum.acc);
     }
 }
 
 constexpr int kWaves = 4;          // wavefronts per workgroup
-constexpr int kShortPerWave = 8;   // short rows a wavefront works through, 64/G at a time
 constexpr int kSingleBlocksPerXcd = 512;  // B-workgroups per XCD (fewer when the graph cannot have that many such rows)
 
 // Three kinds of workgroup.
@@ -483,9 +511,7 @@ constexpr int kSingleBlocksPerXcd = 512;  // B-workgroups per XCD (fewer when th
 // would otherwise take 144 at 128-byte bf16 rows and lose a resident wavefront; none of them spills at 128.
 template <typename T, int LOG_G, bool NARROW, int MODE>
 __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))) void spmm_rows(const LayerArgs<T> a) {
-    constexpr int G = 1 << LOG_G;
     constexpr int NB = 64 >> LOG_G;
-    constexpr bool VALS = MODE != kPlain;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // The launch has one workgroup more than the schedule needs; it writes the all-zero row of the Z
@@ -506,7 +532,7 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
     const int64_t a_lo = h->xcd_first[x], a_hi = h->xcd_first[x + 1];
     int64_t n_a = (a_hi - a_lo + kWaves - 1) / kWaves;
     if (n_a > a.a_blocks) n_a = a.a_blocks;   // a longer stretch than the launch was sized for: go round again
-    const int64_t c_total = ((int64_t)h->n_short + kWaves * kShortPerWave - 1) / (kWaves * kShortPerWave);
+    const int64_t c_total = ((int64_t)h->n_short + kWaves * NB - 1) / (kWaves * NB);
     const int64_t n_b = a.b_blocks;                      // a fixed number, with equal shares of the rows
     const int64_t n_c = (c_total + kXcds - 1) / kXcds;
     const int64_t total = n_a + n_b + n_c;
@@ -537,44 +563,12 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4))
     // user rows fill the gaps (in node order the launch ended with a tail: 62 against 43 us on a sampled
     // subgraph of 175 k nodes)
     if (!a.sched.orig) rb = c_total - 1 - rb;
-    const int64_t n_short = a.sched.header->n_short;
-    const int64_t first = (rb * kWaves + wave) * kShortPerWave;
-    if (first >= n_short) return;
-    const int n_rows = n_short - first < kShortPerWave ? (int)(n_short - first) : kShortPerWave;
-    int32_t my_row = 0, my_beg = 0, my_len = -1, my_node = 0;
-    float my_s = 0.0f;
-    if (lane < n_rows) {
-        my_row = a.sched.short_rows[first + lane];
-        my_beg = a.sched.zrow_ptr[my_row];
-        my_len = a.sched.zrow_ptr[my_row + 1] - my_beg;
-        my_node = node_of(a, my_row);
-        my_s = row_scale<T>(a, my_node, my_len, refuse);
-    }
-    const int c = lane & (G - 1);
-    const int g = lane >> LOG_G;
-    const int32_t none = from_caller(MODE) ? 0 : a.n;
-    int32_t beg = __shfl(my_beg, g), len = __shfl(my_len, g);
-    int32_t idx_cur = c < len ? *(a.cols + beg + c) : none;
-    float wgt_cur = 0.0f;
-    if constexpr (VALS)
-        if (c < len) wgt_cur = entry_value<T, MODE>(a, beg + c);
-#pragma unroll 1
-    for (int r0 = 0; r0 < n_rows; r0 += NB) {
-        const int src = r0 + g;      // the row of this lane's group (lanes >= n_rows hold len -1)
-        const int nxt = (src + NB) & 63;
-        const int32_t nbeg = __shfl(my_beg, nxt);
-        const int32_t nlen = r0 + NB < n_rows ? __shfl(my_len, nxt) : -1;
-        const int32_t idx_nxt = c < nlen ? *(a.cols + nbeg + c) : none;
-        float wgt_nxt = 0.0f;
-        if constexpr (VALS)
-            if (c < nlen) wgt_nxt = entry_value<T, MODE>(a, nbeg + c);
-        run_short_rows<T, LOG_G, NARROW, MODE>(a, beg, len, __shfl(my_row, src), __shfl(my_node, src),
-                                                   __shfl(my_s, src), idx_cur, wgt_cur, lane);
-        beg = nbeg;
-        len = nlen;
-        idx_cur = idx_nxt;
-        wgt_cur = wgt_nxt;
-    }
+    const int64_t at = (rb * kWaves + wave) * NB + (lane >> LOG_G);
+    ShortRow row = {0, 0, -1, 0};
+    if (at < h->n_short) row = a.sched.short_rows[at];
+    float s = 0.0f;
+    if (row.len >= 0) s = row_scale<T>(a, row.node, row.len, refuse);
+    run_short_rows<T, LOG_G, NARROW, MODE>(a, row, s, lane);
 }
 
 constexpr int kReduceThreads = 256;
@@ -722,7 +716,7 @@ int32_t launch_layer(LayerArgs<T>& a, int mode, int64_t n, int64_t nnz, hipStrea
     int64_t a_blocks = nnz > kSegLen ? ceil_div(ceil_div(sched_max_slot(n, nnz), kWaves), kXcds) + 1 : 0;
     int64_t b_blocks = nnz > kShortMax ? ceil_div(ceil_div(sched_max_plain(nnz), kWaves), kXcds) + 1 : 0;
     if (b_blocks > kSingleBlocksPerXcd) b_blocks = kSingleBlocksPerXcd;
-    const int64_t c_blocks = ceil_div(ceil_div(n, kWaves * kShortPerWave), kXcds) + 1;
+    const int64_t c_blocks = ceil_div(ceil_div(n, kWaves * (64 >> log_g)), kXcds) + 1;
     a.n = (int32_t)n;
     a.stream_out = streams_out((uint64_t)(n + 1) * (uint64_t)a.F * sizeof(typename T::elem)) ? 1 : 0;
     a.a_blocks = (int32_t)a_blocks;

@@ -58,7 +58,7 @@ size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool wei
     v.max_multi = sched_max_multi(nnz);
     v.max_slot = sched_max_slot(n, nnz);
     v.header = c.take<SchedHeader>(1);
-    v.short_rows = c.take<int32_t>(n > 0 ? n : 1);
+    v.short_rows = c.take<ShortRow>(n > 0 ? n : 1);
     v.multi_row = c.take<int32_t>(v.max_multi);
     v.slot_base = c.take<int32_t>(v.max_multi);
     v.slot_cnt = c.take<int32_t>(v.max_multi);
