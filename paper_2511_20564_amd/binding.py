@@ -1,4 +1,5 @@
-"""ctypes binding of libe2eg.so: same names and argument order as include/e2eg.h.
+"""Binding of libe2eg.so: same names and argument order as include/e2eg.h.  The entry points that run per
+step go through the extension `_native` (csrc/native.cpp), the few others through ctypes.
 
 Pointer arguments accept a torch tensor (its data_ptr() is passed), an int address or None.
 A negative status raises E2egError with the library's message.  Nothing is computed here.
@@ -75,6 +76,7 @@ SIGNATURES = {
 }
 
 _lib = None
+_ext = None
 
 
 class E2egError(RuntimeError):
@@ -99,6 +101,16 @@ def load_library():
     return _lib
 
 
+def _native():
+    """The extension over the hot entry points; like the library it has no substitute."""
+    global _ext
+    if _ext is None:
+        load_library()
+        from . import _native as ext
+        _ext = ext
+    return _ext
+
+
 def _ptr(x):
     if x is None:
         return None
@@ -108,7 +120,7 @@ def _ptr(x):
 
 
 def _nbytes(t):
-    return 0 if t is None else t.numel() * t.element_size()
+    return 0 if t is None else t.nbytes
 
 
 def _check(status: int):
@@ -130,168 +142,161 @@ def e2eg_last_error() -> str:
 
 
 def e2eg_build_csr_workspace_bytes(n_users, n_items, n_edges) -> int:
-    return int(load_library().e2eg_build_csr_workspace_bytes(n_users, n_items, n_edges))
+    return int(_native().e2eg_build_csr_workspace_bytes(n_users, n_items, n_edges))
 
 
 def e2eg_build_csr(n_users, n_items, n_edges, d_user_ids, d_item_ids, flags, d_row_ptr, d_col_idx,
                    col_capacity, ws, ws_bytes=None, stream=0) -> int:
     """-> nnz"""
     nnz = _i64(0)
-    _check(load_library().e2eg_build_csr(n_users, n_items, n_edges, _ptr(d_user_ids), _ptr(d_item_ids), flags,
-                                         _ptr(d_row_ptr), _ptr(d_col_idx), col_capacity, ctypes.byref(nnz),
-                                         _ptr(ws), _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_build_csr(n_users, n_items, n_edges, d_user_ids, d_item_ids, flags, d_row_ptr, d_col_idx,
+                                    col_capacity, ctypes.addressof(nnz), ws,
+                                    _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
     return int(nnz.value)
 
 
 def e2eg_sched_bytes(n, nnz) -> int:
-    return int(load_library().e2eg_sched_bytes(n, nnz))
+    return int(_native().e2eg_sched_bytes(n, nnz))
 
 
 def e2eg_normalize_workspace_bytes(n, nnz) -> int:
-    return int(load_library().e2eg_normalize_workspace_bytes(n, nnz))
+    return int(_native().e2eg_normalize_workspace_bytes(n, nnz))
 
 
 def e2eg_normalize(n, nnz, d_row_ptr, d_col_idx, d_deg, d_dinv_sqrt, d_sched, sched_bytes, ws, ws_bytes=None,
                    stream=0):
-    _check(load_library().e2eg_normalize(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_deg), _ptr(d_dinv_sqrt),
-                                         _ptr(d_sched),
-                                         _nbytes(d_sched) if sched_bytes is None else sched_bytes, _ptr(ws),
-                                         _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_normalize(n, nnz, d_row_ptr, d_col_idx, d_deg, d_dinv_sqrt, d_sched,
+                                    _nbytes(d_sched) if sched_bytes is None else sched_bytes, ws,
+                                    _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_normalize_built(n, nnz, d_row_ptr, d_col_idx, d_val, d_deg, d_deg_w, d_dinv_sqrt, d_sched, sched_bytes, ws,
                          ws_bytes=None, stream=0):
-    _check(load_library().e2eg_normalize_built(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_val), _ptr(d_deg),
-                                               _ptr(d_deg_w), _ptr(d_dinv_sqrt), _ptr(d_sched),
-                                               _nbytes(d_sched) if sched_bytes is None else sched_bytes, _ptr(ws),
-                                               _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_normalize_built(n, nnz, d_row_ptr, d_col_idx, d_val, d_deg, d_deg_w, d_dinv_sqrt, d_sched,
+                                          _nbytes(d_sched) if sched_bytes is None else sched_bytes, ws,
+                                          _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_propagate_workspace_bytes(n, nnz, dtype, F, K) -> int:
-    return int(load_library().e2eg_propagate_workspace_bytes(n, nnz, dtype, F, K))
+    return int(_native().e2eg_propagate_workspace_bytes(n, nnz, dtype, F, K))
 
 
 def e2eg_propagate_fwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_X0, ldx, d_Xout, ldo,
                        layer_stride, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_propagate_fwd(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_dinv_sqrt),
-                                             _ptr(d_sched), dtype, F, K, _ptr(d_X0), ldx, _ptr(d_Xout), ldo,
-                                             layer_stride, _ptr(ws), _nbytes(ws) if ws_bytes is None else ws_bytes,
-                                             stream or None))
+    _check(_native().e2eg_propagate_fwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_X0, ldx,
+                                        d_Xout, ldo, layer_stride, ws, _nbytes(ws) if ws_bytes is None else ws_bytes,
+                                        stream))
 
 
 def e2eg_propagate_bwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_gXK, ldg, d_gLayers,
                        g_layer_stride, d_gX0, ldo, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_propagate_bwd(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_dinv_sqrt),
-                                             _ptr(d_sched), dtype, F, K, _ptr(d_gXK), ldg, _ptr(d_gLayers),
-                                             g_layer_stride, _ptr(d_gX0), ldo, _ptr(ws),
-                                             _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_propagate_bwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_gXK, ldg,
+                                        d_gLayers, g_layer_stride, d_gX0, ldo, ws,
+                                        _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_edge_weights(n_users, n_items, n_edges, d_user_ids, d_item_ids, d_weights, nnz, d_row_ptr, d_col_idx,
                       d_val, stream=0):
-    _check(load_library().e2eg_edge_weights(n_users, n_items, n_edges, _ptr(d_user_ids), _ptr(d_item_ids),
-                                            _ptr(d_weights), nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_val),
-                                            stream or None))
+    _check(_native().e2eg_edge_weights(n_users, n_items, n_edges, d_user_ids, d_item_ids, d_weights, nnz, d_row_ptr,
+                                       d_col_idx, d_val, stream))
 
 
 def e2eg_sched_weighted_bytes(n, nnz) -> int:
-    return int(load_library().e2eg_sched_weighted_bytes(n, nnz))
+    return int(_native().e2eg_sched_weighted_bytes(n, nnz))
 
 
 def e2eg_sched_check_symmetric(d_sched, stream=0):
     """Raises E2egError (INVALID_ARG) if the schedule's structure or values are not symmetric."""
-    _check(load_library().e2eg_sched_check_symmetric(_ptr(d_sched), stream or None))
+    _check(_native().e2eg_sched_check_symmetric(d_sched, stream))
 
 
 def e2eg_normalize_weighted(n, nnz, d_row_ptr, d_col_idx, d_val, d_deg, d_deg_w, d_dinv_sqrt, d_sched, sched_bytes,
                             ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_normalize_weighted(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_val),
-                                                  _ptr(d_deg), _ptr(d_deg_w), _ptr(d_dinv_sqrt), _ptr(d_sched),
-                                                  _nbytes(d_sched) if sched_bytes is None else sched_bytes,
-                                                  _ptr(ws), _nbytes(ws) if ws_bytes is None else ws_bytes,
-                                                  stream or None))
+    _check(_native().e2eg_normalize_weighted(n, nnz, d_row_ptr, d_col_idx, d_val, d_deg, d_deg_w, d_dinv_sqrt,
+                                             d_sched, _nbytes(d_sched) if sched_bytes is None else sched_bytes, ws,
+                                             _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_propagate_weighted_fwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_X0, ldx, d_Xout,
                                 ldo, layer_stride, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_propagate_weighted_fwd(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_dinv_sqrt),
-                                                      _ptr(d_sched), dtype, F, K, _ptr(d_X0), ldx, _ptr(d_Xout),
-                                                      ldo, layer_stride, _ptr(ws),
-                                                      _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_propagate_weighted_fwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K,
+                                                 d_X0, ldx, d_Xout, ldo, layer_stride, ws,
+                                                 _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_propagate_weighted_bwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K, d_gXK, ldg,
                                 d_gLayers, g_layer_stride, d_gX0, ldo, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_propagate_weighted_bwd(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_dinv_sqrt),
-                                                      _ptr(d_sched), dtype, F, K, _ptr(d_gXK), ldg, _ptr(d_gLayers),
-                                                      g_layer_stride, _ptr(d_gX0), ldo, _ptr(ws),
-                                                      _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_propagate_weighted_bwd(n, nnz, d_row_ptr, d_col_idx, d_dinv_sqrt, d_sched, dtype, F, K,
+                                                 d_gXK, ldg, d_gLayers, g_layer_stride, d_gX0, ldo, ws,
+                                                 _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_sampling_weights(nnz, d_val, beta, d_p, stream=0):
-    _check(load_library().e2eg_sampling_weights(nnz, _ptr(d_val), beta, _ptr(d_p), stream or None))
+    _check(_native().e2eg_sampling_weights(nnz, d_val, beta, d_p, stream))
 
 
 def e2eg_sampler_table_bytes(nnz) -> int:
-    return int(load_library().e2eg_sampler_table_bytes(nnz))
+    return int(_native().e2eg_sampler_table_bytes(nnz))
 
 
 def e2eg_sampler_prepare_workspace_bytes(n, nnz) -> int:
-    return int(load_library().e2eg_sampler_prepare_workspace_bytes(n, nnz))
+    return int(_native().e2eg_sampler_prepare_workspace_bytes(n, nnz))
 
 
 def e2eg_sampler_prepare(n, nnz, d_row_ptr, d_col_idx, d_p, d_table, table_bytes, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_sampler_prepare(n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_p), _ptr(d_table),
-                                               _nbytes(d_table) if table_bytes is None else table_bytes, _ptr(ws),
-                                               _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_sampler_prepare(n, nnz, d_row_ptr, d_col_idx, d_p, d_table,
+                                          _nbytes(d_table) if table_bytes is None else table_bytes, ws,
+                                          _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def _fanout_array(fanout):
     return (_i32 * len(fanout))(*[int(k) for k in fanout]) if fanout is not None else None
 
 
+def _addr(array):
+    return None if array is None else ctypes.addressof(array)
+
+
 def e2eg_sample_capacity(n, n_seeds, fanout) -> int:
     """-> the number of draws the fan-outs allow (raises on bad arguments)."""
-    cap = int(load_library().e2eg_sample_capacity(n, n_seeds, len(fanout) if fanout is not None else 0,
-                                                  _fanout_array(fanout)))
+    fan = _fanout_array(fanout)
+    cap = int(_native().e2eg_sample_capacity(n, n_seeds, len(fanout) if fanout is not None else 0, _addr(fan)))
     if cap < 0:
         raise E2egError(E2EG_ERR_INVALID_ARG, e2eg_last_error())
     return cap
 
 
 def e2eg_sample_subgraph_workspace_bytes(n, n_seeds, fanout) -> int:
-    return int(load_library().e2eg_sample_subgraph_workspace_bytes(n, n_seeds, len(fanout), _fanout_array(fanout)))
+    fan = _fanout_array(fanout)
+    return int(_native().e2eg_sample_subgraph_workspace_bytes(n, n_seeds, len(fanout), _addr(fan)))
 
 
 def e2eg_sample_subgraph(n_users, n, nnz, d_row_ptr, d_col_idx, d_table, d_val, n_seeds, d_seeds, fanout, seed, d_nodes,
                          node_capacity, d_edge_users, d_edge_items, d_edge_w, edge_capacity, ws, ws_bytes=None,
                          stream=0):
     """-> (local users, local items, pairs)"""
-    counts = (_i32 * 3)()
-    _check(load_library().e2eg_sample_subgraph(n_users, n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_table),
-                                               _ptr(d_val), n_seeds, _ptr(d_seeds),
-                                               len(fanout) if fanout is not None else 0, _fanout_array(fanout),
-                                               ctypes.c_uint64(seed), _ptr(d_nodes), node_capacity,
-                                               _ptr(d_edge_users), _ptr(d_edge_items), _ptr(d_edge_w), edge_capacity,
-                                               counts, _ptr(ws), _nbytes(ws) if ws_bytes is None else ws_bytes,
-                                               stream or None))
+    counts, fan = (_i32 * 3)(), _fanout_array(fanout)
+    _check(_native().e2eg_sample_subgraph(n_users, n, nnz, d_row_ptr, d_col_idx, d_table, d_val, n_seeds, d_seeds,
+                                          len(fanout) if fanout is not None else 0, _addr(fan),
+                                          seed & 0xffffffffffffffff, d_nodes, node_capacity, d_edge_users,
+                                          d_edge_items, d_edge_w, edge_capacity, ctypes.addressof(counts), ws,
+                                          _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
     return int(counts[0]), int(counts[1]), int(counts[2])
 
 
 def e2eg_layer_transform_workspace_bytes(mode, n, Fin, Fout, dtype) -> int:
-    return int(load_library().e2eg_layer_transform_workspace_bytes(mode, n, Fin, Fout, dtype))
+    return int(_native().e2eg_layer_transform_workspace_bytes(mode, n, Fin, Fout, dtype))
 
 
 def e2eg_layer_transform(mode, n, Fin, Fout, dtype, relu, d_P, d_W, d_H, d_gH, d_gP, d_gW, ws, ws_bytes=None,
                          stream=0):
-    _check(load_library().e2eg_layer_transform(mode, n, Fin, Fout, dtype, relu, _ptr(d_P), _ptr(d_W), _ptr(d_H),
-                                               _ptr(d_gH), _ptr(d_gP), _ptr(d_gW), _ptr(ws),
-                                               _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_layer_transform(mode, n, Fin, Fout, dtype, relu, d_P, d_W, d_H, d_gH, d_gP, d_gW, ws,
+                                          _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_layer_transform_noalloc(mode, n, Fin, Fout, dtype, relu, d_P, d_W, d_H, d_gH, d_gP, d_gW, stream=0):
-    _check(load_library().e2eg_layer_transform_noalloc(mode, n, Fin, Fout, dtype, relu, _ptr(d_P), _ptr(d_W),
-                                                       _ptr(d_H), _ptr(d_gH), _ptr(d_gP), _ptr(d_gW), stream or None))
+    _check(_native().e2eg_layer_transform_noalloc(mode, n, Fin, Fout, dtype, relu, d_P, d_W, d_H, d_gH, d_gP, d_gW,
+                                                  stream))
 
 
 def e2eg_profile_begin(capacity: int):
@@ -311,38 +316,35 @@ def e2eg_profile_copy(d_dst, d_src, nbytes: int, stream=0):
 
 
 def e2eg_readout_mean(n, dtype, F, K, d_X0, ldx, d_layers, ld, layer_stride, d_Y, ldy, stream=0):
-    _check(load_library().e2eg_readout_mean(n, dtype, F, K, _ptr(d_X0), ldx, _ptr(d_layers), ld, layer_stride,
-                                            _ptr(d_Y), ldy, stream or None))
+    _check(_native().e2eg_readout_mean(n, dtype, F, K, d_X0, ldx, d_layers, ld, layer_stride, d_Y, ldy, stream))
 
 
 def e2eg_gfae_loss_workspace_bytes(n, F) -> int:
-    return int(load_library().e2eg_gfae_loss_workspace_bytes(n, F))
+    return int(_native().e2eg_gfae_loss_workspace_bytes(n, F))
 
 
 def e2eg_gfae_loss(n, dtype, F, d_X, ldx, d_Y, ldy, d_loss, d_gY, ldg, grad_scale, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_gfae_loss(n, dtype, F, _ptr(d_X), ldx, _ptr(d_Y), ldy, _ptr(d_loss), _ptr(d_gY), ldg,
-                                         grad_scale, _ptr(ws), _nbytes(ws) if ws_bytes is None else ws_bytes,
-                                         stream or None))
+    _check(_native().e2eg_gfae_loss(n, dtype, F, d_X, ldx, d_Y, ldy, d_loss, d_gY, ldg, grad_scale, ws,
+                                    _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_aggregate_workspace_bytes(n, nnz, dtype, F) -> int:
-    return int(load_library().e2eg_aggregate_workspace_bytes(n, nnz, dtype, F))
+    return int(_native().e2eg_aggregate_workspace_bytes(n, nnz, dtype, F))
 
 
 def e2eg_aggregate(mode, n, nnz, d_row_ptr, d_col_idx, d_sched, dtype, F, d_X, ldx, d_addend, ld_add, d_Y, ldy, ws,
                    ws_bytes=None, stream=0):
-    _check(load_library().e2eg_aggregate(mode, n, nnz, _ptr(d_row_ptr), _ptr(d_col_idx), _ptr(d_sched), dtype, F,
-                                         _ptr(d_X), ldx, _ptr(d_addend), ld_add, _ptr(d_Y), ldy, _ptr(ws),
-                                         _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_aggregate(mode, n, nnz, d_row_ptr, d_col_idx, d_sched, dtype, F, d_X, ldx, d_addend, ld_add,
+                                    d_Y, ldy, ws, _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_block_norms_workspace_bytes(n, F, T) -> int:
-    return int(load_library().e2eg_block_norms_workspace_bytes(n, F, T))
+    return int(_native().e2eg_block_norms_workspace_bytes(n, F, T))
 
 
 def e2eg_block_norms(n, dtype, F, T, d_G, ld, d_norms, ws, ws_bytes=None, stream=0):
-    _check(load_library().e2eg_block_norms(n, dtype, F, T, _ptr(d_G), ld, _ptr(d_norms), _ptr(ws),
-                                           _nbytes(ws) if ws_bytes is None else ws_bytes, stream or None))
+    _check(_native().e2eg_block_norms(n, dtype, F, T, d_G, ld, d_norms, ws,
+                                      _nbytes(ws) if ws_bytes is None else ws_bytes, stream))
 
 
 def e2eg_gradnorm_step(loss, loss0, gnorm, w, gamma=1.0, lr=0.025):

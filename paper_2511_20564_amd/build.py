@@ -1,13 +1,16 @@
-"""Builds libe2eg.so (HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
+"""Builds libe2eg.so (HIP kernels + C ABI) for gfx950 with hipcc, and the extension _native.so that calls it
+from Python with g++, in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libe2eg.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["status.hip", "scan.hip", "sort.hip", "build_csr.hip", "normalize.hip", "propagate.hip", "transform.hip", "readout.hip", "sampler.hip"]
 
 HIPCC_FLAGS = [
@@ -23,19 +26,24 @@ def sources():
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "common.h"), os.path.join(HERE, "..", "include", "e2eg.h")]
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = sources() + [os.path.join(CSRC, f) for f in ("common.h", "radix.h", "native.cpp")]
+    deps.append(os.path.join(HERE, "..", "include", "e2eg.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
 
 def build(verbose: bool = True) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB] + sources()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+    lib = [hipcc] + HIPCC_FLAGS + ["-o", LIB] + sources()
+    native = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+              "-I" + sysconfig.get_paths()["include"], "-o", NATIVE, os.path.join(CSRC, "native.cpp"),
+              "-L" + HERE, "-l:libe2eg.so", "-Wl,-rpath,$ORIGIN"]
+    for cmd in (lib, native):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
     return LIB
 
 

@@ -943,17 +943,18 @@ extern "C" int32_t e2eg_build_csr(int32_t n_users, int32_t n_items, int64_t n_ed
     BucketPlan plan;
     const bool bucketed = plan_buckets(n_users, n_items, n_edges, &plan);
     if (bucketed) {
-        const int32_t st = build_bucketed(w, plan, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
+        int32_t st = build_bucketed(w, plan, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
         if (st != E2EG_OK) return st;
-        E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.buckets.result, sizeof(host_small), hipMemcpyDeviceToHost, stream));
-        E2EG_HIP_TRY(hipStreamSynchronize(stream));
+        if ((st = read_back(w.buckets.result, 3, host_small, stream)) != E2EG_OK) return st;
     }
     if (!bucketed || (host_small[1] == 0 && host_small[2] != 0)) {
-        const int32_t st = build_sorted(w, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
+        int32_t st = build_sorted(w, n_users, n_items, n_edges, d_user_ids, d_item_ids, self, d_row_ptr, d_col_idx, stream);
         if (st != E2EG_OK) return st;
-        if (n_edges > 0)
-            E2EG_HIP_TRY(hipMemcpyAsync(host_small, w.small, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-        E2EG_HIP_TRY(hipStreamSynchronize(stream));
+        if (n_edges > 0) {
+            if ((st = read_back(w.small, 2, host_small, stream)) != E2EG_OK) return st;
+        } else {
+            E2EG_HIP_TRY(hipStreamSynchronize(stream));
+        }
     }
     if (host_small[1] != 0) return fail(E2EG_ERR_BAD_INDEX, "build_csr: a user or item id is out of range");
     *h_nnz_out = 2 * (int64_t)host_small[0] + n * self;

@@ -60,6 +60,11 @@ inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintp
 // unless e2eg_profile_begin() is active on this thread.
 void profile_mark(hipStream_t stream, bool after);
 
+// ---- few results to the host (status.hip) --------------------------------------------------
+// Waits until everything enqueued on `stream` so far is done and copies `count` (at most 8) int32 from d_src
+// to `host`.
+int32_t read_back(const int32_t* d_src, int count, int32_t* host, hipStream_t stream);
+
 // ---- device-wide exclusive scan (scan.hip) -------------------------------------------------
 // out[i] = sum(in[0..i-1]); in == out allowed.  If d_total != nullptr the grand total is stored
 // there.  `ws` needs scan_workspace_bytes(count).  Enqueued on `stream`.

@@ -1723,7 +1723,10 @@ extern "C" size_t e2eg_sched_weighted_bytes(int32_t n, int64_t nnz) {
 
 extern "C" size_t e2eg_normalize_workspace_bytes(int32_t n, int64_t nnz) {
     if (n < 0 || nnz < 0) return 0;
-    return carve_norm(nullptr, n, nnz).bytes;
+    // The size is part of the interface: it has always held two arrays of 8-byte keys per entry, and a caller's
+    // buffer for one size may serve smaller ones.  What is used of it now is less.
+    const size_t used = carve_norm(nullptr, n, nnz).bytes, promised = 16 * (size_t)nnz;
+    return used > promised ? used : promised;
 }
 
 namespace {

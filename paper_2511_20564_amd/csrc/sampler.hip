@@ -670,8 +670,7 @@ extern "C" int32_t e2eg_sample_subgraph(int32_t n_users, int32_t n, int64_t nnz,
     }
     E2EG_LAUNCH_CHECK("emit_edges");
     int32_t host[4] = {0, 0, 0, 0};
-    E2EG_HIP_TRY(hipMemcpyAsync(host, w.small, sizeof(host), hipMemcpyDeviceToHost, stream));
-    E2EG_HIP_TRY(hipStreamSynchronize(stream));  // the one wait: the counts size what the caller does next
+    if ((st = read_back(w.small, 4, host, stream)) != E2EG_OK) return st;  // the one wait: the counts size what the caller does next
     if (host[3] & 1) return fail(E2EG_ERR_BAD_INDEX, "%s: a seed is out of range", who);
     if (host[3] & 2) return fail(E2EG_ERR_BAD_INDEX, "%s: a stored entry joins two users or two items", who);
     h_counts[0] = host[0];

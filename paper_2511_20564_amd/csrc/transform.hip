@@ -411,13 +411,23 @@ __global__ __launch_bounds__(kReduceThreads) void weight_grad_reduce(const float
     }
 }
 
+// Partial matrices the workspace query promises: at most 256, each of a multiple of 64 rows, at least 128.
+int64_t promised_partials(int64_t n) {
+    int64_t rows = ceil_div(ceil_div(n > 0 ? n : 1, 256), 64) * 64;
+    if (rows < 128) rows = 128;
+    return ceil_div(n > 0 ? n : 1, rows);
+}
+
 // Workgroups of dense_backward per group of columns of P, and so partial matrices: one per compute unit, fewer
-// where there are fewer than 128 rows for each.
+// where there are fewer than 128 rows for each, or where only the promised number fits in the static array.
 int32_t back_groups(int32_t n, int32_t fin, int32_t fout) {
     const int64_t column_groups = fout > 128 ? ceil_div(fin, 128) : 1;
     const int64_t most = kTileGroups / column_groups;
     const int64_t want = ceil_div(n > 0 ? n : 1, 128);
-    return (int32_t)(want < most ? want : most);
+    const int64_t groups = want < most ? want : most;
+    const int64_t fit = E2EG_TRANSFORM_STATIC_SCRATCH_BYTES / ((int64_t)fin * fout * (int64_t)sizeof(float));
+    const int64_t promised = promised_partials(n);
+    return (int32_t)(groups > fit && promised <= fit ? promised : groups);
 }
 
 // Streaming stores once the result is far larger than the caches (5 % at 4 M rows); below that the next
@@ -480,7 +490,8 @@ extern "C" size_t e2eg_layer_transform_workspace_bytes(int32_t mode, int32_t n, 
                                                        int32_t Fout, int32_t dtype) {
     if (n < 0 || Fin <= 0 || Fout <= 0 || dtype != E2EG_BF16) return 0;
     if (mode != E2EG_TRANSFORM_BWD) return kAlign;
-    const int64_t blocks = back_groups(n, Fin, Fout);
+    const int64_t used = back_groups(n, Fin, Fout), promised = promised_partials(n);
+    const int64_t blocks = used > promised ? used : promised;
     return align_up((size_t)blocks * (size_t)Fin * (size_t)Fout * sizeof(float));
 }
 

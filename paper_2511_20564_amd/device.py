@@ -10,14 +10,23 @@ import torch
 from . import binding as B
 
 
+_ready = False
+
+
 def _require_gpu():
+    global _ready
+    if _ready:
+        return
     if not torch.cuda.is_available():
         raise RuntimeError("paper_2511_20564_amd needs a GPU: there is no CPU implementation")
     B.load_library()
+    torch.cuda.init()
+    _ready = True
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle: torch.cuda.current_stream() makes an object of it, 1.5 us a call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _bytes(nbytes: int, device) -> torch.Tensor:
