@@ -162,7 +162,6 @@ constexpr int32_t kSchedValuesNotSymmetric = 2;
 struct SchedView {
     SchedHeader* header;
     int32_t* orig;        // [n] node at internal position p (small form: null, p itself)
-    int32_t* zpos;        // [n] internal position of node i (small form: null)
     int32_t* zrow_ptr;    // [n + 1] row pointers of the internal CSR (small form: the caller's)
     int32_t* zcol;        // [nnz] internal column ids; in each row the popular ones first, by popularity, then
                           // the others in the caller's order (small form: the same array as znode)

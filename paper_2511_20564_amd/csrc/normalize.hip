@@ -244,11 +244,16 @@ __global__ __launch_bounds__(kTileThreads) void count_top(const int32_t* __restr
     }
 }
 
-constexpr uint16_t kNotTop = 0xffff;
+// What the entry passes need of a column, in one 8-byte gather (two gathers, of position and scale, made
+// order_rows 983 us on 101 M entries, 58 M of them in its rows).
+struct alignas(8) NodeInfo {
+    int32_t pos;   // large form: internal position (below kTopNodes: the rank of a popular node); small: rank, or kTopNodes
+    float dinv;    // d~^-1/2
+};
 struct TopOut {
     int32_t* node;      // [kTopNodes] the popular nodes in node order
     int32_t* deg;       // [kTopNodes] and their degrees
-    uint16_t* rank;     // [n] small form: rank of a popular node (set by rank_top), kNotTop elsewhere
+    NodeInfo* info;     // [n]
     int32_t* zdeg;      // [n] large form: row lengths by internal row
     uint64_t* is_top;   // large form: a bit per node
 };
@@ -256,7 +261,8 @@ struct TopOut {
 // One tile of nodes; before[0], before[1]: nodes above the threshold class and in it in earlier tiles.
 // Large form: internal positions of the nodes that are not popular (behind the popular ones, in node order).
 template <bool SMALL>
-__device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr, int64_t n, const Threshold th,
+__device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr, const float* __restrict__ dinv_sqrt,
+                                            int64_t n, const Threshold th,
                                             int32_t (&before)[2], const SchedView& s, const TopOut& out,
                                             int32_t (*red)[2]) {
     const int32_t room = kTopNodes - th.above;   // popular nodes of the threshold class
@@ -302,11 +308,11 @@ __device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr,
                 out.node[top_before] = (int32_t)i;
                 out.deg[top_before] = d[r];
             } else if (SMALL) {
-                out.rank[i] = kNotTop;
+                out.info[i] = NodeInfo{kTopNodes, dinv_sqrt[i]};
             } else {
                 const int32_t p = n_top + (int32_t)i - top_before;
                 s.orig[p] = (int32_t)i;
-                s.zpos[i] = p;
+                out.info[i] = NodeInfo{p, dinv_sqrt[i]};
                 out.zdeg[p] = d[r];
             }
         }
@@ -316,7 +322,8 @@ __device__ __forceinline__ void number_tile(const int32_t* __restrict__ row_ptr,
 }
 
 template <bool SMALL, int OCT>
-__global__ __launch_bounds__(kTileThreads) void number_nodes(const int32_t* __restrict__ row_ptr, int64_t n,
+__global__ __launch_bounds__(kTileThreads) void number_nodes(const int32_t* __restrict__ row_ptr,
+                                                             const float* __restrict__ dinv_sqrt, int64_t n,
                                                              const int32_t* __restrict__ classes,
                                                              const int32_t* __restrict__ top_totals, SchedView s, TopOut out) {
     __shared__ int32_t red[kTileWaves][2];
@@ -328,7 +335,7 @@ __global__ __launch_bounds__(kTileThreads) void number_nodes(const int32_t* __re
         before[1] += top_totals[2 * t + 1];
     }
     block_sums<2>(before, red);
-    number_tile<SMALL>(row_ptr, n, th, before, s, out, red);
+    number_tile<SMALL>(row_ptr, dinv_sqrt, n, th, before, s, out, red);
 }
 
 // A popular node's rank is the number of popular nodes of larger degree, or of equal degree and before it:
@@ -336,7 +343,7 @@ __global__ __launch_bounds__(kTileThreads) void number_nodes(const int32_t* __re
 constexpr int kRankLanes = 16;
 constexpr int kRankThreads = 512;
 template <bool SMALL>
-__global__ __launch_bounds__(kRankThreads) void rank_top(int32_t n_top, SchedView s, TopOut out) {
+__global__ __launch_bounds__(kRankThreads) void rank_top(int32_t n_top, const float* __restrict__ dinv_sqrt, SchedView s, TopOut out) {
     __shared__ __attribute__((aligned(16))) int32_t deg[kTopNodes];
     constexpr int kLoads = kTopNodes / 4 / kRankThreads;
 #pragma unroll
@@ -371,11 +378,9 @@ __global__ __launch_bounds__(kRankThreads) void rank_top(int32_t n_top, SchedVie
     for (int off = kRankLanes / 2; off > 0; off >>= 1) rank += __shfl_xor(rank, off);
     if (c < n_top && threadIdx.x % kRankLanes == 0) {
         const int32_t i = out.node[c];
-        if (SMALL) {
-            out.rank[i] = (uint16_t)rank;
-        } else {
+        out.info[i] = NodeInfo{rank, dinv_sqrt[i]};
+        if (!SMALL) {
             s.orig[rank] = i;
-            s.zpos[i] = rank;
             out.zdeg[rank] = d;
         }
     }
@@ -397,7 +402,8 @@ struct Chunks {
 // ordered by window once the columns are in place.  The last workgroup writes the header.
 template <bool SMALL, bool NUMBER>
 __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restrict__ row_ptr,
-                                                          const int32_t* __restrict__ zdeg, int64_t n, int64_t nnz,
+                                                          const int32_t* __restrict__ zdeg,
+                                                          const float* __restrict__ dinv_sqrt, int64_t n, int64_t nnz,
                                                           int32_t wide_rows, int32_t wide_min,
                                                           const int32_t* __restrict__ totals, SchedView s,
                                                           Segment* __restrict__ seg_out, Chunks chunks,
@@ -663,7 +669,7 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
             counts[1] += c == th.cls ? class_before[c] : 0;
         }
         block_sums<2>(counts, red2);
-        number_tile<true>(row_ptr, n, th, counts, s, out, red2);
+        number_tile<true>(row_ptr, dinv_sqrt, n, th, counts, s, out, red2);
     }
 }
 
@@ -753,8 +759,7 @@ constexpr int kSmallTile = 1024;
 constexpr int kSmallRounds = (kSmallTile + kShortMax + kThreads - 1) / kThreads;
 __global__ __launch_bounds__(kThreads) void order_small(const int32_t* __restrict__ row_ptr,
                                                         const int32_t* __restrict__ col, const float* __restrict__ val,
-                                                        const float* __restrict__ dinv_sqrt,
-                                                        const uint16_t* __restrict__ top_rank, int64_t n, int64_t nnz,
+                                                        const NodeInfo* __restrict__ info, int64_t n, int64_t nnz,
                                                         int tile, int64_t tile_blocks, SchedView s) {
     __shared__ int32_t rows[kTileRowsMax + 1];
     __shared__ int32_t keys[kSmallRounds * kThreads];
@@ -786,9 +791,9 @@ __global__ __launch_bounds__(kThreads) void order_small(const int32_t* __restric
                 const int32_t x = r * kThreads + (int32_t)threadIdx.x;
                 di[r] = 0.0f;
                 if (j[r] >= 0) {
-                    const uint16_t t = top_rank[j[r]];
-                    di[r] = dinv_sqrt[j[r]];
-                    keys[x] = t == kNotTop ? kTopNodes + x : (int32_t)t;
+                    const NodeInfo t = info[j[r]];
+                    di[r] = t.dinv;
+                    keys[x] = t.pos == kTopNodes ? kTopNodes + x : t.pos;
                 }
             }
             __syncthreads();
@@ -823,8 +828,8 @@ __global__ __launch_bounds__(kThreads) void order_small(const int32_t* __restric
         int32_t tops = 0;
 #pragma unroll 8
         for (int32_t idx = threadIdx.x; idx < L; idx += kThreads) {
-            const uint16_t r = top_rank[col[b + idx]];
-            if (r != kNotTop) {
+            const int32_t r = info[col[b + idx]].pos;
+            if (r != kTopNodes) {
                 map.set(r);
                 ++tops;
             }
@@ -851,9 +856,9 @@ __global__ __launch_bounds__(kThreads) void order_small(const int32_t* __restric
             uint64_t bal[kRounds];
 #pragma unroll
             for (int r = 0; r < kRounds; ++r) {
-                const uint16_t t = j[r] >= 0 ? top_rank[j[r]] : kNotTop;
-                di[r] = j[r] >= 0 ? dinv_sqrt[j[r]] : 0.0f;
-                rank[r] = t == kNotTop ? -1 : (int32_t)t;
+                const NodeInfo t = j[r] >= 0 ? info[j[r]] : NodeInfo{kTopNodes, 0.0f};
+                di[r] = t.dinv;
+                rank[r] = t.pos == kTopNodes ? -1 : t.pos;
                 bal[r] = __ballot(rank[r] >= 0);
                 if (lane == 0) round_tops[r][wave] = __popcll(bal[r]);
             }
@@ -925,7 +930,7 @@ __device__ __forceinline__ void order_row(const SchedView& s, TopBitmap& map, in
 
 __global__ __launch_bounds__(kThreads) void order_rows(const int32_t* __restrict__ row_ptr,
                                                        const int32_t* __restrict__ col, const float* __restrict__ val,
-                                                       const float* __restrict__ dinv_sqrt, int64_t n, SchedView s) {
+                                                       const NodeInfo* __restrict__ info, int64_t n, SchedView s) {
     __shared__ TopBitmap maps[kOrderWaves];
     constexpr int kShortRounds = kShortMax / 64;
     constexpr int kLongRounds = kSegLen / 64;
@@ -935,7 +940,7 @@ __global__ __launch_bounds__(kThreads) void order_rows(const int32_t* __restrict
     const int q0 = lane < kRowsPerWave && row0 + lane < n ? lane : 0;
     const int32_t my_beg = row_ptr[row0 + q0];
     int32_t my_len = row_ptr[row0 + q0 + 1] - my_beg;
-    const int32_t my_dest = s.zrow_ptr[s.zpos[row0 + q0]];
+    const int32_t my_dest = s.zrow_ptr[info[row0 + q0].pos];
     if (row0 + lane >= n) my_len = 0;
     int32_t beg[kRowsPerWave], len[kRowsPerWave], dest[kRowsPerWave];
 #pragma unroll
@@ -964,8 +969,9 @@ __global__ __launch_bounds__(kThreads) void order_rows(const int32_t* __restrict
                 pos[q][r] = 0;
                 dinv[q][r] = 0.0f;
                 if (node[q][r] >= 0) {
-                    pos[q][r] = s.zpos[node[q][r]];
-                    dinv[q][r] = dinv_sqrt[node[q][r]];
+                    const NodeInfo t = info[node[q][r]];
+                    pos[q][r] = t.pos;
+                    dinv[q][r] = t.dinv;
                 }
             }
 #pragma unroll
@@ -990,8 +996,9 @@ __global__ __launch_bounds__(kThreads) void order_rows(const int32_t* __restrict
             pos[r] = 0;
             dinv[r] = 0.0f;
             if (node[r] >= 0) {
-                pos[r] = s.zpos[node[r]];
-                dinv[r] = dinv_sqrt[node[r]];
+                const NodeInfo t = info[node[r]];
+                pos[r] = t.pos;
+                dinv[r] = t.dinv;
             }
         }
         order_row<kLongRounds>(s, map, lane, __builtin_amdgcn_readlane(my_dest, q), node, pos, dinv, v);
@@ -1036,7 +1043,7 @@ __global__ __launch_bounds__(kThreads) void count_chunks(const int32_t* __restri
 
 __global__ __launch_bounds__(kThreads) void place_chunks(const int32_t* __restrict__ row_ptr,
                                                          const int32_t* __restrict__ col, const float* __restrict__ val,
-                                                         const float* __restrict__ dinv_sqrt, SchedView s, Chunks chunks) {
+                                                         const NodeInfo* __restrict__ info, SchedView s, Chunks chunks) {
     __shared__ int32_t red[kThreads / 64][2];
     __shared__ int32_t round_tops[kChunkRounds][kThreads / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1062,8 +1069,9 @@ __global__ __launch_bounds__(kThreads) void place_chunks(const int32_t* __restri
             pos[r] = kTopNodes;
             di[r] = 0.0f;
             if (j[r] >= 0) {
-                pos[r] = s.zpos[j[r]];
-                di[r] = dinv_sqrt[j[r]];
+                const NodeInfo t = info[j[r]];
+                pos[r] = t.pos;
+                di[r] = t.dinv;
             }
         }
         // the row's popular entries in pieces before this one, and in all
@@ -1286,11 +1294,13 @@ constexpr int kDegLanes = 16;
 __global__ __launch_bounds__(kThreads) void weighted_degrees(const int32_t* __restrict__ row_ptr,
                                                              const float* __restrict__ val, int64_t n, int64_t short_blocks,
                                                              SchedView s, float* __restrict__ deg_w,
-                                                             float* __restrict__ dinv_sqrt) {
+                                                             float* __restrict__ dinv_sqrt, NodeInfo* __restrict__ info) {
     __shared__ double red[kThreads];
     auto finish = [&](int64_t row, double sum) {
         if (deg_w) deg_w[row] = (float)sum;
-        dinv_sqrt[row] = sum > 0.0 ? (float)(1.0 / sqrt(sum)) : 0.0f;
+        const float dinv = sum > 0.0 ? (float)(1.0 / sqrt(sum)) : 0.0f;
+        dinv_sqrt[row] = dinv;
+        info[row].dinv = dinv;   // over the one of the row's length
     };
     if ((int64_t)blockIdx.x < short_blocks) {
         const int64_t row = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kDegLanes;
@@ -1557,8 +1567,8 @@ NormWs carve_norm(void* base, int64_t n, int64_t nnz) {
     w.top_totals = c.take<int32_t>(2 * tiles);
     w.top.node = c.take<int32_t>(kTopNodes);
     w.top.deg = c.take<int32_t>(kTopNodes);
+    w.top.info = c.take<NodeInfo>(n > 0 ? n : 1);
     if (sched_is_small(nnz)) {
-        w.top.rank = c.take<uint16_t>(n > 0 ? n : 1);
         if (tiles <= kFewTiles) w.tile_classes = c.take<int32_t>(tiles * kClasses<kSmallOct>);
     } else {
         const int64_t wide = sched_max_wide_rows(n, nnz), nwin = sched_windows(n), slots = sched_max_slot(n, nnz);
@@ -1583,11 +1593,11 @@ NormWs carve_norm(void* base, int64_t n, int64_t nnz) {
 }
 
 int32_t run_weighted_degrees(int64_t n, int64_t nnz, const int32_t* row_ptr, const float* val, const SchedView& view,
-                             float* deg_w, float* dinv, hipStream_t stream) {
+                             float* deg_w, float* dinv, NodeInfo* info, hipStream_t stream) {
     const int64_t short_blocks = ceil_div(n * kDegLanes, kThreads);
     const int64_t split = nnz <= kSegLen ? 0 : view.max_multi < kDegBlocks ? view.max_multi : kDegBlocks;
     weighted_degrees<<<dim3((unsigned)(short_blocks + split)), dim3(kThreads), 0, stream>>>(row_ptr, val, n, short_blocks,
-                                                                                          view, deg_w, dinv);
+                                                                                          view, deg_w, dinv, info);
     E2EG_LAUNCH_CHECK("weighted_degrees");
     return E2EG_OK;
 }
@@ -1598,7 +1608,7 @@ int32_t normalize_small(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
     if (w.tile_classes) {
         row_stats<true, true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, deg, dinv, w.totals, w.tile_classes);
         E2EG_LAUNCH_CHECK("row_stats");
-        emit_rows<true, true><<<tiles, tile_blk, 0, stream>>>(row_ptr, nullptr, n, nnz, 0, 0, w.totals, view, view.segs,
+        emit_rows<true, true><<<tiles, tile_blk, 0, stream>>>(row_ptr, nullptr, dinv, n, nnz, 0, 0, w.totals, view, view.segs,
                                                              w.chunks, w.tile_classes, w.top);
         E2EG_LAUNCH_CHECK("emit_rows");
     } else {
@@ -1606,28 +1616,28 @@ int32_t normalize_small(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
         E2EG_LAUNCH_CHECK("fill_words");
         row_stats<true, false, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, deg, dinv, w.totals, w.zeroed);
         E2EG_LAUNCH_CHECK("row_stats");
-        emit_rows<true, false><<<tiles, tile_blk, 0, stream>>>(row_ptr, nullptr, n, nnz, 0, 0, w.totals, view, view.segs,
+        emit_rows<true, false><<<tiles, tile_blk, 0, stream>>>(row_ptr, nullptr, nullptr, n, nnz, 0, 0, w.totals, view, view.segs,
                                                               w.chunks, nullptr, w.top);
         E2EG_LAUNCH_CHECK("emit_rows");
         count_top<true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, w.zeroed, w.top_totals);
         E2EG_LAUNCH_CHECK("count_top");
-        number_nodes<true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, w.zeroed, w.top_totals, view, w.top);
+        number_nodes<true, kSmallOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, dinv, n, w.zeroed, w.top_totals, view, w.top);
         E2EG_LAUNCH_CHECK("number_nodes");
     }
     if (val && n > 0) {
-        const int32_t st = run_weighted_degrees(n, nnz, row_ptr, val, view, deg_w, dinv, stream);
+        const int32_t st = run_weighted_degrees(n, nnz, row_ptr, val, view, deg_w, dinv, w.top.info, stream);
         if (st != E2EG_OK) return st;
     }
     if (nnz == 0) return E2EG_OK;
     const int32_t n_top = n < kTopNodes ? n : kTopNodes;
-    rank_top<true><<<dim3((unsigned)ceil_div(n_top, kRankThreads / kRankLanes)), dim3(kRankThreads), 0, stream>>>(n_top, view, w.top);
+    rank_top<true><<<dim3((unsigned)ceil_div(n_top, kRankThreads / kRankLanes)), dim3(kRankThreads), 0, stream>>>(n_top, dinv, view, w.top);
     E2EG_LAUNCH_CHECK("rank_top");
     // tiles small enough that the pass has a workgroup for every compute unit
     int tile = kSmallTile;
     while (tile > kThreads && ceil_div(nnz, tile) < 512) tile /= 2;
     const int64_t tile_blocks = ceil_div(nnz, tile);
     const int64_t long_blocks = nnz <= kShortMax ? 0 : view.max_plain < 1024 ? view.max_plain : 1024;
-    order_small<<<dim3((unsigned)(tile_blocks + long_blocks)), blk, 0, stream>>>(row_ptr, col, val, dinv, w.top.rank, n, nnz,
+    order_small<<<dim3((unsigned)(tile_blocks + long_blocks)), blk, 0, stream>>>(row_ptr, col, val, w.top.info, n, nnz,
                                                                               tile, tile_blocks, view);
     E2EG_LAUNCH_CHECK("order_small");
     if (test) {
@@ -1655,30 +1665,30 @@ int32_t normalize_large(int32_t n, int64_t nnz, const int32_t* row_ptr, const in
     E2EG_LAUNCH_CHECK("row_stats");
     count_top<false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, classes, w.top_totals);
     E2EG_LAUNCH_CHECK("count_top");
-    number_nodes<false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, n, classes, w.top_totals, view, w.top);
+    number_nodes<false, kLargeOct><<<tiles, tile_blk, 0, stream>>>(row_ptr, dinv, n, classes, w.top_totals, view, w.top);
     E2EG_LAUNCH_CHECK("number_nodes");
     const int32_t n_top = n < kTopNodes ? n : kTopNodes;
-    rank_top<false><<<dim3((unsigned)ceil_div(n_top, kRankThreads / kRankLanes)), dim3(kRankThreads), 0, stream>>>(n_top, view, w.top);
+    rank_top<false><<<dim3((unsigned)ceil_div(n_top, kRankThreads / kRankLanes)), dim3(kRankThreads), 0, stream>>>(n_top, dinv, view, w.top);
     E2EG_LAUNCH_CHECK("rank_top");
 
     // 2. row pointers and work lists
     row_totals<<<tiles, tile_blk, 0, stream>>>(w.top.zdeg, n, wide_rows, wide_min, w.totals);
     E2EG_LAUNCH_CHECK("row_totals");
-    emit_rows<false, false><<<tiles, tile_blk, 0, stream>>>(nullptr, w.top.zdeg, n, nnz, wide_rows, wide_min, w.totals, view,
+    emit_rows<false, false><<<tiles, tile_blk, 0, stream>>>(nullptr, w.top.zdeg, nullptr, n, nnz, wide_rows, wide_min, w.totals, view,
                                                            w.seg_tmp, w.chunks, nullptr, w.top);
     E2EG_LAUNCH_CHECK("emit_rows");
     if (val) {
-        const int32_t st = run_weighted_degrees(n, nnz, row_ptr, val, view, deg_w, dinv, stream);
+        const int32_t st = run_weighted_degrees(n, nnz, row_ptr, val, view, deg_w, dinv, w.top.info, stream);
         if (st != E2EG_OK) return st;
     }
 
     // 3. the CSR in internal ids, and the symmetry test
-    order_rows<<<dim3((unsigned)ceil_div(n, kOrderWaves * kRowsPerWave)), blk, 0, stream>>>(row_ptr, col, val, dinv, n, view);
+    order_rows<<<dim3((unsigned)ceil_div(n, kOrderWaves * kRowsPerWave)), blk, 0, stream>>>(row_ptr, col, val, w.top.info, n, view);
     E2EG_LAUNCH_CHECK("order_rows");
     const dim3 chunk_blocks((unsigned)(w.chunks.max_chunks < kChunkBlocks ? w.chunks.max_chunks : kChunkBlocks));
     count_chunks<<<chunk_blocks, blk, 0, stream>>>(row_ptr, col, w.top.is_top, view, w.chunks);
     E2EG_LAUNCH_CHECK("count_chunks");
-    place_chunks<<<chunk_blocks, blk, 0, stream>>>(row_ptr, col, val, dinv, view, w.chunks);
+    place_chunks<<<chunk_blocks, blk, 0, stream>>>(row_ptr, col, val, w.top.info, view, w.chunks);
     E2EG_LAUNCH_CHECK("place_chunks");
     const int64_t split_blocks = view.max_multi < 4096 ? view.max_multi : 4096;
     order_split_rows<<<dim3((unsigned)split_blocks), dim3(kSplitThreads), 0, stream>>>(view);

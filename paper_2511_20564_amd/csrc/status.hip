@@ -144,12 +144,11 @@ size_t sched_carve(void* base, int64_t n, int64_t nnz, SchedView* view, bool wei
     v.znode = c.take<int32_t>(entries);
     v.zs = c.take<float>(entries);
     if (small) {
-        v.orig = v.zpos = nullptr;
+        v.orig = nullptr;
         v.zrow_ptr = const_cast<int32_t*>(row_ptr);
         v.zcol = v.znode;
     } else {
         v.orig = c.take<int32_t>(n > 0 ? n : 1);
-        v.zpos = c.take<int32_t>(n > 0 ? n : 1);
         v.zrow_ptr = c.take<int32_t>(n + 1);
         v.zcol = c.take<int32_t>(entries);
     }
