@@ -41,13 +41,16 @@ struct PairsIn {
     __device__ __forceinline__ bool ok(int32_t u, int32_t i) const {
         return (uint32_t)u < (uint32_t)n_users && (uint32_t)i < (uint32_t)n_items;
     }
-    __device__ __forceinline__ uint64_t load(int64_t e) const {
-        const int32_t u = users[e], i = items[e];
-        return ok(u, i) ? ((uint64_t)(uint32_t)u << item_bits) | (uint32_t)i : 0ull;
+    struct raw {
+        int32_t user, item;
+    };
+    __device__ __forceinline__ raw load(int64_t e) const { return raw{users[e], items[e]}; }
+    __device__ __forceinline__ raw none() const { return raw{0, 0}; }
+    __device__ __forceinline__ bool ok(raw r) const { return ok(r.user, r.item); }
+    __device__ __forceinline__ uint64_t key(raw r) const {
+        return ok(r) ? ((uint64_t)(uint32_t)r.user << item_bits) | (uint32_t)r.item : 0ull;
     }
-    __device__ __forceinline__ void check(int64_t e) const {
-        if (!ok(users[e], items[e])) atomicOr(bad, 1);
-    }
+    __device__ __forceinline__ void report() const { atomicOr(bad, 1); }
 };
 
 // Sorted (item, user) keys -> item rows: key k of the list lands behind the user rows and the earlier
@@ -359,15 +362,7 @@ __device__ __forceinline__ int32_t scan_block(int32_t v, int32_t* lds, int32_t* 
 // Ranks of a wavefront's keys by digit, in input order: the running per-wavefront counts are in `cnt`.
 template <int BITS>
 __device__ __forceinline__ int rank_digit(int d, bool valid, int nbits, uint64_t lt_mask, uint16_t* cnt) {
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < BITS; ++b) {
-        if (b < nbits) {
-            const bool bit = (d >> b) & 1;
-            const uint64_t bal = __ballot(valid && bit);
-            peers &= bit ? bal : ~bal;
-        }
-    }
+    const uint64_t peers = lanes_of_digit<BITS>(d, nbits, __ballot(valid));
     const int below = __popcll(peers & lt_mask);
     const int pre = cnt[d];
     if (valid && below == 0) cnt[d] = (uint16_t)(pre + __popcll(peers));

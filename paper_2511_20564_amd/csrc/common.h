@@ -60,6 +60,25 @@ inline bool aligned_to(const void* p, size_t a) { return (reinterpret_cast<uintp
 // unless e2eg_profile_begin() is active on this thread.
 void profile_mark(hipStream_t stream, bool after);
 
+// ---- lanes of equal digit --------------------------------------------------------------------
+// The lanes of a wavefront among `valid` (a ballot) whose digit d (nbits bits, at most BITS) equals the
+// caller's.  Four instructions a bit: the bit spread to a mask, the ballot, and peers & ~(ballot ^ mask) for
+// each half (with a select between the ballot and its complement: seven).
+template <int BITS>
+__device__ __forceinline__ uint64_t lanes_of_digit(int d, int nbits, uint64_t valid) {
+    uint32_t lo = (uint32_t)valid, hi = (uint32_t)(valid >> 32);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        if (b < nbits) {
+            const uint32_t mask = (uint32_t)((int32_t)((uint32_t)d << (31 - b)) >> 31);
+            const uint64_t bal = __ballot(mask != 0);
+            lo &= ~((uint32_t)bal ^ mask);
+            hi &= ~((uint32_t)(bal >> 32) ^ mask);
+        }
+    }
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // ---- few results to the host (status.hip) --------------------------------------------------
 // Waits until everything enqueued on `stream` so far is done and copies `count` (at most 8) int32 from d_src
 // to `host`.

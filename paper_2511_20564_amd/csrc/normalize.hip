@@ -455,13 +455,7 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
         len[r] = d;
         const int g = !valid ? kDigits - 1 : d <= kShortMax ? d : d <= kSegLen ? kShortMax + 1 : kShortMax + 2;
         digit[r] = g;
-        uint64_t peers = ~0ull;
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (g >> b) & 1;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
-        }
+        const uint64_t peers = lanes_of_digit<8>(g, 8, ~0ull);
         const int pre = wave_cnt[wave][g];
         const int below = __popcll(peers & lt_mask);
         rank[r] = pre + below;

@@ -27,8 +27,12 @@ constexpr int kFusedTiles = 64;   // up to this many tiles the scatter adds up i
 
 struct KeysIn {
     const uint64_t* keys;
-    __device__ __forceinline__ uint64_t load(int64_t i) const { return keys[i]; }
-    __device__ __forceinline__ void check(int64_t) const {}
+    using raw = uint64_t;   // what is loaded, and the key of it
+    __device__ __forceinline__ raw load(int64_t i) const { return keys[i]; }
+    __device__ __forceinline__ raw none() const { return 0ull; }
+    __device__ __forceinline__ uint64_t key(raw r) const { return r; }
+    __device__ __forceinline__ bool ok(raw) const { return true; }
+    __device__ __forceinline__ void report() const {}
 };
 struct KeysOut {
     static constexpr bool kRuns = false;
@@ -50,20 +54,22 @@ __global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, int64_t cou
     if (d_count) count = *d_count;
     const int64_t base = (int64_t)blockIdx.x * S::kTile;
     int* mine = h[(threadIdx.x >> 6) % S::kCopies];
-    uint64_t key[S::kItems];
+    typename In::raw raw[S::kItems];
 #pragma unroll
     for (int k = 0; k < S::kItems; ++k) {
         const int64_t i = base + k * S::kThreads + threadIdx.x;
-        key[k] = i < count ? in.load(i) : 0ull;
+        raw[k] = i < count ? in.load(i) : in.none();
     }
+    bool ok = true;
 #pragma unroll
     for (int k = 0; k < S::kItems; ++k) {
         const int64_t i = base + k * S::kThreads + threadIdx.x;
         if (i < count) {
-            in.check(i);
-            atomicAdd(&mine[(int)(key[k] >> shift) & (bins - 1)], 1);
+            ok = ok && in.ok(raw[k]);
+            atomicAdd(&mine[(int)(in.key(raw[k]) >> shift) & (bins - 1)], 1);
         }
     }
+    if (!ok) in.report();
     __syncthreads();
     for (int d = threadIdx.x; d < bins; d += S::kThreads) {
         int t = 0;
@@ -102,10 +108,15 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
     const int64_t chunk = tile_base + (int64_t)wave * (64 * S::kItems);
     uint64_t key[S::kItems];
     uint16_t rank[S::kItems];
+    {
+        typename In::raw raw[S::kItems];
 #pragma unroll
-    for (int r = 0; r < S::kItems; ++r) {
-        const int64_t i = chunk + r * 64 + lane;
-        key[r] = i < count ? in.load(i) : 0ull;
+        for (int r = 0; r < S::kItems; ++r) {
+            const int64_t i = chunk + r * 64 + lane;
+            raw[r] = i < count ? in.load(i) : in.none();
+        }
+#pragma unroll
+        for (int r = 0; r < S::kItems; ++r) key[r] = in.key(raw[r]);
     }
     for (int k = threadIdx.x; k < kWaves * kBins / 2; k += S::kThreads) reinterpret_cast<uint32_t*>(&wave_cnt[0][0])[k] = 0;
     __syncthreads();
@@ -113,15 +124,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
     for (int r = 0; r < S::kItems; ++r) {
         const bool valid = chunk + r * 64 + lane < count;
         const int d = (int)(key[r] >> shift) & (bins - 1);
-        uint64_t peers = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < S::kBits; ++b) {
-            if (b < nbits) {
-                const bool bit = (d >> b) & 1;
-                const uint64_t bal = __ballot(valid && bit);
-                peers &= bit ? bal : ~bal;
-            }
-        }
+        const uint64_t peers = lanes_of_digit<S::kBits>(d, nbits, __ballot(valid));
         const int pre = wave_cnt[wave][d];
         const int below = __popcll(peers & lt_mask);
         rank[r] = (uint16_t)(pre + below);
