@@ -11,7 +11,7 @@
 //   4. row_ptr from a prefix sum of the counts, the diagonal beside it.
 // The number of distinct pairs is known on the device only; launches are sized by the number of pairs
 // given, and the host waits once, at the end.
-// Bound by HBM for large graphs (8 sort passes of 16 bytes read and 8 written per pair).
+// Large graphs: the same steps with 32-bit keys where the ids allow it ("long lists" below).
 // Small graphs are bound by the number of launches (17 of the above) and take another way, "buckets" below:
 // five launches.
 #include "radix.h"
@@ -41,32 +41,73 @@ struct PairsIn {
     __device__ __forceinline__ bool ok(int32_t u, int32_t i) const {
         return (uint32_t)u < (uint32_t)n_users && (uint32_t)i < (uint32_t)n_items;
     }
+    using Key = uint64_t;
     struct raw {
         int32_t user, item;
     };
-    __device__ __forceinline__ raw load(int64_t e) const { return raw{users[e], items[e]}; }
+    __device__ __forceinline__ PairsIn from(int64_t base) const {
+        return PairsIn{users + base, items + base, n_users, n_items, item_bits, bad};
+    }
+    __device__ __forceinline__ raw load(uint32_t e) const { return raw{users[e], items[e]}; }
     __device__ __forceinline__ raw none() const { return raw{0, 0}; }
     __device__ __forceinline__ bool ok(raw r) const { return ok(r.user, r.item); }
     __device__ __forceinline__ uint64_t key(raw r) const {
-        return ok(r) ? ((uint64_t)(uint32_t)r.user << item_bits) | (uint32_t)r.item : 0ull;
+        const uint32_t u = (uint32_t)r.user < (uint32_t)n_users ? (uint32_t)r.user : 0u;
+        const uint32_t i = (uint32_t)r.item < (uint32_t)n_items ? (uint32_t)r.item : 0u;
+        return ((uint64_t)u << item_bits) | i;
     }
     __device__ __forceinline__ void report() const { atomicOr(bad, 1); }
+};
+
+// Their users alone, for digits of the user.
+struct UsersIn {
+    const int32_t* users;
+    int32_t n_users;
+    int item_bits;
+    using Key = uint64_t;
+    using raw = int32_t;
+    __device__ __forceinline__ UsersIn from(int64_t base) const { return UsersIn{users + base, n_users, item_bits}; }
+    __device__ __forceinline__ raw load(uint32_t e) const { return users[e]; }
+    __device__ __forceinline__ raw none() const { return 0; }
+    __device__ __forceinline__ bool ok(raw) const { return true; }
+    __device__ __forceinline__ uint64_t key(raw r) const {
+        return (uint64_t)((uint32_t)r < (uint32_t)n_users ? (uint32_t)r : 0u) << item_bits;
+    }
+    __device__ __forceinline__ void report() const {}
 };
 
 // Sorted (item, user) keys -> item rows: key k of the list lands behind the user rows and the earlier
 // items' diagonal entries.
 struct ItemRowsOut {
-    static constexpr bool kRuns = true;
+    static constexpr bool kRuns = true, kChecks = false;
     int32_t* col_idx;
     const int32_t* pairs;   // number of distinct pairs
     int32_t* counts;        // per item, cleared
     int64_t n_users;
     int32_t self;
     int user_bits;
-    __device__ __forceinline__ int32_t group(uint64_t key) const { return (int32_t)(key >> user_bits); }
-    __device__ __forceinline__ void store(int64_t at, uint64_t key) const {
-        const int64_t row0 = *pairs + (n_users + group(key)) * self;
+    __device__ __forceinline__ int32_t group(uint64_t key, int) const { return (int32_t)(key >> user_bits); }
+    __device__ __forceinline__ void store(uint32_t at, uint64_t key, int segment) const {
+        const int64_t row0 = *pairs + (n_users + group(key, segment)) * self;
         col_idx[row0 + at] = (int32_t)(key & ((1ull << user_bits) - 1));
+    }
+};
+
+// The same for keys that have lost the leading digit of the item, which is the segment.
+struct ItemSegmentsOut {
+    static constexpr bool kRuns = true, kChecks = false;
+    int32_t* col_idx;
+    const int32_t* pairs;
+    int32_t* counts;
+    int64_t n_users;
+    int32_t self;
+    int user_bits, item_low;
+    __device__ __forceinline__ int32_t group(uint32_t key, int segment) const {
+        return (segment << item_low) | (int32_t)(key >> user_bits);
+    }
+    __device__ __forceinline__ void store(uint32_t at, uint32_t key, int segment) const {
+        const int64_t row0 = *pairs + (n_users + group(key, segment)) * self;
+        col_idx[row0 + at] = (int32_t)(key & ((1u << user_bits) - 1));
     }
 };
 
@@ -158,6 +199,270 @@ __global__ __launch_bounds__(kHeadThreads) void emit_pairs(const uint64_t* __res
         if (last_of_user[r]) run_end[u] = pos + (head ? 1 : 0);
         if (k == count - 1) *n_pairs = pos + (head ? 1 : 0);
     }
+}
+
+// ---- long lists: 32-bit keys ------------------------------------------------------------------------
+// A pass over a list of tens of millions moves its keys twice through memory, so they are made half as
+// large: the first pass takes the leading digit of the user off, and what is left of user and item, up to 32 bits,
+// is sorted segment by segment (Segmented).  The distinct pairs go to segments of the item's leading
+// digit in the kernel that writes the user rows; there only the rest of the item is left to sort by, since
+// the users of an item arrive in order.  50 M pairs of 20 + 19 bits: 2830 us with 64-bit keys throughout (eight passes
+// of about 300, repeats counted and dropped in 320), 1910 us so (a pass: histogram 48, offsets 17, scatter 136).
+// The scatter is bound by the ranking of the keys (103 us of vector instructions), not by its 400 MB any more.
+struct ListSort {
+    static constexpr int kThreads = 512, kItems = 16, kBits = 8, kCopies = 16, kTile = kThreads * kItems;
+};
+
+// Where the segments begin: `offs` is the scanned table [segments][tiles] of the pass that made them,
+// d_count (or count) the number of keys.
+__global__ __launch_bounds__(kMaxSegments) void plan_segments(const int32_t* __restrict__ offs, int32_t tiles, int32_t n,
+                                                              int64_t count, const int32_t* __restrict__ d_count, Segments* s) {
+    __shared__ int32_t first[kMaxSegments + 1];
+    __shared__ int32_t red[kMaxSegments / 64];
+    const int g = threadIdx.x, lane = g & 63, wave = g >> 6;
+    if (g < n) first[g] = offs[(int64_t)g * tiles];
+    if (g == 0) first[n] = d_count ? *d_count : (int32_t)count;
+    __syncthreads();
+    const int32_t mine = g < n ? (first[g + 1] - first[g] + ListSort::kTile - 1) / ListSort::kTile : 0;
+    int32_t inc = mine;
+#pragma unroll
+    for (int dlt = 1; dlt < 64; dlt <<= 1) {
+        const int32_t t = __shfl_up(inc, dlt, 64);
+        if (lane >= dlt) inc += t;
+    }
+    if (lane == 63) red[wave] = inc;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kMaxSegments / 64; ++w)
+        if (w < wave) inc += red[w];
+    if (g < n) {
+        s->first[g] = first[g];
+        s->tile[g] = inc - mine;
+        if (g == n - 1) {
+            s->first[n] = first[n];
+            s->tile[n] = inc;
+        }
+    }
+}
+
+// The sorted list, its repeats skipped: distinct pairs of every tile, and their counts by the item's leading
+// digit, [digits][tiles].
+__global__ __launch_bounds__(ListSort::kThreads) void count_distinct(const uint32_t* __restrict__ keys, Segmented tiling,
+                                                                     int item_bits, int item_low, int bins,
+                                                                     int32_t* __restrict__ tile_cnt, int32_t* __restrict__ hist) {
+    using S = ListSort;
+    __shared__ int h[kMaxSegments * S::kCopies];
+    __shared__ int32_t red[S::kThreads / 64];
+    const Place at = tiling.place<S>(bins);
+    for (int k = threadIdx.x; k < kMaxSegments * S::kCopies; k += S::kThreads) h[k] = 0;
+    __syncthreads();
+    int* mine = h + threadIdx.x % S::kCopies;
+    // indexes inside the tile: its keys, and whether there is one before them in the segment
+    const int left = (int)(at.end - at.base);
+    const bool starts = left <= 0 || at.base == tiling.s->first[at.segment];
+    const uint32_t* tile_keys = keys + at.base;
+    const uint32_t item_mask = (1u << item_bits) - 1;
+    uint32_t key[S::kItems], prev[S::kItems];
+#pragma unroll
+    for (int k = 0; k < S::kItems; ++k) {
+        const int i = k * S::kThreads + (int)threadIdx.x;
+        key[k] = i < left ? tile_keys[i] : 0u;
+        prev[k] = i < left && (i > 0 || !starts) ? tile_keys[i - 1] : 0u;
+    }
+    int32_t heads = 0;
+#pragma unroll
+    for (int k = 0; k < S::kItems; ++k) {
+        const int i = k * S::kThreads + (int)threadIdx.x;
+        const bool head = i < left && ((i == 0 && starts) || key[k] != prev[k]);
+        if (head) atomicAdd(&mine[((key[k] & item_mask) >> item_low) * S::kCopies], 1);
+        heads += __popcll(__ballot(head));
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = heads;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int32_t t = 0;
+#pragma unroll
+        for (int w = 0; w < S::kThreads / 64; ++w) t += red[w];
+        tile_cnt[blockIdx.x] = t;
+    }
+    for (int d = threadIdx.x; d < bins; d += S::kThreads) {
+        int t = 0;
+#pragma unroll
+        for (int c = 0; c < S::kCopies; ++c) t += h[d * S::kCopies + ((c + d) % S::kCopies)];
+        hist[(int64_t)d * gridDim.x + blockIdx.x] = t;
+    }
+}
+
+// The lanes of a wavefront whose key (round r of its consecutive keys) is no repeat: the lane before's key comes by
+// wave_shr:1, which leaves lane 0 its first operand, the last key of the round before.
+template <int ITEMS>
+__device__ __forceinline__ uint32_t key_before(const uint32_t (&key)[ITEMS], int r, uint32_t before_all) {
+    const uint32_t edge = r == 0 ? before_all : (uint32_t)__builtin_amdgcn_readlane((int)key[r > 0 ? r - 1 : 0], 63);
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)edge, (int)key[r], 0x138, 0xf, 0xf, false);
+}
+
+// The distinct pairs as user rows: pair k lands behind its user's diagonal entry.  tile_cnt: the distinct pairs
+// before every tile.  (In one kernel with spread_distinct, which reads the same keys, the two took 320 us, its
+// registers leaving room for one workgroup on a compute unit; apart they take 132 + 159.)
+constexpr int kUserRounds = 8;
+constexpr int kUserThreads = ListSort::kTile / kUserRounds;
+__global__ __launch_bounds__(kUserThreads) void write_user_rows(const uint32_t* __restrict__ keys, Segmented tiling, int64_t count,
+                                                                int user_low, int item_bits, int32_t n_users, int32_t self,
+                                                                const int32_t* __restrict__ tile_cnt,
+                                                                int32_t* __restrict__ col_idx, int32_t* __restrict__ run_start,
+                                                                int32_t* __restrict__ run_end, int32_t* __restrict__ n_pairs) {
+    constexpr int kWaves = kUserThreads / 64;
+    __shared__ int32_t red[kWaves];
+    const Place at = tiling.place<ListSort>(1);
+    if (at.base >= at.end) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // indexes inside the tile: of its keys, of the segment's first and last, of the list's last
+    const int left = (int)(at.end - at.base), chunk = wave * (64 * kUserRounds);
+    const int first = at.base == tiling.s->first[at.segment] ? 0 : -1;
+    const int last = at.end == tiling.s->first[at.segment + 1] ? left - 1 : left;
+    const int list_last = at.end == count ? left - 1 : left;
+    const uint32_t* tile_keys = keys + at.base;
+    const uint32_t item_mask = (1u << item_bits) - 1;
+    uint32_t key[kUserRounds];
+#pragma unroll
+    for (int r = 0; r < kUserRounds; ++r) {
+        const int i = chunk + r * 64 + lane;
+        key[r] = i < left ? tile_keys[i] : 0u;
+    }
+    // the keys before and behind the wavefront's (a tile that is not full ends with its segment)
+    const int behind_at = chunk + 64 * kUserRounds;
+    const uint32_t before_all = chunk > first && chunk < left ? tile_keys[chunk - 1] : 0u;
+    const uint32_t behind_all = behind_at <= last ? tile_keys[behind_at] : 0u;
+    // which keys are no repeats, which are the first of their user's
+    uint64_t head[kUserRounds], lead[kUserRounds + 1];
+    int32_t heads = 0;
+#pragma unroll
+    for (int r = 0; r < kUserRounds; ++r) {
+        const int i = chunk + r * 64 + lane;
+        const uint32_t prev = key_before(key, r, before_all);
+        head[r] = __ballot(i < left && (i == first || key[r] != prev));
+        lead[r] = __ballot(i < left && (i == first || (prev >> item_bits) != (key[r] >> item_bits)));
+        heads += __popcll(head[r]);
+    }
+    const uint32_t last_key = (uint32_t)__builtin_amdgcn_readlane((int)key[kUserRounds - 1], 63);
+    lead[kUserRounds] = (behind_all >> item_bits) != (last_key >> item_bits) ? 1 : 0;
+    if (lane == 0) red[wave] = heads;
+    __syncthreads();
+    int32_t pos0 = tile_cnt[blockIdx.x];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w)
+        if (w < wave) pos0 += red[w];
+#pragma unroll
+    for (int r = 0; r < kUserRounds; ++r) {
+        const int i = chunk + r * 64 + lane;
+        const bool mine = (head[r] >> lane) & 1;
+        const int32_t pos = pos0 + __popcll(head[r] & lt_mask);
+        pos0 += __popcll(head[r]);
+        const int32_t u = (int32_t)(((uint32_t)at.segment << user_low) | (key[r] >> item_bits));
+        if (mine) col_idx[pos + (int64_t)(u + 1) * self] = n_users + (int32_t)(key[r] & item_mask);
+        if (i >= left) continue;
+        if ((lead[r] >> lane) & 1) run_start[u] = pos;
+        // the last of its user's: the next key leads, or there is none
+        const uint64_t ends = (lead[r] >> 1) | (lead[r + 1] << 63);
+        if (i == last || ((ends >> lane) & 1)) run_end[u] = pos + (mine ? 1 : 0);
+        if (i == list_last) *n_pairs = pos + (mine ? 1 : 0);
+    }
+}
+
+// The distinct pairs by the leading digit of the item, in order, as keys (rest of the item, user).  offs: the
+// counts of count_distinct, scanned.
+__global__ __launch_bounds__(ListSort::kThreads) __attribute__((amdgpu_waves_per_eu(4))) void spread_distinct(const uint32_t* __restrict__ keys, Segmented tiling,
+                                                                      int user_low, int user_bits, int item_bits, int item_low,
+                                                                      int digit_bits, const int32_t* __restrict__ offs,
+                                                                      uint32_t* __restrict__ by_item) {
+    using S = ListSort;
+    constexpr int kWaves = S::kThreads / 64;
+    static_assert(S::kThreads >= kMaxSegments && kMaxSegments == 256, "a thread per digit, digits in bytes");
+    __shared__ uint16_t wave_cnt[kWaves][kMaxSegments];
+    __shared__ int32_t shift_by[kMaxSegments];
+    __shared__ int32_t red[kWaves];
+    __shared__ uint32_t tile[S::kTile];
+    __shared__ uint8_t tile_digit[S::kTile];
+    const Place at = tiling.place<S>(1);
+    if (at.base >= at.end) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    const int left = (int)(at.end - at.base), chunk = wave * (64 * S::kItems);
+    const int first = at.base == tiling.s->first[at.segment] ? 0 : -1;   // the segment's first key, seen from the tile
+    const uint32_t* tile_keys = keys + at.base;
+    const uint32_t item_mask = (1u << item_bits) - 1, low_mask = (1u << item_low) - 1;
+    const int32_t base = (int)threadIdx.x < 1 << digit_bits ? offs[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] : 0;
+    uint32_t key[S::kItems];
+#pragma unroll
+    for (int r = 0; r < S::kItems; ++r) {
+        const int i = chunk + r * 64 + lane;
+        key[r] = i < left ? tile_keys[i] : 0u;
+    }
+    const uint32_t before_all = chunk > first && chunk < left ? tile_keys[chunk - 1] : 0u;
+    for (int k = threadIdx.x; k < kWaves * kMaxSegments / 2; k += S::kThreads) reinterpret_cast<uint32_t*>(&wave_cnt[0][0])[k] = 0;
+    __syncthreads();
+    uint64_t head[S::kItems];
+    uint16_t rank[S::kItems];
+#pragma unroll
+    for (int r = 0; r < S::kItems; ++r) {
+        const int i = chunk + r * 64 + lane;
+        const uint32_t prev = key_before(key, r, before_all);
+        const bool mine = i < left && (i == first || key[r] != prev);
+        head[r] = __ballot(mine);
+        const int d = (int)((key[r] & item_mask) >> item_low);
+        const uint64_t peers = lanes_of_digit<8>(d, digit_bits, head[r]);
+        const int pre = wave_cnt[wave][d];
+        const int below = __popcll(peers & lt_mask);
+        rank[r] = (uint16_t)(pre + below);
+        if (mine && below == 0) wave_cnt[wave][d] = (uint16_t)(pre + __popcll(peers));
+    }
+    __syncthreads();
+    {   // digit t of thread t: its place in the tile, where the tile's keys of it go, and every wavefront's first place
+        int32_t mine = 0;
+        if (threadIdx.x < kMaxSegments)
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) mine += wave_cnt[w][threadIdx.x];
+        int32_t inc = mine;
+#pragma unroll
+        for (int dlt = 1; dlt < 64; dlt <<= 1) {
+            const int32_t t = __shfl_up(inc, dlt, 64);
+            if (lane >= dlt) inc += t;
+        }
+        if (lane == 63) red[wave] = inc;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+            if (w < wave) inc += red[w];
+        if (threadIdx.x < kMaxSegments) {
+            int32_t place = inc - mine;
+            shift_by[threadIdx.x] = base - place;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const int c = wave_cnt[w][threadIdx.x];
+                wave_cnt[w][threadIdx.x] = (uint16_t)place;
+                place += c;
+            }
+        }
+    }
+    __syncthreads();
+    int32_t all = 0;   // red[] holds inclusive sums over the digits; those of the first wavefronts cover them all
+#pragma unroll
+    for (int w = 0; w < kMaxSegments / 64; ++w) all += red[w];
+#pragma unroll
+    for (int r = 0; r < S::kItems; ++r) {
+        if ((head[r] >> lane) & 1) {
+            const uint32_t item = key[r] & item_mask;
+            const int d = (int)(item >> item_low);
+            const uint32_t u = ((uint32_t)at.segment << user_low) | (key[r] >> item_bits);
+            const int place = wave_cnt[wave][d] + rank[r];
+            tile[place] = ((item & low_mask) << user_bits) | u;
+            tile_digit[place] = (uint8_t)d;
+        }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int p = threadIdx.x; p < all; p += S::kThreads) by_item[(uint32_t)(shift_by[tile_digit[p]] + p)] = tile[p];
 }
 
 // ---- row pointers ----------------------------------------------------------------------------------
@@ -328,7 +633,7 @@ __global__ __launch_bounds__(SplitSort::kThreads) void count_ranges(PairsIn in, 
         if (e < count) {
             const bool ok = in.ok(u[k], i[k]);
             if (!ok) bad = 1;
-            atomicAdd(&h[ok ? (int)((((uint64_t)(uint32_t)u[k] << in.item_bits) | (uint32_t)i[k]) >> shift) : 0], 1);
+            atomicAdd(&h[(int)(in.key(PairsIn::raw{u[k], i[k]}) >> shift)], 1);
         }
     }
     __syncthreads();
@@ -766,9 +1071,27 @@ struct BuildWs {
     int32_t* run_end;
     int64_t zero_count;
     void* scan_ws;
+    Segments* segments;  // [2] of the users, of the items
+    int32_t* cells;      // digit counts of the segments' tiles
     BucketWs buckets;
     size_t bytes;
 };
+
+// The widths of the 32-bit way; tiles 0 where it is not taken: short lists, whose passes are bound by launches,
+// and id ranges of more than 40 bits together.
+struct ListPlan {
+    int user_bits, item_bits;
+    int user_low, item_low;   // bits behind the leading digit
+    int64_t tiles;            // upper bound
+};
+ListPlan plan_lists(int32_t n_users, int32_t n_items, int64_t n_edges) {
+    ListPlan p = {bits_for(n_users), bits_for(n_items), 0, 0, 0};
+    p.user_low = p.user_bits > 8 ? p.user_bits - 8 : 0;
+    p.item_low = p.item_bits > 9 ? p.item_bits - 8 : 1;   // something is left for the pass that writes the item rows
+    if (sorts_large(n_edges) && p.user_low + p.item_bits <= 32 && p.item_low + p.user_bits <= 32)
+        p.tiles = ceil_div(n_edges, ListSort::kTile) + kMaxSegments;
+    return p;
+}
 
 BuildWs carve_build(void* base, int32_t n_users, int32_t n_items, int64_t n_edges) {
     const int64_t n = (int64_t)n_users + n_items;
@@ -779,6 +1102,7 @@ BuildWs carve_build(void* base, int32_t n_users, int32_t n_items, int64_t n_edge
     w.buf_b = c.take<uint64_t>(e);
     const int64_t head_tiles = ceil_div(e, kHeadTile), row_tiles = ceil_div(n > 0 ? n : 1, kRowTile);
     const int64_t tiles = head_tiles > row_tiles ? head_tiles : row_tiles;
+    const int64_t cells = plan_lists(n_users, n_items, n_edges).tiles * kMaxSegments;
     w.tile_cnt = c.take<int32_t>(tiles);
     w.sort_ws = c.take<char>(radix_sort_workspace_bytes(e));
     w.zero_count = 64 + 2 * (n + 1);
@@ -786,7 +1110,9 @@ BuildWs carve_build(void* base, int32_t n_users, int32_t n_items, int64_t n_edge
     w.small = w.zeroed;
     w.run_start = w.zeroed ? w.zeroed + 64 : nullptr;
     w.run_end = w.zeroed ? w.run_start + (n + 1) : nullptr;
-    w.scan_ws = c.take<char>(scan_workspace_bytes(tiles));
+    w.scan_ws = c.take<char>(scan_workspace_bytes(tiles > cells ? tiles : cells));
+    w.segments = c.take<Segments>(2);
+    w.cells = c.take<int32_t>(cells > 0 ? cells : 1);
     w.buckets = carve_buckets(c, n_edges);
     w.bytes = c.size();
     return w;
@@ -842,6 +1168,83 @@ int32_t sort_pairs(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t n
     return E2EG_OK;
 }
 
+// One pass over the segments' keys.
+template <typename Out>
+int32_t segment_pass(const BuildWs& w, const ListPlan& p, const Segments* s, int n, const uint32_t* keys, Out out, int shift,
+                     int nbits, hipStream_t stream) {
+    const ArrayIn<uint32_t> in{keys};
+    const Segmented tiling{s, n};
+    const dim3 grid((unsigned)p.tiles), blk(ListSort::kThreads);
+    sort_histogram<ListSort, ArrayIn<uint32_t>, Segmented, false><<<grid, blk, 0, stream>>>(in, tiling, shift, nbits, w.cells);
+    E2EG_LAUNCH_CHECK("sort_histogram");
+    E2EG_HIP_TRY(exclusive_scan_i32(w.cells, w.cells, p.tiles << nbits, nullptr, w.scan_ws, stream));
+    sort_scatter<ListSort, ArrayIn<uint32_t>, Out, Segmented, false><<<grid, blk, 0, stream>>>(in, out, tiling, shift, nbits, w.cells);
+    E2EG_LAUNCH_CHECK("sort_scatter");
+    return E2EG_OK;
+}
+
+// As sort_pairs, with 32-bit keys.
+int32_t sort_lists(const BuildWs& w, const ListPlan& p, int32_t n_users, int32_t n_items, int64_t n_edges, const int32_t* users,
+                   const int32_t* items, int32_t self, int32_t* col_idx, hipStream_t stream) {
+    uint32_t* src = reinterpret_cast<uint32_t*>(w.buf_a);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(w.buf_b);
+    const auto swap = [&] { uint32_t* t = src; src = dst; dst = t; };
+    const dim3 blk(ListSort::kThreads);
+    const int32_t whole_tiles = (int32_t)ceil_div(n_edges, ListSort::kTile);
+    const int user_digit = p.user_bits - p.user_low, item_digit = p.item_bits - p.item_low;
+    const int rest = p.user_low + p.item_bits;   // bits of a user segment's keys
+    {   // segments of the user's leading digit
+        const Whole whole{n_edges, nullptr, whole_tiles};
+        sort_histogram<ListSort, UsersIn, Whole, false><<<dim3((unsigned)whole_tiles), blk, 0, stream>>>(
+            UsersIn{users, n_users, p.item_bits}, whole, rest, user_digit, w.cells);
+        E2EG_LAUNCH_CHECK("sort_histogram");
+        E2EG_HIP_TRY(exclusive_scan_i32(w.cells, w.cells, (int64_t)whole_tiles << user_digit, nullptr, w.scan_ws, stream));
+        sort_scatter<ListSort, PairsIn, LowBitsOut, Whole, false><<<dim3((unsigned)whole_tiles), blk, 0, stream>>>(
+            PairsIn{users, items, n_users, n_items, p.item_bits, w.small + 1},
+            LowBitsOut{src, (uint32_t)((1ull << rest) - 1)}, whole, rest, user_digit, w.cells);
+        E2EG_LAUNCH_CHECK("sort_scatter");
+        plan_segments<<<dim3(1), dim3(kMaxSegments), 0, stream>>>(w.cells, whole_tiles, 1 << user_digit, n_edges, nullptr, w.segments);
+        E2EG_LAUNCH_CHECK("plan_segments");
+    }
+    const int passes = (rest + ListSort::kBits - 1) / ListSort::kBits;
+    for (int q = 0, shift = 0; q < passes; ++q) {
+        const int width = sort_width(rest, passes, q);
+        const int32_t st = segment_pass(w, p, w.segments, 1 << user_digit, src, ArrayOut<uint32_t>{dst}, shift, width, stream);
+        if (st != E2EG_OK) return st;
+        shift += width;
+        swap();
+    }
+    const dim3 grid((unsigned)p.tiles);
+    const Segmented tiling{w.segments, 1 << user_digit};
+    count_distinct<<<grid, blk, 0, stream>>>(src, tiling, p.item_bits, p.item_low, 1 << item_digit, w.tile_cnt, w.cells);
+    E2EG_LAUNCH_CHECK("count_distinct");
+    E2EG_HIP_TRY(exclusive_scan_i32(w.tile_cnt, w.tile_cnt, p.tiles, nullptr, w.scan_ws, stream));
+    E2EG_HIP_TRY(exclusive_scan_i32(w.cells, w.cells, p.tiles << item_digit, nullptr, w.scan_ws, stream));
+    write_user_rows<<<grid, dim3(kUserThreads), 0, stream>>>(src, tiling, n_edges, p.user_low, p.item_bits, n_users, self, w.tile_cnt,
+                                                            col_idx, w.run_start, w.run_end, w.small);
+    E2EG_LAUNCH_CHECK("write_user_rows");
+    spread_distinct<<<grid, blk, 0, stream>>>(src, tiling, p.user_low, p.user_bits, p.item_bits, p.item_low, item_digit, w.cells, dst);
+    E2EG_LAUNCH_CHECK("spread_distinct");
+    plan_segments<<<dim3(1), dim3(kMaxSegments), 0, stream>>>(w.cells, (int32_t)p.tiles, 1 << item_digit, 0, w.small,
+                                                             w.segments + 1);
+    E2EG_LAUNCH_CHECK("plan_segments");
+    swap();
+    const int item_passes = (p.item_low + ListSort::kBits - 1) / ListSort::kBits;
+    for (int q = 0, shift = p.user_bits; q < item_passes; ++q) {
+        const int width = sort_width(p.item_low, item_passes, q);
+        const int32_t st =
+            q + 1 < item_passes
+                ? segment_pass(w, p, w.segments + 1, 1 << item_digit, src, ArrayOut<uint32_t>{dst}, shift, width, stream)
+                : segment_pass(w, p, w.segments + 1, 1 << item_digit, src,
+                               ItemSegmentsOut{col_idx, w.small, w.run_end + n_users, n_users, self, p.user_bits, p.item_low},
+                               shift, width, stream);
+        if (st != E2EG_OK) return st;
+        shift += width;
+        swap();
+    }
+    return E2EG_OK;
+}
+
 // The general way.
 int32_t build_sorted(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t n_edges, const int32_t* users,
                      const int32_t* items, int32_t self, int32_t* row_ptr, int32_t* col_idx, hipStream_t stream) {
@@ -849,7 +1252,9 @@ int32_t build_sorted(const BuildWs& w, int32_t n_users, int32_t n_items, int64_t
     zero_i32<<<dim3(blocks_for(w.zero_count, kThreads)), dim3(kThreads), 0, stream>>>(w.zeroed, w.zero_count);
     E2EG_LAUNCH_CHECK("zero_i32");
     if (n_edges > 0) {
-        const int32_t st = sort_pairs(w, n_users, n_items, n_edges, users, items, self, col_idx, stream);
+        const ListPlan p = plan_lists(n_users, n_items, n_edges);
+        const int32_t st = p.tiles > 0 ? sort_lists(w, p, n_users, n_items, n_edges, users, items, self, col_idx, stream)
+                                       : sort_pairs(w, n_users, n_items, n_edges, users, items, self, col_idx, stream);
         if (st != E2EG_OK) return st;
     }
     if (n == 0) {
@@ -881,8 +1286,8 @@ int32_t build_bucketed(const BuildWs& w, const BucketPlan& p, int32_t n_users, i
     const dim3 user_grid((unsigned)p.n_user_ranges), user_blk(kBucketThreads);
     count_ranges<<<split_grid, split_blk, 0, stream>>>(in, n_edges, shift, p.n_user_ranges, w.buckets);
     E2EG_LAUNCH_CHECK("count_ranges");
-    sort_scatter<SplitSort, PairsIn, KeysOut, true><<<split_grid, split_blk, 0, stream>>>(
-        in, KeysOut{w.buf_a}, n_edges, nullptr, shift, p.user_bits - p.user_low, w.buckets.user_hist, tiles);
+    sort_scatter<SplitSort, PairsIn, KeysOut, Whole, true><<<split_grid, split_blk, 0, stream>>>(
+        in, KeysOut{w.buf_a}, Whole{n_edges, nullptr, tiles}, shift, p.user_bits - p.user_low, w.buckets.user_hist);
     E2EG_LAUNCH_CHECK("sort_scatter");
     sort_ranges<<<user_grid, user_blk, 0, stream>>>(w.buf_a, tiles, p, w.buf_b, w.buckets);
     E2EG_LAUNCH_CHECK("sort_ranges");

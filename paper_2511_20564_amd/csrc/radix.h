@@ -13,7 +13,7 @@ namespace e2eg {
 // of launches: digits of up to 11 bits (two launches a pass while the table is so small that every workgroup
 // adds up its own offsets).
 struct LargeSort {
-    static constexpr int kThreads = 512, kItems = 16, kBits = 8, kCopies = 4, kTile = kThreads * kItems;
+    static constexpr int kThreads = 512, kItems = 16, kBits = 8, kCopies = 16, kTile = kThreads * kItems;
 };
 struct SmallSort {
     static constexpr int kThreads = 1024, kItems = 8, kBits = 11, kCopies = 1, kTile = kThreads * kItems;
@@ -25,48 +25,105 @@ struct SplitSort {
 constexpr int64_t kLargeSortMin = 4 << 20;
 constexpr int kFusedTiles = 64;   // up to this many tiles the scatter adds up its offsets itself
 
-struct KeysIn {
-    const uint64_t* keys;
-    using raw = uint64_t;   // what is loaded, and the key of it
-    __device__ __forceinline__ raw load(int64_t i) const { return keys[i]; }
-    __device__ __forceinline__ raw none() const { return 0ull; }
-    __device__ __forceinline__ uint64_t key(raw r) const { return r; }
+// Keys come as K: 64-bit, or 32-bit once the leading digit has been taken off (Segmented).
+template <typename K>
+struct ArrayIn {
+    const K* keys;
+    using Key = K;
+    using raw = K;   // what is loaded, and the key of it
+    __device__ __forceinline__ ArrayIn from(int64_t base) const { return ArrayIn{keys + base}; }   // as of key `base`
+    __device__ __forceinline__ raw load(uint32_t i) const { return keys[i]; }
+    __device__ __forceinline__ raw none() const { return 0; }
+    __device__ __forceinline__ K key(raw r) const { return r; }
     __device__ __forceinline__ bool ok(raw) const { return true; }
     __device__ __forceinline__ void report() const {}
 };
-struct KeysOut {
-    static constexpr bool kRuns = false;
-    uint64_t* keys;
-    __device__ __forceinline__ void store(int64_t at, uint64_t key) const { keys[at] = key; }
+template <typename K>
+struct ArrayOut {
+    static constexpr bool kRuns = false, kChecks = false;
+    K* keys;
+    __device__ __forceinline__ void store(uint32_t at, K key, int) const { keys[at] = key; }
+};
+using KeysIn = ArrayIn<uint64_t>;
+using KeysOut = ArrayOut<uint64_t>;
+// 64-bit keys in, their low bits out (kChecks: the scatter reports bad input, its histogram having seen less).
+struct LowBitsOut {
+    static constexpr bool kRuns = false, kChecks = true;
+    uint32_t* keys;
+    uint32_t mask;
+    __device__ __forceinline__ void store(uint32_t at, uint64_t key, int) const { keys[at] = (uint32_t)key & mask; }
 };
 
-// Digit counts of every tile.  The table is digit-major [bins][tiles] for a scan, or (TILE_MAJOR)
-// [tiles][bins] for a scatter that adds up its offsets itself.  d_count (may be null): the number of keys,
-// known on the device only; `count` is then its upper bound, which sized the launch.
-template <typename S, typename In, bool TILE_MAJOR>
-__global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, int64_t count, const int32_t* __restrict__ d_count,
-                                                              int shift, int nbits, int32_t* __restrict__ hist,
-                                                              int32_t tiles) {
-    __shared__ int h[S::kCopies][1 << S::kBits];   // copies: fewer lanes meet on one word
+// How a list is cut into tiles, one workgroup each.
+// Whole: tiles of consecutive keys; the table of digit counts is digit-major [bins][tiles] for a scan, or
+// tile-major [tiles][bins] for a scatter that adds up its offsets itself.  d_count (may be null): the
+// number of keys, known on the device only; `count` is then its upper bound, which sized the launch.
+struct Place {
+    int64_t base, end;   // keys of the tile (base >= end: none)
+    int64_t cell;        // its count of digit d is at cell + d * step
+    int32_t step;
+    int segment;
+};
+struct Whole {
+    int64_t count;
+    const int32_t* d_count;
+    int32_t tiles;
+    template <typename S>
+    __device__ __forceinline__ Place place(int) const {
+        const int64_t n = d_count ? *d_count : count, base = (int64_t)blockIdx.x * S::kTile;
+        return Place{base, base + S::kTile < n ? base + S::kTile : n, (int64_t)blockIdx.x, tiles, 0};
+    }
+};
+// Segmented: every segment (the keys of one value of a leading digit) is sorted by itself and has its own
+// tiles; the table is [segments][bins][tiles of the segment], so that one scan of it gives the places in
+// the whole list.
+constexpr int kMaxSegments = 256;
+struct Segments {
+    int32_t first[kMaxSegments + 1];   // first key of every segment
+    int32_t tile[kMaxSegments + 1];    // first tile
+};
+struct Segmented {
+    const Segments* s;
+    int32_t n;   // segments
+    template <typename S>
+    __device__ __forceinline__ Place place(int bins) const {
+        // the segment whose tiles these are: the last one that begins at or before this tile (empty ones begin there too)
+        const int g = __syncthreads_count((int)threadIdx.x < n && s->tile[threadIdx.x] <= (int)blockIdx.x) - 1;
+        const int32_t t0 = s->tile[g], t1 = s->tile[g + 1];
+        const int64_t end = s->first[g + 1];
+        if ((int)blockIdx.x >= t1) return Place{end, end, 0, 0, g};   // the launch is sized for an upper bound
+        const int64_t base = s->first[g] + (int64_t)((int)blockIdx.x - t0) * S::kTile;
+        return Place{base, base + S::kTile < end ? base + S::kTile : end, (int64_t)t0 * bins + ((int)blockIdx.x - t0), t1 - t0, g};
+    }
+};
+
+// Digit counts of every tile.
+template <typename S, typename In, typename Tiling, bool TILE_MAJOR>
+__global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, Tiling tiling, int shift, int nbits,
+                                                              int32_t* __restrict__ hist) {
+    // [digit][copy], a copy for every kCopies-th lane: with few digits, or popular ones, the lanes of a wavefront
+    // would meet on one word and take turns
+    __shared__ int h[S::kCopies << S::kBits];
     const int bins = 1 << nbits;
-    for (int k = threadIdx.x; k < S::kCopies << S::kBits; k += S::kThreads) (&h[0][0])[k] = 0;
+    for (int k = threadIdx.x; k < S::kCopies << S::kBits; k += S::kThreads) h[k] = 0;
     __syncthreads();
-    if (d_count) count = *d_count;
-    const int64_t base = (int64_t)blockIdx.x * S::kTile;
-    int* mine = h[(threadIdx.x >> 6) % S::kCopies];
+    const Place at = tiling.template place<S>(bins);
+    int* mine = h + threadIdx.x % S::kCopies;
+    const int left = (int)(at.end - at.base);   // 32-bit indexes inside the tile: the passes are bound by VALU work
+    const In tile_in = in.from(at.base);
     typename In::raw raw[S::kItems];
 #pragma unroll
     for (int k = 0; k < S::kItems; ++k) {
-        const int64_t i = base + k * S::kThreads + threadIdx.x;
-        raw[k] = i < count ? in.load(i) : in.none();
+        const int i = k * S::kThreads + (int)threadIdx.x;
+        raw[k] = i < left ? tile_in.load(i) : in.none();
     }
     bool ok = true;
 #pragma unroll
     for (int k = 0; k < S::kItems; ++k) {
-        const int64_t i = base + k * S::kThreads + threadIdx.x;
-        if (i < count) {
+        const int i = k * S::kThreads + (int)threadIdx.x;
+        if (i < left) {
             ok = ok && in.ok(raw[k]);
-            atomicAdd(&mine[(int)(in.key(raw[k]) >> shift) & (bins - 1)], 1);
+            atomicAdd(&mine[((int)(in.key(raw[k]) >> shift) & (bins - 1)) * S::kCopies], 1);
         }
     }
     if (!ok) in.report();
@@ -74,9 +131,9 @@ __global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, int64_t cou
     for (int d = threadIdx.x; d < bins; d += S::kThreads) {
         int t = 0;
 #pragma unroll
-        for (int c = 0; c < S::kCopies; ++c) t += h[c][d];
+        for (int c = 0; c < S::kCopies; ++c) t += h[d * S::kCopies + ((c + d) % S::kCopies)];
         if (TILE_MAJOR) hist[(int64_t)blockIdx.x * bins + d] = t;
-        else hist[(int64_t)d * tiles + blockIdx.x] = t;
+        else if (at.step > 0) hist[at.cell + (int64_t)d * at.step] = t;
     }
 }
 
@@ -87,42 +144,48 @@ __global__ __launch_bounds__(S::kThreads) void sort_histogram(In in, int64_t cou
 // `offs` is the digit-major table of scanned offsets, or, with COUNTS, the raw tile-major histogram, from
 // which every workgroup then adds up its own offsets (few tiles: a short loop of coalesced reads that
 // saves the launches of a scan).
-template <typename S, typename In, typename Out, bool COUNTS>
-__global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int64_t count,
-                                                            const int32_t* __restrict__ d_count, int shift, int nbits,
-                                                            const int32_t* __restrict__ offs, int32_t tiles) {
+template <typename S, typename In, typename Out, typename Tiling, bool COUNTS>
+__global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, Tiling tiling, int shift, int nbits,
+                                                            const int32_t* __restrict__ offs) {
+    using Key = typename In::Key;
     constexpr int kBins = 1 << S::kBits;
     constexpr int kWaves = S::kThreads / 64;
     constexpr int kPer = kBins > S::kThreads ? kBins / S::kThreads : 1;   // digits of one thread, consecutive
     __shared__ uint16_t wave_cnt[kWaves][kBins];   // keys of digit d in wavefront w, then their first place in the tile
     __shared__ int wave_tot[kWaves];
     __shared__ int shift_by[kBins];                // where the tile's keys of digit d go, less their first place in the tile
-    __shared__ uint64_t tile[S::kTile];
+    __shared__ Key tile[S::kTile];
     const int bins = 1 << nbits;
-    if (d_count) count = *d_count;
-    const int64_t tile_base = (int64_t)blockIdx.x * S::kTile;
-    if (tile_base >= count) return;
+    const Place place = tiling.template place<S>(bins);
+    if (place.base >= place.end) return;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int64_t chunk = tile_base + (int64_t)wave * (64 * S::kItems);
-    uint64_t key[S::kItems];
+    const int left = (int)(place.end - place.base), chunk = wave * (64 * S::kItems);   // indexes inside the tile
+    const In tile_in = in.from(place.base);
+    Key key[S::kItems];
     uint16_t rank[S::kItems];
     {
         typename In::raw raw[S::kItems];
 #pragma unroll
         for (int r = 0; r < S::kItems; ++r) {
-            const int64_t i = chunk + r * 64 + lane;
-            raw[r] = i < count ? in.load(i) : in.none();
+            const int i = chunk + r * 64 + lane;
+            raw[r] = i < left ? tile_in.load(i) : in.none();
         }
 #pragma unroll
         for (int r = 0; r < S::kItems; ++r) key[r] = in.key(raw[r]);
+        if constexpr (Out::kChecks) {
+            bool ok = true;
+#pragma unroll
+            for (int r = 0; r < S::kItems; ++r) ok = ok && (chunk + r * 64 + lane >= left || in.ok(raw[r]));
+            if (!ok) in.report();
+        }
     }
     for (int k = threadIdx.x; k < kWaves * kBins / 2; k += S::kThreads) reinterpret_cast<uint32_t*>(&wave_cnt[0][0])[k] = 0;
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < S::kItems; ++r) {
-        const bool valid = chunk + r * 64 + lane < count;
+        const bool valid = chunk + r * 64 + lane < left;
         const int d = (int)(key[r] >> shift) & (bins - 1);
         const uint64_t peers = lanes_of_digit<S::kBits>(d, nbits, __ballot(valid));
         const int pre = wave_cnt[wave][d];
@@ -162,7 +225,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
         };
         int first = scan(sum);
         int base[kPer];
-        if (COUNTS) {
+        if constexpr (COUNTS) {
             // keys with a smaller digit anywhere, plus keys with this digit in earlier tiles
             int before[kPer], total[kPer], all = 0;
 #pragma unroll
@@ -173,7 +236,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
             const int dd = kParts > 1 ? threadIdx.x % kBins : d0, part = kParts > 1 ? threadIdx.x / kBins : 0;
             if (dd < bins) {
 #pragma unroll 16
-                for (int b = part; b < tiles; b += kParts)
+                for (int b = part; b < tiling.tiles; b += kParts)
 #pragma unroll
                     for (int p = 0; p < kPer; ++p) {
                         const int c = dd + p < bins ? offs[(int64_t)b * bins + dd + p] : 0;
@@ -203,7 +266,7 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
             }
         } else {
 #pragma unroll
-            for (int p = 0; p < kPer; ++p) base[p] = d0 + p < bins ? offs[(int64_t)(d0 + p) * tiles + blockIdx.x] : 0;
+            for (int p = 0; p < kPer; ++p) base[p] = d0 + p < bins ? offs[place.cell + (int64_t)(d0 + p) * place.step] : 0;
         }
 #pragma unroll
         for (int p = 0; p < kPer; ++p) {
@@ -223,25 +286,23 @@ __global__ __launch_bounds__(S::kThreads) void sort_scatter(In in, Out out, int6
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < S::kItems; ++r) {
-        if (chunk + r * 64 + lane < count) {
+        if (chunk + r * 64 + lane < left) {
             const int d = (int)(key[r] >> shift) & (bins - 1);
             tile[wave_cnt[wave][d] + rank[r]] = key[r];
         }
     }
     __syncthreads();
-    const int64_t left = count - tile_base;
-    const int valid_keys = left < S::kTile ? (int)left : S::kTile;
 #pragma unroll 4
-    for (int p = threadIdx.x; p < valid_keys; p += S::kThreads) {
-        const uint64_t k = tile[p];
+    for (int p = threadIdx.x; p < left; p += S::kThreads) {
+        const Key k = tile[p];
         const int d = (int)(k >> shift) & (bins - 1);
-        out.store((int64_t)shift_by[d] + p, k);
+        out.store((uint32_t)(shift_by[d] + p), k, place.segment);
         if constexpr (Out::kRuns) {
             // the last pass leaves equal groups next to each other in the tile: a group's number of keys is
             // one past its last place less its first
-            const int32_t g = out.group(k);
-            const bool head = p == 0 || out.group(tile[p - 1]) != g;
-            const bool tail = p == valid_keys - 1 || out.group(tile[p + 1]) != g;
+            const int32_t g = out.group(k, place.segment);
+            const bool head = p == 0 || out.group(tile[p - 1], place.segment) != g;
+            const bool tail = p == left - 1 || out.group(tile[p + 1], place.segment) != g;
             const int delta = (tail ? p + 1 : 0) - (head ? p : 0);
             if (delta != 0) atomicAdd(out.counts + g, delta);
         }
@@ -255,17 +316,18 @@ int32_t radix_pass_as(In in, Out out, int64_t count, const int32_t* d_count, int
     const int32_t tiles = (int32_t)ceil_div(count, S::kTile);
     const dim3 grid((unsigned)tiles), blk(S::kThreads);
     int32_t* hist = static_cast<int32_t*>(ws);
+    const Whole whole{count, d_count, tiles};
     if (tiles <= kFusedTiles) {
-        sort_histogram<S, In, true><<<grid, blk, 0, stream>>>(in, count, d_count, shift, nbits, hist, tiles);
+        sort_histogram<S, In, Whole, true><<<grid, blk, 0, stream>>>(in, whole, shift, nbits, hist);
         E2EG_LAUNCH_CHECK("sort_histogram");
-        sort_scatter<S, In, Out, true><<<grid, blk, 0, stream>>>(in, out, count, d_count, shift, nbits, hist, tiles);
+        sort_scatter<S, In, Out, Whole, true><<<grid, blk, 0, stream>>>(in, out, whole, shift, nbits, hist);
     } else {
         const int64_t cells = (int64_t)tiles << nbits;
         void* scan_ws = static_cast<char*>(ws) + align_up((size_t)cells * sizeof(int32_t));
-        sort_histogram<S, In, false><<<grid, blk, 0, stream>>>(in, count, d_count, shift, nbits, hist, tiles);
+        sort_histogram<S, In, Whole, false><<<grid, blk, 0, stream>>>(in, whole, shift, nbits, hist);
         E2EG_LAUNCH_CHECK("sort_histogram");
         E2EG_HIP_TRY(exclusive_scan_i32(hist, hist, cells, nullptr, scan_ws, stream));
-        sort_scatter<S, In, Out, false><<<grid, blk, 0, stream>>>(in, out, count, d_count, shift, nbits, hist, tiles);
+        sort_scatter<S, In, Out, Whole, false><<<grid, blk, 0, stream>>>(in, out, whole, shift, nbits, hist);
     }
     E2EG_LAUNCH_CHECK("sort_scatter");
     return E2EG_OK;
