@@ -29,7 +29,7 @@ def needs_build() -> bool:
     if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
-    deps = sources() + [os.path.join(CSRC, f) for f in ("common.h", "radix.h", "native.cpp")]
+    deps = sources() + [os.path.join(CSRC, f) for f in ("common.h", "radix.h", "entry_tiles.h", "native.cpp")]
     deps.append(os.path.join(HERE, "..", "include", "e2eg.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 

@@ -14,6 +14,7 @@
 // Large graphs: the same steps with 32-bit keys where the ids allow it ("long lists" below).
 // Small graphs are bound by the number of launches (17 of the above) and take another way, "buckets" below:
 // five launches.
+#include "entry_tiles.h"
 #include "radix.h"
 
 namespace e2eg {
@@ -1023,41 +1024,88 @@ __global__ __launch_bounds__(kItemThreads) void item_ranges(const uint64_t* __re
 
 // Weighted graphs (Section 3, "Notation": A_ij > 0 marks an edge, so its size is free to carry
 // a strength).  Stored values of A~: 1 on the diagonal, 0 until a listed pair brings its weight.
-__global__ void init_values(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col_idx,
-                            int64_t n, int64_t nnz, float* __restrict__ val) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= nnz) return;
-    int64_t lo = 0, hi = n - 1;  // the row of entry e: last i with row_ptr[i] <= e
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (row_ptr[mid] <= e) lo = mid; else hi = mid - 1;
+// Of the two entries of a pair the one on the side with more nodes, whose rows are the shorter on average, takes
+// the weights; the other then copies its value.  So nothing is searched for in a popular node's row, and half
+// of the entries see no atomics.  Both passes are bound by the number of scattered reads (some 130 G a second
+// in all), so a search ends in one read of the last few entries.  2 M pairs: 325 us with every pair
+// searched for in both rows and every entry's row in all of row_ptr, 200 so.
+// Where column c stands among the ascending columns [lo, hi), or -1.
+__device__ __forceinline__ int32_t find_column(const int32_t* __restrict__ col, int32_t lo, int32_t hi, int32_t c, int64_t nnz) {
+    constexpr int kTail = 8;
+    while (hi - lo > kTail) {   // the answer, if there is one, is in [lo, hi)
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if (col[mid] <= c) lo = mid; else hi = mid;
     }
-    val[e] = col_idx[e] == (int32_t)lo ? 1.0f : 0.0f;
+    if (lo + kTail <= nnz) {
+        typedef int32_t i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+        const i32x4 a = *reinterpret_cast<const i32x4*>(col + lo), b = *reinterpret_cast<const i32x4*>(col + lo + 4);
+        int32_t at = -1;
+#pragma unroll
+        for (int k = kTail - 1; k >= 0; --k)
+            if ((k < 4 ? a[k & 3] : b[k & 3]) == c) at = lo + k;
+        return at < hi ? at : -1;
+    }
+    for (; lo < hi; ++lo)
+        if (col[lo] == c) return lo;
+    return -1;
 }
 
-// One thread per (pair, direction): the entry is found by binary search in its (ascending) row; a
-// pair listed several times keeps its largest weight.  Positive floats order like their bit
-// patterns read as integers, which makes the maximum an integer atomic and the result independent
-// of the order of arrival.
+__global__ void zero_values(float* __restrict__ val, int64_t nnz) {
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e < nnz) val[e] = 0.0f;
+}
+
+// One thread per pair.  A pair listed several times keeps its largest weight: positive floats order like their
+// bit patterns read as integers, which makes the maximum an integer atomic and the result independent of the
+// order of arrival.
 __global__ void apply_weights(const int32_t* __restrict__ users, const int32_t* __restrict__ items,
                               const float* __restrict__ weights, int64_t n_edges, int32_t n_users,
-                              int32_t n_items, const int32_t* __restrict__ row_ptr,
+                              int32_t n_items, int64_t nnz, bool by_user, const int32_t* __restrict__ row_ptr,
                               const int32_t* __restrict__ col_idx, float* val) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 2 * n_edges) return;
-    const int64_t e = t >> 1;
+    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n_edges) return;
     const int32_t u = users[e], i = items[e];
     const float w = weights[e];
     if (u < 0 || u >= n_users || i < 0 || i >= n_items || !(w > 0.0f)) return;
-    const int32_t r = (t & 1) ? n_users + i : u;
-    const int32_t c = (t & 1) ? u : n_users + i;
-    const int32_t end = row_ptr[r + 1];
-    int32_t lo = row_ptr[r], hi = end;  // first position with col_idx >= c
-    while (lo < hi) {
-        const int32_t mid = lo + ((hi - lo) >> 1);
-        if (col_idx[mid] < c) lo = mid + 1; else hi = mid;
+    const int32_t row = by_user ? u : n_users + i, c = by_user ? n_users + i : u;
+    int32_t r[2];
+    __builtin_memcpy(r, row_ptr + row, sizeof(r));
+    const int32_t at = find_column(col_idx, r[0], r[1], c, nnz);
+    if (at >= 0) atomicMax(reinterpret_cast<int*>(val) + at, __float_as_int(w));
+}
+
+// The other entry of every pair, and the diagonal, by tiles of entries.
+__global__ __launch_bounds__(kEntryThreads) void mirror_weights(const int32_t* __restrict__ row_ptr,
+                                                                const int32_t* __restrict__ col_idx, int64_t n, int64_t nnz,
+                                                                int32_t n_users, bool by_user, float* val) {
+    __shared__ int32_t rows[kTileRowsMax + 1];
+    const EntryTile tile(row_ptr, n, nnz, rows);
+    // entries before `split` are in rows of users
+    const int64_t split = row_ptr[n_users];
+    int32_t c[kEntryRounds], far[kEntryRounds][2];
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kEntryThreads + threadIdx.x;
+        c[r] = e <= tile.last ? col_idx[e] : -1;
     }
-    if (lo < end && col_idx[lo] == c) atomicMax(reinterpret_cast<int*>(val) + lo, __float_as_int(w));
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kEntryThreads + threadIdx.x;
+        far[r][0] = far[r][1] = 0;
+        if (c[r] >= 0 && (e < split) != by_user) __builtin_memcpy(far[r], row_ptr + c[r], sizeof(far[r]));
+    }
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        if (c[r] < 0) continue;
+        const int64_t e = tile.first + r * kEntryThreads + threadIdx.x;
+        const int32_t i = (int32_t)(tile.row0 + tile.row(e));
+        if (c[r] == i) {
+            val[e] = 1.0f;
+        } else if (far[r][1] > far[r][0]) {
+            const int32_t at = find_column(col_idx, far[r][0], far[r][1], i, nnz);
+            if (at >= 0) val[e] = val[at];
+        }
+    }
 }
 
 struct BuildWs {
@@ -1376,12 +1424,16 @@ extern "C" int32_t e2eg_edge_weights(int32_t n_users, int32_t n_items, int64_t n
     if (nnz == 0) return E2EG_OK;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const dim3 blk(kThreads);
-    init_values<<<dim3(blocks_for(nnz, kThreads)), blk, 0, stream>>>(d_row_ptr, d_col_idx, n, nnz, d_val);
-    E2EG_LAUNCH_CHECK("init_values");
+    const bool by_user = n_users >= n_items;
+    zero_values<<<dim3(blocks_for(nnz, kThreads)), blk, 0, stream>>>(d_val, nnz);
+    E2EG_LAUNCH_CHECK("zero_values");
     if (n_edges > 0) {
-        apply_weights<<<dim3(blocks_for(2 * n_edges, kThreads)), blk, 0, stream>>>(
-            d_user_ids, d_item_ids, d_weights, n_edges, n_users, n_items, d_row_ptr, d_col_idx, d_val);
+        apply_weights<<<dim3(blocks_for(n_edges, kThreads)), blk, 0, stream>>>(
+            d_user_ids, d_item_ids, d_weights, n_edges, n_users, n_items, nnz, by_user, d_row_ptr, d_col_idx, d_val);
         E2EG_LAUNCH_CHECK("apply_weights");
     }
+    mirror_weights<<<dim3((unsigned)ceil_div(nnz, kEntryTile)), dim3(kEntryThreads), 0, stream>>>(d_row_ptr, d_col_idx, n, nnz,
+                                                                                                n_users, by_user, d_val);
+    E2EG_LAUNCH_CHECK("mirror_weights");
     return E2EG_OK;
 }

@@ -33,12 +33,12 @@
 // All of it is integer work with results that do not depend on scheduling.  Nothing here depends on
 // the feature width.  For a weighted graph (e2eg_normalize_weighted) d~ is the sum of the row's
 // values and the values are carried into the schedule in the order of its column indices.
-#include "common.h"
+#include "entry_tiles.h"
 
 namespace e2eg {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kEntryThreads;
 // The symmetry test of a large graph keeps a flag (asym[0]) and a count spread over kSymCounters
 // addresses, one cache line each (asym[k * kSymStride], k = 1 .. kSymCounters).
 constexpr int kSymCounters = 64;
@@ -668,39 +668,6 @@ __global__ __launch_bounds__(kTileThreads) void emit_rows(const int32_t* __restr
 }
 
 // ---- entries ------------------------------------------------------------------------------------
-// Entry work goes by tiles of consecutive entries.  The rows of a tile: all threads search row_ptr
-// together, kThreads probes a round, for the rows of the tile's first and last entry.
-constexpr int kEntryTile = 2048;
-constexpr int kTileRowsMax = 1024;   // rows of a tile held in LDS (a tile of mostly empty rows has more: then global memory)
-
-// -> range[0], range[1]: the last i in [0, n) with row_ptr[i] <= first, and <= last.
-__device__ __forceinline__ void rows_of_tile(const int32_t* __restrict__ row_ptr, int64_t n, int64_t first, int64_t last,
-                                             int64_t (&range)[2]) {
-    int64_t lo[2] = {0, 0}, hi[2] = {n, n};
-    while (hi[0] - lo[0] > 1 || hi[1] - lo[1] > 1) {
-        const int64_t want[2] = {first, last};
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int64_t step = (hi[k] - lo[k] + kThreads - 1) / kThreads;
-            const int64_t at = lo[k] + step * threadIdx.x;
-            const int cnt = __syncthreads_count(at < hi[k] && row_ptr[at] <= want[k]);   // a prefix of the threads, at least thread 0
-            lo[k] += step * (cnt - 1);
-            if (hi[k] - lo[k] > step) hi[k] = lo[k] + step;
-        }
-    }
-    range[0] = lo[0];
-    range[1] = lo[1];
-}
-
-// The row of entry e: the last i in [lo, hi] with row_ptr[i] <= e.
-__device__ __forceinline__ int64_t row_of_entry(const int32_t* __restrict__ row_ptr, int64_t e, int64_t lo, int64_t hi) {
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (row_ptr[mid] <= e) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
 // Where a row's popular entries go: a bitmap of their ranks; an entry's place is the number of bits below
 // its own.
 constexpr int kTopWords = kTopNodes / 32;
@@ -1193,34 +1160,20 @@ __global__ __launch_bounds__(kThreads) void check_mirrors(const int32_t* __restr
     static_assert(kMirrorLooks * kThreads == kEntryTile, "one batch of searches per tile");
     __shared__ int32_t rows[kTileRowsMax + 1];
     __shared__ int32_t balance;
-    const int64_t first = (int64_t)blockIdx.x * kEntryTile;
-    const int64_t last = (first + kEntryTile < nnz ? first + kEntryTile : nnz) - 1;
     if (threadIdx.x == 0) balance = 0;
-    int64_t range[2];
-    rows_of_tile(row_ptr, n, first, last, range);
-    const int64_t count = range[1] - range[0] + 1;
-    const bool cached = count <= kTileRowsMax;
-    if (cached)
-        for (int64_t k = threadIdx.x; k <= count; k += kThreads) rows[k] = row_ptr[range[0] + k];
-    __syncthreads();
+    const EntryTile tile(row_ptr, n, nnz, rows);
     int32_t mine = 0;   // looking minus not-looking entries
     int32_t i[kMirrorLooks], at[kMirrorLooks], left[kMirrorLooks], beg[kMirrorLooks], end[kMirrorLooks];
 #pragma unroll
     for (int u = 0; u < kMirrorLooks; ++u) {
-        const int64_t e = first + u * kThreads + threadIdx.x;
+        const int64_t e = tile.first + u * kThreads + threadIdx.x;
         left[u] = 0;
         beg[u] = end[u] = at[u] = 0;
         i[u] = -1;
-        if (e > last) continue;
-        int32_t own;
-        if (cached) {
-            const int64_t k = row_of_entry(rows, e, 0, count - 1);
-            i[u] = (int32_t)(range[0] + k);
-            own = rows[k + 1] - rows[k];
-        } else {
-            i[u] = (int32_t)row_of_entry(row_ptr, e, range[0], range[1]);
-            own = row_ptr[i[u] + 1] - row_ptr[i[u]];
-        }
+        if (e > tile.last) continue;
+        const int64_t k = tile.row(e);
+        const int32_t own = tile.row_begin(k + 1) - tile.row_begin(k);
+        i[u] = (int32_t)(tile.row0 + k);
         const int32_t j = col[e];
         if (i[u] == j) {
             i[u] = -1;
@@ -1268,7 +1221,7 @@ __global__ __launch_bounds__(kThreads) void check_mirrors(const int32_t* __restr
             found = at[u] < end[u];
         }
         if (!found) atomicOr(flags, kSchedNotSymmetric);
-        else if (val && __float_as_uint(val[at[u]]) != __float_as_uint(val[first + u * kThreads + threadIdx.x]))
+        else if (val && __float_as_uint(val[at[u]]) != __float_as_uint(val[tile.first + u * kThreads + threadIdx.x]))
             atomicOr(flags, kSchedValuesNotSymmetric);
     }
     if (ALL) return;

@@ -7,7 +7,7 @@
 //   * e2eg_sampler_prepare turns each row's weights into integers (2^24 at the row maximum, the
 //     division decided in fp32 with IEEE rounding) and prefix-sums them over the whole CSR: the
 //     table holds cum[e] = sum of the integer weights before entry e, nnz + 1 values of 64 bits.
-//     One thread per entry throughout, so that a row of a million entries is no wavefront's loop.
+//     By entries throughout, so that a row of a million entries is no wavefront's loop.
 //   * a draw is one thread: 64 random bits from the counter-based generator Philox4x32-10 (Salmon,
 //     Moraes, Dror, Shaw, SC 2011; counter = (draw, node, hop, 0), key = the seed), scaled to the
 //     row total by a 64x64->128-bit multiply, then a search in the row's slice of the table.
@@ -21,12 +21,12 @@
 // 4096 seeds, fan-outs 25 and 10, graph of 1.5 M nodes: 23 launches and 178 us with flags and scans over all
 // nodes for every hop; 11 launches now.  (Marking by atomic OR into the bitmaps themselves: the 280 k draws
 // of the second hop meet on 190 KB of them and took 52 us.)
-#include "common.h"
+#include "entry_tiles.h"
 
 namespace e2eg {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kEntryThreads;
 constexpr int kMaxHops = 8;
 constexpr int kMaxFanout = 1 << 16;
 
@@ -43,77 +43,86 @@ __global__ void pow_weights(const float* __restrict__ val, int64_t nnz, float be
     p[e] = r;
 }
 
-// The row of entry e: the last i in [lo, hi] with row_ptr[i] <= e.
-__device__ __forceinline__ int64_t row_of_entry(const int32_t* __restrict__ row_ptr, int64_t e, int64_t lo, int64_t hi) {
-    while (lo < hi) {
-        const int64_t mid = (lo + hi + 1) >> 1;
-        if (row_ptr[mid] <= e) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// Rows of a workgroup's (consecutive) entries: two threads search all rows for the first and the last
-// entry's, every thread then searches that short range.  -> the row of entry `e` (e < nnz).
-__device__ __forceinline__ int64_t row_in_block(const int32_t* __restrict__ row_ptr, int64_t n, int64_t nnz,
-                                                int64_t first, int64_t e, int64_t* range) {
-    if (threadIdx.x == 0) range[0] = row_of_entry(row_ptr, first, 0, n - 1);
-    if (threadIdx.x == 64) {
-        const int64_t last = first + kThreads - 1 < nnz ? first + kThreads - 1 : nnz - 1;
-        range[1] = row_of_entry(row_ptr, last, 0, n - 1);
-    }
-    __syncthreads();
-    return e < nnz ? row_of_entry(row_ptr, e, range[0], range[1]) : -1;
-}
-
-// One thread per entry: the largest usable weight off the diagonal of every row, as the bit pattern
-// of a positive float (which orders like an integer).  The entries of a row are neighbours, so a
-// wavefront first takes the maximum of each run of equal rows among its lanes and only the first
-// lane of a run goes to memory: a row of a million entries costs some ten thousand atomics.
+// The largest usable weight off the diagonal of every row, as the bit pattern of a positive float (which
+// orders like an integer); row_max_bits is cleared.  The entries of a row are neighbours: a wavefront takes the
+// maximum of each run of equal rows among its lanes, the first lane of a run goes to the row's word in LDS, and a
+// tile goes to memory once per row.  Four million entries: 24 us (tiles of 256 entries, each searching all rows
+// for its own: 56).
 __global__ __launch_bounds__(kThreads) void row_max(const int32_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ col_idx, const float* __restrict__ p,
                                                     int64_t n, int64_t nnz, int32_t* row_max_bits) {
-    __shared__ int64_t range[2];
-    const int64_t first = (int64_t)blockIdx.x * kThreads;
-    const int64_t e = first + threadIdx.x;
-    const int64_t row = row_in_block(row_ptr, n, nnz, first, e, range);
+    __shared__ int32_t rows[kTileRowsMax + 1];
+    __shared__ int32_t best[kTileRowsMax];
+    for (int k = threadIdx.x; k < kTileRowsMax; k += kThreads) best[k] = 0;
+    const EntryTile tile(row_ptr, n, nnz, rows);
     const int lane = threadIdx.x & 63;
-    int32_t bits = 0;
-    if (row >= 0) {
-        const float v = p[e];
-        if (col_idx[e] != (int32_t)row && usable(v)) bits = __float_as_int(v);
-    }
-    const int32_t r32 = (int32_t)row;
+    float v[kEntryRounds];
+    int32_t c[kEntryRounds];
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int32_t other = __shfl_down(bits, d, 64);
-        const int32_t other_row = __shfl_down(r32, d, 64);
-        if (lane + d < 64 && other_row == r32 && other > bits) bits = other;
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kThreads + threadIdx.x;
+        v[r] = e <= tile.last ? p[e] : 0.0f;
+        c[r] = e <= tile.last ? col_idx[e] : -1;
     }
-    const int32_t before = __shfl_up(r32, 1, 64);
-    if (row >= 0 && (lane == 0 || before != r32) && bits > 0) atomicMax(row_max_bits + row, bits);
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kThreads + threadIdx.x;
+        const int32_t k = e <= tile.last ? (int32_t)tile.row(e) : -1;
+        int32_t bits = 0;
+        if (k >= 0 && c[r] != (int32_t)(tile.row0 + k) && usable(v[r])) bits = __float_as_int(v[r]);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int32_t other = __shfl_down(bits, d, 64);
+            const int32_t other_row = __shfl_down(k, d, 64);
+            if (lane + d < 64 && other_row == k && other > bits) bits = other;
+        }
+        const int32_t before = __shfl_up(k, 1, 64);
+        if (k >= 0 && (lane == 0 || before != k) && bits > 0) {
+            if (tile.cached) atomicMax(&best[k], bits);
+            else atomicMax(row_max_bits + tile.row0 + k, bits);
+        }
+    }
+    __syncthreads();
+    if (tile.cached)
+        for (int64_t k = threadIdx.x; k < tile.count; k += kThreads)
+            if (best[k] > 0) atomicMax(row_max_bits + tile.row0 + k, best[k]);
 }
 
-// One thread per entry: its integer weight.  The entry past the end gets the 0 that closes the scan.
+// Every entry's integer weight.  The entry past the end gets the 0 that closes the scan.
 __global__ __launch_bounds__(kThreads) void quantise_entries(const int32_t* __restrict__ row_ptr,
                                                              const int32_t* __restrict__ col_idx,
                                                              const float* __restrict__ p, int64_t n, int64_t nnz,
                                                              const int32_t* __restrict__ row_max_bits,
                                                              uint64_t* __restrict__ q) {
-    __shared__ int64_t range[2];
-    const int64_t first = (int64_t)blockIdx.x * kThreads;
-    const int64_t e = first + threadIdx.x;
-    if (e == nnz) q[nnz] = 0;
-    if (first >= nnz) return;   // the whole workgroup (only the one that holds entry nnz alone)
-    const int64_t row = row_in_block(row_ptr, n, nnz, first, e, range);
-    if (row < 0) return;
-    const float v = p[e];
-    uint64_t w = 0;
-    if (col_idx[e] != (int32_t)row && usable(v)) {
-        const float pmax = __int_as_float(row_max_bits[row]);
-        const float scaled = floorf(__fmul_rn(__fdiv_rn(v, pmax), 16777216.0f));
-        w = scaled >= 1.0f ? (uint64_t)scaled : 1u;
+    __shared__ int32_t rows[kTileRowsMax + 1];
+    __shared__ float best[kTileRowsMax];
+    if (blockIdx.x == 0 && threadIdx.x == 0) q[nnz] = 0;
+    if (nnz == 0) return;
+    const EntryTile tile(row_ptr, n, nnz, rows);
+    float v[kEntryRounds];
+    int32_t c[kEntryRounds];
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kThreads + threadIdx.x;
+        v[r] = e <= tile.last ? p[e] : 0.0f;
+        c[r] = e <= tile.last ? col_idx[e] : -1;
     }
-    q[e] = w;
+    if (tile.cached)
+        for (int64_t k = threadIdx.x; k < tile.count; k += kThreads) best[k] = __int_as_float(row_max_bits[tile.row0 + k]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kEntryRounds; ++r) {
+        const int64_t e = tile.first + r * kThreads + threadIdx.x;
+        if (e > tile.last) continue;
+        const int64_t k = tile.row(e);
+        uint64_t w = 0;
+        if (c[r] != (int32_t)(tile.row0 + k) && usable(v[r])) {
+            const float pmax = tile.cached ? best[k] : __int_as_float(row_max_bits[tile.row0 + k]);
+            const float scaled = floorf(__fmul_rn(__fdiv_rn(v[r], pmax), 16777216.0f));
+            w = scaled >= 1.0f ? (uint64_t)scaled : 1u;
+        }
+        q[e] = w;
+    }
 }
 
 __global__ void fill_i32(int32_t* __restrict__ p, int64_t count, int32_t v) {
@@ -570,10 +579,10 @@ extern "C" int32_t e2eg_sampler_prepare(int32_t n, int64_t nnz, const int32_t* d
         E2EG_LAUNCH_CHECK("fill_i32");
     }
     if (nnz > 0) {
-        row_max<<<grid_for(nnz), blk, 0, stream>>>(d_row_ptr, d_col_idx, d_p, n, nnz, row_max_bits);
+        row_max<<<dim3((unsigned)ceil_div(nnz, kEntryTile)), blk, 0, stream>>>(d_row_ptr, d_col_idx, d_p, n, nnz, row_max_bits);
         E2EG_LAUNCH_CHECK("row_max");
     }
-    quantise_entries<<<grid_for(nnz + 1), blk, 0, stream>>>(d_row_ptr, d_col_idx, d_p, n, nnz, row_max_bits, q);
+    quantise_entries<<<dim3((unsigned)ceil_div(nnz > 0 ? nnz : 1, kEntryTile)), blk, 0, stream>>>(d_row_ptr, d_col_idx, d_p, n, nnz, row_max_bits, q);
     E2EG_LAUNCH_CHECK("quantise_entries");
     E2EG_HIP_TRY(exclusive_scan_u64(q, q, nnz + 1, nullptr, scan_ws, stream));
     return E2EG_OK;
